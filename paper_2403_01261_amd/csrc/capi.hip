@@ -3,9 +3,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <cstddef>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -148,6 +151,12 @@ struct Scratch {
   int64_t gcols_cap = -1, gw_cap = -1, goff_cap = -1, batch_glab_cap = -1;
   int32_t *gcols = nullptr;
   uint32_t *gw = nullptr;
+  // small graphs: the slots and release word of the workgroups' meetings, the
+  // number of the last launch on them, and what a launch reports (pinned host
+  // memory; device memory in the no-alloc scratch)
+  unsigned long long *small_sync = nullptr;
+  uint32_t small_epoch = 0;
+  gsl::SmallResult *small_result = nullptr;
 };
 
 }  // namespace
@@ -275,6 +284,8 @@ void free_scratch(Scratch &s) {
   hipFree(s.goff);
   hipFree(s.gcols);
   hipFree(s.gw);
+  hipFree(s.small_sync);
+  if (s.small_result) hipHostFree(s.small_result);
   hipFree(s.old2new);
   hipFree(s.lab2);
   hipFree(s.minorig);
@@ -610,6 +621,220 @@ struct Launch {
   size_t ev;
 };
 
+// ---- small graphs: the whole call in one launch (small.hip) ----
+// Vertices up to which a call runs as one launch.
+constexpr int64_t kSmallMaxVertices = int64_t(1) << 18;
+constexpr int64_t kSmallMaxEntries = int64_t(1) << 24;
+constexpr int64_t kSmallMaxGraphs = 4096;
+// Ticks (100 MHz) after which a workgroup's wait for the others gives up: 1 s,
+// unless GSL_SMALL_WAIT_TICKS says otherwise when the library is first used.
+long long small_wait_ticks() {
+  static const long long ticks = [] {
+    const char *e = getenv("GSL_SMALL_WAIT_TICKS");
+    return e ? atoll(e) : 100000000ll;
+  }();
+  return ticks;
+}
+constexpr int64_t kSmallSyncWords = gsl::kSmallGrid + 32;  // the release word on a cache line of its own
+constexpr int64_t kSmallRecBytes = (int64_t)gsl::kSmallMaxSweeps * gsl::kSmallGrid * 8;
+constexpr int64_t kSmallTierRecBytes = (int64_t)gsl::kSmallGrid * gsl::kNumTiers * gsl::kSmallTierFields * 4;
+static_assert(kSmallRecBytes + kSmallTierRecBytes + (int64_t)gsl::kSmallGrid * 8 <=
+                  (int64_t)gsl::kNumTiers * gsl::kMaxTierGrid * gsl::kCountFields * 8,
+              "the small-graph records fit the tier records' buffer");
+
+// Workgroups of small-graph launches in flight per device (a weighted one
+// counts twice, for its registers).  They wait for each other, so together
+// they must fit the device: a call that would pass kSmallGrid takes the
+// general path instead.
+constexpr int kMaxDevices = 64;
+std::atomic<int> g_small_blocks[kMaxDevices];
+
+struct SmallSlots {  // the share of one call, given back when it returns
+  int dev = -1, blocks = 0;
+  bool take(int device, int want) {
+    if (device < 0 || device >= kMaxDevices) return false;
+    if (g_small_blocks[device].fetch_add(want) + want > gsl::kSmallGrid) {
+      g_small_blocks[device].fetch_sub(want);
+      return false;
+    }
+    dev = device;
+    blocks = want;
+    return true;
+  }
+  ~SmallSlots() {
+    if (blocks) g_small_blocks[dev].fetch_sub(blocks);
+  }
+};
+
+int ensure_small(Scratch &s, hipStream_t st) {
+  if (!s.fixed) {
+    if (!s.small_sync && dmalloc(&s.small_sync, kSmallSyncWords) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(GSL_ENOMEM, "device allocation failed");
+    }
+    if (!s.small_result && hipHostMalloc(reinterpret_cast<void **>(&s.small_result), sizeof(gsl::SmallResult),
+                                         hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      s.small_result = nullptr;
+      return fail(GSL_ENOMEM, "pinned host allocation failed");
+    }
+  }
+  // the words of a former launch carry its number, which comes again after
+  // 2^24 launches only
+  if (s.small_epoch == 0 || s.small_epoch == (1u << 24) - 1) {
+    HIP_TRY(gsl::launch_fill_u64(reinterpret_cast<uint64_t *>(s.small_sync), 0, kSmallSyncWords, st));
+    s.small_epoch = 0;
+  }
+  ++s.small_epoch;
+  return GSL_OK;
+}
+
+// Launches `a` (its graph, labels, flags, split arrays, batch and loop state
+// set) and waits; the meeting words, records and result are filled in here.
+// head receives the result without the statistics, which stay in
+// s.small_result when they were asked for.
+int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, gsl::SmallResult *head) {
+  int rc = ensure_small(s, st);
+  if (rc) return rc;
+  char *rec = reinterpret_cast<char *>(s.tier_part);
+  a.rec = reinterpret_cast<unsigned long long *>(rec);
+  a.heavy = reinterpret_cast<unsigned long long *>(rec + kSmallRecBytes);
+  a.tier_rec = reinterpret_cast<unsigned int *>(rec + kSmallRecBytes + (int64_t)gsl::kSmallGrid * 8);
+  a.slots = s.small_sync;
+  a.release = s.small_sync + gsl::kSmallGrid + 16;
+  a.epoch = s.small_epoch;
+  a.spin_limit = small_wait_ticks();
+  a.result = s.small_result;
+  a.max_nnz = kSmallMaxEntries;
+  const gsl::TierConfig cfg = gsl::kDefaultTiers;
+  for (int t = 0; t < gsl::kNumTiers; ++t) a.tiers.b[t] = cfg.bound[t];
+  constexpr size_t kHead = offsetof(gsl::SmallResult, tier);
+  if (!s.fixed) {
+    s.small_result->status = gsl::kSmallPending;
+    s.small_result->aborted = 0;
+  }
+  HIP_TRY(gsl::launch_small(a, st));
+  if (s.fixed) HIP_TRY(hipMemcpyAsync(head, s.small_result, kHead, hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  if (!s.fixed) memcpy(head, s.small_result, kHead);
+  if (head->aborted == a.epoch) head->status = gsl::kSmallAborted;
+  if (head->status == gsl::kSmallPending) return fail(GSL_EDEVICE, "the small-graph kernel reported nothing");
+  return GSL_OK;
+}
+
+// Result arrays of a batch: local ids, scattered to the graphs' own outputs,
+// sweep counts and flags.
+int finish_batch(Scratch &s, hipStream_t st, const Batch *batch, int64_t n, int32_t *labels_out) {
+  HIP_TRY(gsl::launch_localize(labels_out, batch->vtx_base, batch->graphs, n, st));
+  if (batch->scatter)
+    HIP_TRY(gsl::launch_scatter_labels(batch->scatter, labels_out, batch->vtx_base, batch->flags,
+                                       batch->graphs, n, st));
+  if (batch->flags_host)
+    HIP_TRY(hipMemcpyAsync(batch->flags_host, batch->flags, (size_t)batch->graphs * sizeof(uint32_t),
+                           hipMemcpyDeviceToHost, st));
+  if (batch->iters_dev)
+    HIP_TRY(hipMemcpyAsync(batch->iters_dev, s.giters, (size_t)batch->graphs * sizeof(int32_t),
+                           hipMemcpyDeviceToDevice, st));
+  if (batch->iters_host)
+    HIP_TRY(hipMemcpyAsync(batch->iters_host, s.giters, (size_t)batch->graphs * sizeof(int32_t),
+                           hipMemcpyDeviceToHost, st));
+  return GSL_OK;
+}
+
+constexpr int kGeneral = 2;  // small_impl: run the general path
+
+bool is_default_tiers(const gsl::TierConfig &c) {
+  for (int t = 0; t < gsl::kNumTiers; ++t)
+    if (c.bound[t] != gsl::kDefaultTiers.bound[t] || c.variant[t] != gsl::kDefaultTiers.variant[t]) return false;
+  return true;
+}
+
+// A call on a small graph or batch in one launch; kGeneral where the general
+// path has to run it (nothing but scratch and outputs has been written then).
+int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
+               int64_t n, int32_t max_iters, double tolerance, const gsl_options &o, gsl_stats *stats,
+               int32_t *labels_out, const Batch *batch) {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  const int grid = gsl::small_grid(n, weights != nullptr, batch != nullptr);
+  SmallSlots share;
+  if (!share.take(dev, weights ? 2 * grid : grid)) return kGeneral;
+  gsl::SmallArgs a;
+  memset(&a, 0, sizeof(a));
+  a.off = offsets;
+  a.cols = cols;
+  a.w = weights;
+  a.n = n;
+  a.lab[0] = labels_out;
+  a.lab[1] = s.Cn;
+  a.act[0] = s.act[0];
+  a.act[1] = s.act[1];
+  a.parent = s.parent;
+  a.rep = s.rep;
+  a.cp = s.sigma;
+  a.out = labels_out;
+  a.ctrl.max_iters = max_iters;
+  a.ctrl.graph_max_iters = max_iters;
+  a.ctrl.prune = o.prune ? 1 : 0;
+  a.ctrl.limit = gsl_convergence_limit(n, tolerance);
+  a.ctrl.n = n;
+  a.ctrl.dense = 1;
+  a.init = 1;
+  a.split = o.split ? 1 : 0;
+  a.stats = stats ? 1 : 0;
+  a.layout_auto = o.layout == 0 ? 1 : 0;
+  if (batch) {
+    HIP_TRY(gsl::launch_batch_init(batch->vtx_base, batch->graphs, max_iters, tolerance, s.gid, s.glimit,
+                                   s.giters, s.gdone, s.gdn, st));
+    a.ctrl.graphs = batch->graphs;
+    a.gid = s.gid;
+    a.gdone = s.gdone;
+    a.gdn = s.gdn;
+    a.glimit = s.glimit;
+    a.giters = s.giters;
+    a.graphs = batch->graphs;
+  }
+  gsl::SmallResult head;
+  int rc = run_small(s, st, a, &head);
+  if (rc) return rc;
+  if (head.status == gsl::kSmallDeclined || head.status == gsl::kSmallAborted) return kGeneral;
+  if (head.status == gsl::kSmallBadStart)
+    return fail(GSL_EINVAL, "offsets[0] must be 0 (got %lld)", (long long)head.first_offset);
+  if (head.status == gsl::kSmallBadEnd) return fail(GSL_EINVAL, "offsets[n] must be >= 0");
+  if (head.status == gsl::kSmallNoCols) return fail(GSL_EINVAL, "cols must not be NULL when offsets[n] > 0");
+  if (batch) {
+    if ((rc = finish_batch(s, st, batch, n, labels_out))) return rc;
+    HIP_TRY(hipStreamSynchronize(st));
+  }
+  if (head.ctrl.error)
+    return fail(GSL_EOVERFLOW, "a vertex's summed row weight reaches 2^32; weights are summed in 32 bits");
+  if (stats) {
+    const gsl::SmallResult &r = *s.small_result;
+    const int32_t it = head.ctrl.it;
+    stats->iterations = it;
+    stats->split_rounds = o.split ? 1 : 0;
+    stats->nnz = head.nnz;
+    stats->max_degree = r.tier[0][0];
+    for (int k = 0; k < it && k < GSL_STATS_MAX_ITERS; ++k) {
+      stats->changed[k] = r.changed[k];
+      stats->processed[k] = r.processed[k];
+      stats->edges[k] = r.edges[k];
+      stats->marked[k] = r.marked[k];
+    }
+    for (int t = 0; t < gsl::kNumTiers; ++t) {
+      stats->tier_vertices[t] = r.tier[t][4];
+      if (t == 0 || r.tier[t][4] <= 0) continue;
+      stats->tier_processed[t] = r.tier[t][0];
+      stats->tier_edges[t] = r.tier[t][1];
+      stats->tier_changed[t] = r.tier[t][2];
+      stats->tier_marked[t] = r.tier[t][3];
+      stats->tier_launches[t] = it;
+      for (int k = 1; k < it; ++k) stats->tier_sparse[t] += o.prune && r.marked[k - 1] ? 1 : 0;
+    }
+  }
+  return GSL_OK;
+}
+
 // f32: `weights` holds fp32 values (summed in fp64) instead of uint32.
 int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
              int64_t n, int32_t max_iters, double tolerance, const gsl_options *opt, gsl_stats *stats,
@@ -629,6 +854,12 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   // bounds only)
   const gsl::TierConfig cfg = f32 ? gsl::kF32Tiers : current_tiers();
   const HubLimits hub_lim = current_hub_limits();
+  if (n <= kSmallMaxVertices && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
+      !o.async_sweeps && o.layout != 1 && (!batch || batch->graphs <= kSmallMaxGraphs) &&
+      is_default_tiers(cfg)) {
+    rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch);
+    if (rc != kGeneral) return rc;
+  }
   if (o.timing) {
     if (s.fixed) return fail(GSL_EINVAL, "timing is not available without allocation");
     if ((rc = ensure_events(s))) return rc;
@@ -958,21 +1189,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     HIP_TRY(gsl::launch_split(offsets, cols, n, C, s.parent, labels_out, s.list, plan.tier_count,
                               plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, cfg, st));
   }
-  if (batch) {
-    HIP_TRY(gsl::launch_localize(labels_out, batch->vtx_base, batch->graphs, n, st));
-    if (batch->scatter)
-      HIP_TRY(gsl::launch_scatter_labels(batch->scatter, labels_out, batch->vtx_base, batch->flags,
-                                         batch->graphs, n, st));
-    if (batch->flags_host)
-      HIP_TRY(hipMemcpyAsync(batch->flags_host, batch->flags, (size_t)batch->graphs * sizeof(uint32_t),
-                             hipMemcpyDeviceToHost, st));
-    if (batch->iters_dev)
-      HIP_TRY(hipMemcpyAsync(batch->iters_dev, s.giters, (size_t)batch->graphs * sizeof(int32_t),
-                             hipMemcpyDeviceToDevice, st));
-    if (batch->iters_host)
-      HIP_TRY(hipMemcpyAsync(batch->iters_host, s.giters, (size_t)batch->graphs * sizeof(int32_t),
-                             hipMemcpyDeviceToHost, st));
-  }
+  if (batch && (rc = finish_batch(s, st, batch, n, labels_out))) return rc;
   if (timed) HIP_TRY(hipEventRecord(s.ev[3], st));
   static_assert(sizeof(gsl::SweepCtrl) <= (kPinSmall - 2) * sizeof(int64_t), "loop state fits the pinned words");
   gsl::SweepCtrl *pfc = reinterpret_cast<gsl::SweepCtrl *>(s.pin + 2);
@@ -1087,7 +1304,8 @@ constexpr int64_t kNoAllocLayoutBytes =
     al256(8LL * GSL_NOALLOC_MAX_VERTICES) + al256(8 * kNoAllocPlanEntries) +  // sigma, plan counts
     3 * al256(8LL * (GSL_NOALLOC_MAX_HUBS + 1)) + 3 * al256(8LL * GSL_NOALLOC_MAX_HUBS) +
     2 * al256(4 * kNoAllocHubChunks) +
-    al256(8 * kNoAllocStagingPairs) + al256(4 * kNoAllocHistEntries);
+    al256(8 * kNoAllocStagingPairs) + al256(4 * kNoAllocHistEntries) +
+    al256(8 * kSmallSyncWords) + al256(sizeof(gsl::SmallResult));
 static_assert(kNoAllocLayoutBytes <= GSL_NOALLOC_SCRATCH_BYTES, "the no-alloc buffers fit the static scratch");
 
 struct NoAlloc {
@@ -1140,6 +1358,8 @@ int noalloc_setup(NoAlloc &na) {
   s.hub_staging_cap = kNoAllocStagingPairs;
   carve(&s.hub_hist, 4 * kNoAllocHistEntries);
   s.hub_hist_cap = kNoAllocHistEntries;
+  carve(&s.small_sync, 8 * kSmallSyncWords);
+  carve(&s.small_result, sizeof(gsl::SmallResult));
   if (used != kNoAllocLayoutBytes) return fail(GSL_EDEVICE, "no-alloc layout mismatch");
   // host side: pageable mirrors, and room for the hub layout vectors
   na.pin.assign((size_t)(kPinSmall + 3 * (GSL_NOALLOC_MAX_HUBS + 1)), 0);
@@ -1394,6 +1614,7 @@ int64_t graphs_bytes(int64_t n, int64_t nnz, int64_t graphs, bool weighted, int3
   b += (int64_t)sizeof(Counters) + 4 * 8 * (int64_t)(max_iters > 0 ? max_iters : 1) + (int64_t)sizeof(gsl::SweepCtrl);
   b += n * 4 + G * (4 + 8 + 8 + 1 + 8 + 8 + 8 + (int64_t)sizeof(gsl::GraphDesc) + 4) + 8;  // batch arrays
   b += (n + 1) * 8 + nnz * 4 * (weighted ? 2 : 1) + n * 4;                          // gathered CSR, labels
+  b += kSmallSyncWords * 8;
   return b + hub_bytes_bound(nnz);
 }
 
@@ -1411,6 +1632,7 @@ int64_t session_bytes(int64_t cap_v, int64_t cap_e, int64_t cap_g, bool weighted
   b += 2 * 4096 * 8 + (int64_t)gsl::kNumTiers * gsl::kMaxTierGrid * gsl::kCountFields * 8;  // partials, tier records
   b += (int64_t)sizeof(Counters) + 4 * 8 * (kSessionSweepCap + 2) + (int64_t)sizeof(gsl::SweepCtrl);
   b += cap_v * 4 + G * (4 + 8 + 8 + 1 + 8 + 8 + 8 + (int64_t)sizeof(gsl::GraphDesc) + 4) + 8;  // batch arrays
+  b += kSmallSyncWords * 8;
   return b + hub_bytes_bound(cap_e);
 }
 

@@ -194,6 +194,19 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long x) {
   return x;
 }
 
+// Sum of a 32-bit value over the wavefront with DPP moves (every lane must be
+// active; the result is uniform).  An LDS add of one address by many lanes
+// would be unrolled into a loop over the lanes instead.
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast 15, 31
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+
 // Block-wide sum; the result is valid in thread 0.  `red` needs
 // blockDim.x / 64 entries.  Contains __syncthreads.
 __device__ __forceinline__ unsigned long long block_sum(unsigned long long x,

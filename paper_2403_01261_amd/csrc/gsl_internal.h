@@ -188,6 +188,66 @@ struct TierGrids {
   int g[kNumTiers];
 };
 
+// ---- small graphs: the whole call in one launch (small.hip) ----
+constexpr int kSmallGrid = 1024;          // most workgroups of a launch (all resident at once)
+constexpr int64_t kSmallOne = 256;        // graphs up to here run in one workgroup, in LDS
+constexpr int kSmallMaxSweeps = 100;
+constexpr int kSmallMaxDegree = 2048;     // rows above: the general path
+constexpr int kSmallTierFields = 6;       // processed, edges, changed, marked; vertices, entries of the tier
+enum : int32_t {
+  kSmallPending = 0,
+  kSmallOk,
+  kSmallDeclined,   // a row, the entries or the layout rule call for the general path
+  kSmallAborted,    // a wait ran out
+  kSmallBadStart,   // offsets[0] != 0
+  kSmallBadEnd,     // offsets[n] < 0
+  kSmallNoCols      // entries but no columns
+};
+struct SmallResult {
+  int32_t status;
+  uint32_t aborted;   // the launch's epoch when a workgroup's wait ran out
+  int64_t first_offset, nnz;
+  SweepCtrl ctrl;   // the loop state after the last sweep
+  // statistics (SmallArgs::stats): tier[0][0] is the largest degree
+  int64_t tier[kNumTiers][kSmallTierFields];
+  int64_t changed[kSmallMaxSweeps], processed[kSmallMaxSweeps], edges[kSmallMaxSweeps], marked[kSmallMaxSweeps];
+};
+struct SmallArgs {
+  const int64_t *off;
+  const int32_t *cols;
+  const uint32_t *w;      // NULL: unit weights
+  int64_t n, max_nnz;
+  int32_t *lab[2];        // sweep t reads lab[t & 1] and writes the other
+  uint8_t *act[2];        // active flags, as in SweepArgs
+  int32_t *parent, *rep;  // split
+  unsigned long long *cp;
+  int32_t *out;           // labels out: split, or as they are after the last sweep
+  SweepCtrl ctrl;         // loop state before the first sweep
+  int32_t init;           // the call starts here: labels are the vertex ids, flags and parents are set up
+  int32_t split, stats;
+  int32_t layout_auto;    // decline graphs that the layout rule renumbers
+  TierBounds tiers;       // for the statistics
+  // batches (gdn NULL for a single graph)
+  const int32_t *gid;
+  uint8_t *gdone;
+  int64_t *gdn;
+  const int64_t *glimit;
+  int32_t *giters;
+  int64_t graphs;
+  // meetings of the workgroups
+  unsigned long long *slots, *release;
+  uint32_t epoch;         // 24 bits, another for each launch on these slots
+  long long spin_limit;   // ticks (100 MHz) after which a wait gives up
+  unsigned long long *rec;    // [kSmallMaxSweeps][kSmallGrid] processed, edges
+  unsigned int *tier_rec;     // [kSmallGrid][kNumTiers][kSmallTierFields]
+  unsigned long long *heavy;  // [kSmallGrid]
+  SmallResult *result;
+};
+// Workgroups of a launch on n vertices (at most kSmallGrid; half as many with
+// weights, whose rows need twice the registers), and the launch.
+int small_grid(int64_t n, bool weighted, bool batch);
+hipError_t launch_small(const SmallArgs &a, hipStream_t s);
+
 // ---- launchers (stream-ordered, no synchronisation) ----
 hipError_t launch_plan(const int64_t *off, int64_t n, int32_t *list, int64_t *blk_counts,
                        Counters *ctr, const TierConfig &cfg, hipStream_t s);
