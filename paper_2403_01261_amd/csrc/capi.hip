@@ -835,6 +835,42 @@ int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t
   return GSL_OK;
 }
 
+// The smallest thread-per-vertex variant for rows of up to `longest` entries
+// in place of a larger one; other variants stay.
+int thread_variant(int variant, int64_t longest) {
+  if (gsl::kVariants[variant].group != 1) return variant;
+  for (int v : {0, 15, 16})
+    if (gsl::variant_capacity(v) >= longest && gsl::variant_capacity(v) < gsl::variant_capacity(variant)) return v;
+  return variant;
+}
+
+// Cluster order (see launch_cluster_order): for graphs of short rows (at most
+// four entries a row on average, seven of eight rows in tier 1) whose
+// neighbours lie far apart in the caller's ids -- more than kClusterFar ids,
+// half an XCD's L2 of labels, for over half of a sample -- and whose sweeps
+// may repeat often enough to pay for the order and the copy, about three
+// sweeps' time.  Such graphs (roads, long paths) converge slowly.  Measured on
+// shuffled road graphs, original layout -> cluster order, 20 sweeps, ms per
+// call: 2 M vertices 2.23 -> 1.86, 4 M 4.62 -> 3.13, 12 M 15.1 -> 8.5, 24 M
+// 27.4 -> 16.8; below 2 M vertices the labels are near enough to L2's size.
+constexpr int64_t kClusterMinVertices = 2000000;
+constexpr int64_t kClusterFar = int64_t(1) << 19;
+constexpr int32_t kClusterMinSweeps = 8;
+
+int wants_clusters(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, int64_t n, int64_t nnz,
+                   int32_t max_iters, const Counters &plan, bool *wanted) {
+  *wanted = false;
+  const int64_t np = n - plan.tier_count[0];
+  if (n < kClusterMinVertices || max_iters < kClusterMinSweeps || nnz > 4 * np || 8 * plan.tier_count[1] < 7 * np)
+    return GSL_OK;
+  unsigned long long *out = reinterpret_cast<unsigned long long *>(&s.ctr->pad[0]);
+  HIP_TRY(gsl::launch_spread(offsets, cols, n, kClusterFar, out, st));
+  HIP_TRY(hipMemcpyAsync(s.pin, out, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  *wanted = s.pin[0] > 0 && 2 * s.pin[1] > s.pin[0];
+  return GSL_OK;
+}
+
 // f32: `weights` holds fp32 values (summed in fp64) instead of uint32.
 int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
              int64_t n, int32_t max_iters, double tolerance, const gsl_options *opt, gsl_stats *stats,
@@ -884,8 +920,16 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   int64_t heavy = 0;  // entries of the tiers whose rows all have degree > 64
   for (int t = 1; t < gsl::kNumTiers; ++t)
     if (cfg.bound[t - 1] >= 64) heavy += plan.tier_edges[t];
-  const bool renumber = !batch && (o.layout == 1 || (o.layout == 0 && 2 * heavy > nnz));
   const int64_t np = n - plan.tier_count[0];  // non-isolated vertices
+  bool renumber = !batch && (o.layout == 1 || (o.layout == 0 && 2 * heavy > nnz));
+  bool clustered = false;
+  if (!batch && o.layout == 0 && !renumber && (rc = wants_clusters(s, st, offsets, cols, n, nnz, max_iters, plan, &clustered)))
+    return rc;
+  if (clustered) {
+    // without memory for the copy the sweeps run on the caller's graph
+    renumber = ensure_copy(s, n, nnz, weights != nullptr) == GSL_OK;
+    clustered = renumber;
+  }
   const int64_t *g_off = offsets;
   const int32_t *g_cols = cols;
   const uint32_t *g_w = weights;
@@ -903,11 +947,14 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
         return fail(GSL_EDEVICE, "hipEventCreate failed");
       HIP_TRY(hipEventRecord(s.ev_reorder, st));
     }
+    if (clustered)
+      HIP_TRY(gsl::launch_cluster_order(offsets, cols, n, plan.tier_count, plan.tier_start, cfg.bound[1], s.parent,
+                                        s.rep, s.lab2, s.minorig, s.blk_counts, s.list, s.old2new, st));
     HIP_TRY(gsl::launch_reorder(offsets, cols, weights, n, s.list, plan.tier_count, plan.tier_start,
                                 s.hub_chunk_start, s.hub_chunk_owner, H > 0 ? s.h_chunk[(size_t)H] : 0, s.old2new, s.off2,
                                 s.cols2, weights ? s.w2 : nullptr, s.lab2, s.blk_counts, s.first_key,
                                 s.hub_rowsum, reinterpret_cast<unsigned long long *>(&s.ctr->first_flags),
-                                dn_arr, max_iters > 0 ? 1 : 0, cfg, st));
+                                dn_arr, max_iters > 0 ? 1 : 0, cfg, (int64_t)plan.max_degree, clustered, f32, st));
     g_off = s.off2;
     g_cols = s.cols2;
     g_w = weights ? s.w2 : nullptr;
@@ -985,6 +1032,12 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   a.flist = frontier ? s.parent : nullptr;
   const gsl::HubLayout L{s.hub_chunk_start, s.hub_part_start, s.hub_hist_start, s.hub_chunk_owner,
                          s.hub_part_owner, s.hub_records};
+  // The default table's short rows take the thread-per-vertex kernel of the
+  // graph's longest row: the kernel for 32 entries sorts 32 registers whatever
+  // the row holds (24 M road vertices, rows of 2 - 7 entries).
+  int variant[gsl::kNumTiers];
+  for (int t = 0; t < gsl::kNumTiers; ++t)
+    variant[t] = is_default_tiers(cfg) ? thread_variant(cfg.variant[t], (int64_t)plan.max_degree) : cfg.variant[t];
 
   // Timing records (timing mode only).
   std::vector<Launch> launches;
@@ -1040,7 +1093,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
         if (f32)
           HIP_TRY(gsl::launch_sweep_tier_f32(t, a, g_list, plan.tier_start[t], cnt, &grids.g[t], cur));
         else
-          HIP_TRY(gsl::launch_sweep_tier(cfg.variant[t], a, g_list, plan.tier_start[t], cnt, &grids.g[t], cur));
+          HIP_TRY(gsl::launch_sweep_tier(variant[t], a, g_list, plan.tier_start[t], cnt, &grids.g[t], cur));
       }
       if (timed && (rc = rec(nev++))) return rc;
     }
@@ -1110,7 +1163,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     for (int t = 0; t < gsl::kNumTiers; ++t) {
       key.push_back((uint64_t)plan.tier_count[t]);
       key.push_back((uint64_t)plan.tier_start[t]);
-      key.push_back((uint64_t)cfg.variant[t]);
+      key.push_back((uint64_t)variant[t]);
     }
     // Hub launches bake in their grid sizes (chunks and partitions of each
     // batch, all chunks for fp32 weights) and dynamic LDS (largest partition

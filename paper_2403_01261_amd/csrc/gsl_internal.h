@@ -424,7 +424,26 @@ hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_
                           int64_t *off2, int32_t *cols2, uint32_t *w2, int32_t *lab,
                           int64_t *scan_tmp, unsigned long long *first_key,
                           unsigned long long *hub_rowsum, unsigned long long *flags,
-                          unsigned long long *dn0, int apply_first, const TierConfig &cfg, hipStream_t s);
+                          unsigned long long *dn0, int apply_first, const TierConfig &cfg, int64_t max_degree,
+                          bool inverted, bool f32, hipStream_t s);
+// out[0] row entries of a sample of the vertices, out[1] those whose column
+// is more than `far` ids from its vertex.
+hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, int64_t far, unsigned long long *out,
+                         hipStream_t s);
+// Tier 1 of the list (rows of up to `longest` entries) in cluster order, and
+// the inverse of the whole list.  A cluster is a vertex that is the smallest
+// neighbour of its members or of theirs, so members are within four edges of
+// each other and a row's neighbours mostly share its cluster.  A wavefront of
+// 64 rows of a shuffled road graph then gathers its labels from 0.23 128-byte
+// lines per entry instead of 1.0 (24 M vertices: 1,210 -> 340 us per sweep, the
+// sort of 8 registers instead of 32 included).  The order costs 2.0 ms there (a gather and
+// an atomic per vertex, a scan, a gather and a scatter), the copy and the
+// scattered output 3.5 ms.  first, cluster,
+// rank and count are scratch of n entries each, scan_tmp of plan_blocks(n).
+hipError_t launch_cluster_order(const int64_t *off, const int32_t *cols, int64_t n, const int64_t *tier_count_h,
+                                const int64_t *tier_start_h, int64_t longest, int32_t *first, int32_t *cluster,
+                                int32_t *rank, int32_t *count, int64_t *scan_tmp, int32_t *list, int32_t *old2new,
+                                hipStream_t s);
 hipError_t launch_reorder_scatter(const int32_t *list, const int32_t *val, int64_t np, int64_t n,
                                   int32_t *out, hipStream_t s);
 hipError_t launch_check_labels(const int32_t *labels, int64_t n, unsigned long long *bad,

@@ -7,6 +7,10 @@
 // most label gathers -- into a few megabytes that stay in L2.  Labels keep
 // their original-id values, so the smallest-label tie-break and the output are
 // unchanged; only storage positions move.
+//
+// Graphs of short rows whose neighbours lie far apart in the caller's ids are
+// renumbered too, for another reason: every label gather of such a graph
+// misses L2 (see launch_cluster_order).
 #include "device_common.h"
 #include "gsl_internal.h"
 
@@ -16,9 +20,10 @@ namespace {
 
 constexpr int kScanBlock = 1024;
 
-__global__ void reorder_invert(const int32_t *__restrict__ list, int64_t n, int32_t *__restrict__ old2new) {
+__global__ void reorder_invert(const int32_t *__restrict__ list, int64_t first, int64_t end,
+                               int32_t *__restrict__ old2new) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride)
+  for (int64_t p = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < end; p += stride)
     old2new[list[p]] = (int32_t)p;
 }
 
@@ -37,7 +42,8 @@ __global__ void reorder_degrees(const int64_t *__restrict__ off, const int32_t *
 }
 
 // In-place inclusive scan of a[0..n): per-block scan, block totals to sums.
-__global__ __launch_bounds__(kScanBlock) void scan_local(int64_t *a, int64_t n, int64_t *sums) {
+template <class T>
+__global__ __launch_bounds__(kScanBlock) void scan_local(T *a, int64_t n, int64_t *sums) {
   __shared__ int64_t part[kScanBlock];
   const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
   part[threadIdx.x] = i < n ? a[i] : 0;
@@ -48,7 +54,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_local(int64_t *a, int64_t n, 
     part[threadIdx.x] += y;
     __syncthreads();
   }
-  if (i < n) a[i] = part[threadIdx.x];
+  if (i < n) a[i] = (T)part[threadIdx.x];
   if (threadIdx.x == kScanBlock - 1) sums[blockIdx.x] = part[kScanBlock - 1];
 }
 
@@ -75,15 +81,106 @@ __global__ __launch_bounds__(kScanBlock) void scan_sums(int64_t *sums, int64_t n
   }
 }
 
-__global__ __launch_bounds__(kScanBlock) void scan_add(int64_t *a, int64_t n, const int64_t *sums) {
+template <class T>
+__global__ __launch_bounds__(kScanBlock) void scan_add(T *a, int64_t n, const int64_t *sums) {
   const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-  if (i < n) a[i] += sums[blockIdx.x];
+  if (i < n) a[i] += (T)sums[blockIdx.x];
+}
+
+template <class T>
+void scan_inclusive(T *a, int64_t n, int64_t *sums, hipStream_t s) {
+  const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
+  scan_local<T><<<(unsigned)nb, kScanBlock, 0, s>>>(a, n, sums);
+  scan_sums<<<1, kScanBlock, 0, s>>>(sums, nb);
+  scan_add<T><<<(unsigned)nb, kScanBlock, 0, s>>>(a, n, sums);
+}
+
+// ---- cluster order of the short rows (launch_cluster_order) ----
+
+// Of up to kSpreadSamples vertices spread over the graph: entries seen (the
+// first and last of each row) and those more than `far` ids from their vertex.
+constexpr int64_t kSpreadSamples = 1 << 16;
+__global__ __launch_bounds__(256) void sample_spread(const int64_t *__restrict__ off, const int32_t *__restrict__ cols,
+                                                     int64_t n, int64_t samples, int64_t far,
+                                                     unsigned long long *out) {
+  __shared__ unsigned long long red[256 / kWave];
+  unsigned long long seen = 0, spread = 0;
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < samples) {
+    const int64_t v = (int64_t)((unsigned long long)k * (unsigned long long)n / (unsigned long long)samples);
+    const int64_t b = off[v], e = off[v + 1];
+    if (e > b) {
+      const int64_t x = cols[b], y = cols[e - 1];
+      seen = 2;
+      spread = (x > v ? x - v : v - x) > far;
+      spread += (y > v ? y - v : v - y) > far;
+    }
+  }
+  seen = block_sum(seen, red);
+  spread = block_sum(spread, red);
+  if (threadIdx.x == 0 && seen) {
+    atomicAdd(&out[0], seen);
+    atomicAdd(&out[1], spread);
+  }
+}
+
+// first[v] = smallest neighbour of v (v itself without one), count cleared.
+__global__ __launch_bounds__(256) void cluster_first(const int64_t *__restrict__ off,
+                                                     const int32_t *__restrict__ cols, int64_t n, int64_t longest,
+                                                     int32_t *__restrict__ first, int32_t *__restrict__ count) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+    const int64_t b = off[v], e = off[v + 1];
+    int32_t m = 0x7fffffff;
+    if (e - b <= longest)
+      for (int64_t p = b; p < e; ++p) {
+        const int32_t j = cols[p];
+        m = j != (int32_t)v && j < m ? j : m;
+      }
+    first[v] = m == 0x7fffffff ? (int32_t)v : m;
+    count[v] = 0;
+  }
+}
+
+// The cluster of v -- the smaller of its smallest neighbour and that one's --
+// and v's rank in it (any order will do).
+__global__ __launch_bounds__(256) void cluster_rank(const int64_t *__restrict__ off, int64_t n, int64_t longest,
+                                                    const int32_t *__restrict__ first, int32_t *__restrict__ cluster,
+                                                    int32_t *__restrict__ rank, int32_t *count) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+    const int64_t d = off[v + 1] - off[v];
+    if (d <= 0 || d > longest) {
+      cluster[v] = -1;
+      continue;
+    }
+    const int32_t m = first[v], mm = first[m], c = mm < m ? mm : m;
+    cluster[v] = c;
+    rank[v] = atomicAdd(&count[c], 1);
+  }
+}
+
+// Positions in the list and their inverse, for the short rows only; end[c] is
+// the end of cluster c among them.
+__global__ __launch_bounds__(256) void cluster_place(const int32_t *__restrict__ cluster,
+                                                     const int32_t *__restrict__ rank,
+                                                     const int32_t *__restrict__ end, int64_t n, int64_t start,
+                                                     int32_t *__restrict__ list, int32_t *__restrict__ old2new) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+    const int32_t c = cluster[v];
+    if (c < 0) continue;
+    const int64_t p = start + end[c] - 1 - rank[v];
+    list[p] = (int32_t)v;
+    old2new[v] = (int32_t)p;
+  }
 }
 
 struct CopyArgs {
   const int64_t *off;
   const int32_t *cols;
   const uint32_t *w;
+  bool f32;  // w holds floats: as bits they order like their values, but for a negative zero
   const int32_t *list;
   const int32_t *old2new;
   const int64_t *off2;
@@ -144,7 +241,7 @@ __global__ __launch_bounds__(BLOCK) void reorder_rows(CopyArgs c, int64_t first,
       unsorted |= jn[k] <= j[k];
       rowsum += w[k];
       if (j[k] != v) {
-        const unsigned long long key = argmax_key((uint32_t)j[k], w[k]);
+        const unsigned long long key = argmax_key((uint32_t)j[k], c.f32 && w[k] == 0x80000000u ? 0u : w[k]);
         best = key > best ? key : best;
       }
     }
@@ -217,7 +314,7 @@ __global__ __launch_bounds__(256) void reorder_hub_rows(CopyArgs c, const int64_
     unsorted |= jn[k] <= j[k];
     rowsum += w[k];
     if (j[k] != v) {
-      const unsigned long long key = argmax_key((uint32_t)j[k], w[k]);
+      const unsigned long long key = argmax_key((uint32_t)j[k], c.f32 && w[k] == 0x80000000u ? 0u : w[k]);
       best = key > best ? key : best;
     }
   }
@@ -302,26 +399,22 @@ hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_
                           int32_t *old2new, int64_t *off2, int32_t *cols2, uint32_t *w2, int32_t *lab,
                           int64_t *scan_tmp, unsigned long long *first_key,
                           unsigned long long *hub_rowsum, unsigned long long *flags,
-                          unsigned long long *dn0, int apply_first, const TierConfig &cfg, hipStream_t s) {
+                          unsigned long long *dn0, int apply_first, const TierConfig &cfg, int64_t max_degree,
+                          bool inverted, bool f32, hipStream_t s) {
   const int64_t np = n - tier_count_h[0];
   constexpr int kCap = 256 * 32;
-  reorder_invert<<<grid_of(n, 256, kCap), 256, 0, s>>>(list, n, old2new);
+  if (!inverted) reorder_invert<<<grid_of(n, 256, kCap), 256, 0, s>>>(list, 0, n, old2new);
   reorder_degrees<<<grid_of(n, 256, kCap), 256, 0, s>>>(off, list, np, n, off2, lab);
-  if (np > 0) {
-    const int64_t nb = (np + kScanBlock - 1) / kScanBlock;
-    scan_local<<<(unsigned)nb, kScanBlock, 0, s>>>(off2 + 1, np, scan_tmp);
-    scan_sums<<<1, kScanBlock, 0, s>>>(scan_tmp, nb);
-    scan_add<<<(unsigned)nb, kScanBlock, 0, s>>>(off2 + 1, np, scan_tmp);
-  }
-  CopyArgs c{off, cols, w, list, old2new, off2, cols2, w2, first_key, hub_rowsum, flags};
+  if (np > 0) scan_inclusive(off2 + 1, np, scan_tmp, s);
+  CopyArgs c{off, cols, w, f32, list, old2new, off2, cols2, w2, first_key, hub_rowsum, flags};
   const int64_t H = tier_count_h[kNumTiers - 1];
   if (H > 0) launch_fill_u64(reinterpret_cast<uint64_t *>(first_key), 0, H, s);
   for (int t = 1; t < kNumTiers; ++t) {
     const int64_t cnt = tier_count_h[t], first = tier_start_h[t];
     if (cnt <= 0) continue;
     // the copy kernel takes rows up to G * K entries: the smallest that
-    // covers the tier's degree bound
-    const int64_t d = cfg.bound[t];
+    // covers the tier's degree bound (and the graph's longest row)
+    const int64_t d = cfg.bound[t] < max_degree ? cfg.bound[t] : max_degree;
     if (t == kNumTiers - 1) {
       if (hub_chunks > 0)
         reorder_hub_rows<<<(unsigned)hub_chunks, 256, 0, s>>>(c, hub_chunk_start, hub_chunk_owner);
@@ -346,6 +439,32 @@ hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_
   if (np > 0)
     first_apply<<<grid_of(np, 256, 1024), 256, 0, s>>>(first_key, list, np, hub_rowsum, H, flags, lab, dn0,
                                                        apply_first);
+  return hipGetLastError();
+}
+
+hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, int64_t far, unsigned long long *out,
+                         hipStream_t s) {
+  hipError_t e = launch_fill_u64(reinterpret_cast<uint64_t *>(out), 0, 2, s);
+  if (e != hipSuccess) return e;
+  const int64_t samples = n < kSpreadSamples ? n : kSpreadSamples;
+  sample_spread<<<grid_of(samples, 256, 1 << 20), 256, 0, s>>>(off, cols, n, samples, far, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_cluster_order(const int64_t *off, const int32_t *cols, int64_t n, const int64_t *tier_count_h,
+                                const int64_t *tier_start_h, int64_t longest, int32_t *first, int32_t *cluster,
+                                int32_t *rank, int32_t *count, int64_t *scan_tmp, int32_t *list, int32_t *old2new,
+                                hipStream_t s) {
+  constexpr int kCap = 256 * 32;
+  const int g = grid_of(n, 256, kCap);
+  cluster_first<<<g, 256, 0, s>>>(off, cols, n, longest, first, count);
+  cluster_rank<<<g, 256, 0, s>>>(off, n, longest, first, cluster, rank, count);
+  scan_inclusive(count, n, scan_tmp, s);
+  cluster_place<<<g, 256, 0, s>>>(cluster, rank, count, n, tier_start_h[1], list, old2new);
+  // the other tiers keep their order: the list's ranges before and after tier 1
+  const int64_t before = tier_start_h[1], after = tier_start_h[1] + tier_count_h[1];
+  if (before > 0) reorder_invert<<<grid_of(before, 256, kCap), 256, 0, s>>>(list, 0, before, old2new);
+  if (after < n) reorder_invert<<<grid_of(n - after, 256, kCap), 256, 0, s>>>(list, after, n, old2new);
   return hipGetLastError();
 }
 
