@@ -1021,6 +1021,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   a.gid = batch ? s.gid : nullptr;
   a.gdone = batch ? s.gdone : nullptr;
   a.inplace = o.async_sweeps ? 1 : 0;
+  a.ids = !renumber && !a.inplace ? 1 : 0;
   a.n = n;
   // Sparse sweeps walk a frontier of the active vertices per tier, built at
   // the start of the sweep into the split's parent array (unused until the
@@ -1143,7 +1144,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     if ((int64_t)len * sweep_launches > kMaxGraphLaunches) len = (int)(kMaxGraphLaunches / sweep_launches);
     const bool chunked = len < max_iters;
     std::vector<uint64_t> key = {(uint64_t)len, (uint64_t)n, (uint64_t)n_sweep, (uint64_t)nnz, (uint64_t)max_iters,
-                                 (uint64_t)o.prune, (uint64_t)renumber, (uint64_t)a.inplace, (uint64_t)f32,
+                                 (uint64_t)o.prune, (uint64_t)renumber, (uint64_t)a.inplace, (uint64_t)a.ids, (uint64_t)f32,
                                  (uint64_t)(uintptr_t)s.fkeys, (uint64_t)(uintptr_t)s.fsums,
                                  (uint64_t)(uintptr_t)g_off, (uint64_t)(uintptr_t)g_cols,
                                  (uint64_t)(uintptr_t)g_w, (uint64_t)(uintptr_t)C, (uint64_t)(uintptr_t)g_list,

@@ -222,23 +222,23 @@ __device__ __forceinline__ unsigned long long block_sum(unsigned long long x,
   return t;
 }
 
-// Batcher's odd-even merge sort of D register values (D a power of two):
-// a sorting network, so the compare-exchange sequence is the same for every
-// input and every index is a compile-time constant once unrolled (19, 63 and
-// 191 compare-exchanges for D = 8, 16, 32).  Labels end up ascending; with
-// W, each weight moves with its label.
-template <int D, bool W>
-__device__ __forceinline__ void sort_by_label(uint32_t (&l)[D], uint32_t (&w)[D]) {
+// Batcher's odd-even merge sort of the first N of D register values: a sorting
+// network, so the compare-exchange sequence is the same for every input and
+// every index is a compile-time constant once unrolled (19, 63, 132 and 191
+// compare-exchanges for N = 8, 16, 24, 32).  Labels end up ascending; with W,
+// each weight moves with its label.
+template <int N, bool W, int D>
+__device__ __forceinline__ void sort_first(uint32_t (&l)[D], uint32_t (&w)[D]) {
 #pragma unroll
-  for (int p = 1; p < D; p <<= 1)
+  for (int p = 1; p < N; p <<= 1)
 #pragma unroll
     for (int k = p; k >= 1; k >>= 1)
 #pragma unroll
-      for (int j = k % p; j + k < D; j += 2 * k)
+      for (int j = k % p; j + k < N; j += 2 * k)
 #pragma unroll
         for (int i = 0; i < k; ++i) {
           const int x = i + j, y = i + j + k;
-          if (y < D && x / (2 * p) == y / (2 * p)) {
+          if (y < N && x / (2 * p) == y / (2 * p)) {
             if constexpr (W) {
               const bool s = l[x] > l[y];
               const uint32_t lx = l[x], wx = w[x];
@@ -253,6 +253,11 @@ __device__ __forceinline__ void sort_by_label(uint32_t (&l)[D], uint32_t (&w)[D]
             }
           }
         }
+}
+
+template <int D, bool W>
+__device__ __forceinline__ void sort_by_label(uint32_t (&l)[D], uint32_t (&w)[D]) {
+  sort_first<D, W>(l, w);
 }
 
 // Per-thread sweep counters, reduced once per block at kernel end.

@@ -148,6 +148,7 @@ struct SweepArgs {
   // so vertices later in the same sweep may already read it (the paper's
   // in-place lpaMove); results then depend on timing.
   int32_t inplace;
+  int32_t ids;  // 1: in sweep 0 every label is its vertex's id (and stays so while the sweep reads it)
   int64_t n;  // vertices (labels C[0..n))
   // Frontier of a sparse sweep: this tier's taking part vertices are
   // flist[first + i], i < *fcount (the tier's own range of the list layout).

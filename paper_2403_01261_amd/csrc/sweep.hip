@@ -66,27 +66,62 @@ __device__ __forceinline__ void flush_counts(const SweepArgs &a, const LocalCoun
 // level by default, any level that fits).  The row's labels (and weights)
 // stay in registers.  A sorting network puts equal labels next to each
 // other, and one pass over the sorted runs keeps the running sum of each run
-// and the largest argmax key seen.  A run's partial sums never exceed its
-// total, so the largest key is that of the label with the largest total (the
-// smallest such label on ties, which the key orders first).  Entries j == i
-// and the padding beyond the row carry the no-label value, which sorts last
-// and never becomes a candidate.  W: weighted rows; without it every entry
-// weighs 1.
+// and the largest seen with its label.  A run's partial sums never exceed its
+// total, so the largest is that of the label with the largest total (the
+// smallest such label on ties, which comes first).  Entries j == i and the
+// padding beyond the row carry values above every label, one of each, which
+// sort last and win only where there is no label.  W: weighted rows; without
+// it every entry weighs 1.
 //
 // The sweep waits on its vector memory instructions (row loads and label
-// gathers, one lane access each): with V4 a row comes in as 16-byte words
-// (load_row), each label is loaded into the register that held its column,
-// and with O32 (fewer than 2^30 vertices) the gather address is the label
-// array's base plus a 32-bit byte offset, which needs no 64-bit address
-// registers.  A sparse sweep after few changes walks the frontier instead of
-// the tier list.
+// gathers, one lane access each; the texture addresser is busy 85 % of the
+// time): with V4 a row comes in as 16-byte words (load_row), each label is
+// loaded into the register that held its column, and with O32 (fewer than 2^30
+// vertices) the gather address is the label array's base plus a 32-bit byte
+// offset, which needs no 64-bit address registers.  A sparse sweep after few
+// changes walks the frontier instead of the tier list.
+//
+// In the loop's first sweep every label is its vertex's id (IDS), so a row
+// without duplicate entries holds every label once and its heaviest entry wins
+// (the first of them): no gathers and no sort (1,024 planted graphs, 30 M
+// vertices: 1,635 -> 770 us).
 // ---------------------------------------------------------------------------
 __device__ const int32_t kZeroI32 = 0;
 __device__ const uint8_t kZeroU8 = 0;
 
+// Label with the largest sum among the first N (>= the row's entries) of a
+// row's labels; no label: a value >= 2^31.
+template <int N, bool W, int D>
+__device__ __forceinline__ uint32_t sorted_winner(uint32_t (&lab)[D], uint32_t (&w)[D]) {
+  sort_first<N, W>(lab, w);
+  uint32_t s = W ? w[0] : 1u, bs = s, bl = lab[0];
+#pragma unroll
+  for (int k = 1; k < N; ++k) {
+    s = (lab[k] == lab[k - 1] ? s : 0u) + (W ? w[k] : 1u);
+    bl = s > bs ? lab[k] : bl;
+    bs = s > bs ? s : bs;
+  }
+  return bl;
+}
+
+// Rows of the kernel for 32 entries are mostly shorter: the network of the
+// longest among the wavefront's active lanes (with weights, whose exchanges
+// take twice the registers, three networks cost a wavefront per SIMD).
+// Together with the 32-bit scan below instead of one of 64-bit keys: 494 ->
+// 357 M vector instructions per sweep of those graphs, 156 -> 119 registers
+// (four wavefronts per SIMD instead of three), 30.0 -> 28.8 ms per call.
+template <bool W, int D>
+__device__ __forceinline__ uint32_t row_winner(uint32_t (&lab)[D], uint32_t (&w)[D], int d) {
+  if constexpr (D == 32 && !W) {
+    if (!__ballot(d > 24)) return __ballot(d > 16) ? sorted_winner<24, W>(lab, w) : sorted_winner<16, W>(lab, w);
+  }
+  return sorted_winner<D, W>(lab, w);
+}
+
 // One listed vertex v that takes part in the sweep.
 template <int D, bool W, bool O32, bool V4>
-__device__ __forceinline__ void thread_vertex(const SweepArgs &a, const SweepView &sv, int32_t v, LocalCounts &lc) {
+__device__ __forceinline__ void thread_vertex(const SweepArgs &a, const SweepView &sv, int32_t v, bool ids,
+                                              LocalCounts &lc) {
   // Everything that depends on v alone is loaded at once (absent arrays read
   // constants instead of branching: a branch would make the wave wait for
   // every load issued before it), so a vertex of a dense sweep waits for four
@@ -100,41 +135,53 @@ __device__ __forceinline__ void thread_vertex(const SweepArgs &a, const SweepVie
   if (*dp) return;
   uint32_t lab[D], w[D];
   load_row<D, V4>(reinterpret_cast<const uint32_t *>(a.cols), b, d, (uint32_t)v, lab);
-#pragma unroll
-  for (int k = 0; k < D; ++k) lab[k] = lab[k] != (uint32_t)v ? gather_label<O32>(a.C, (int32_t)lab[k]) : kNoLabel;
+  uint32_t winner = kNoLabel;
   unsigned long long rowsum = (unsigned long long)d;
-  if constexpr (W) {
-    rowsum = 0;
-    load_row<D, V4>(a.w, b, d, 0u, w);
+  bool rises = ids;
+  if (ids) {
 #pragma unroll
-    for (int k = 0; k < D; ++k) rowsum += w[k];
+    for (int k = 1; k < D; ++k) rises = rises && (k >= d || lab[k - 1] < lab[k]);
+    rises = !__ballot(!rises);  // uniform
   }
-  sort_by_label<D, W>(lab, w);
-  unsigned long long best = 0;
-  uint32_t s = 0;
+  if (rises) {
+    if constexpr (W) {
+      rowsum = 0;
+      load_row<D, V4>(a.w, b, d, 0u, w);
+      uint32_t bw = 0;
 #pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const uint32_t wk = W ? w[k] : 1u;
-    s = (k > 0 && lab[k] == lab[k - 1]) ? s + wk : wk;
-    const unsigned long long key = lab[k] != kNoLabel ? argmax_key(lab[k], s) : 0ull;
-    best = key > best ? key : best;
+      for (int k = 0; k < D; ++k) {
+        rowsum += w[k];
+        const bool more = k < d && lab[k] != (uint32_t)v && (winner == kNoLabel || w[k] > bw);
+        bw = more ? w[k] : bw;
+        winner = more ? lab[k] : winner;
+      }
+    } else {
+      winner = lab[0] != (uint32_t)v ? lab[0] : d > 1 ? lab[1] : kNoLabel;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+      lab[k] = lab[k] != (uint32_t)v ? gather_label<O32>(a.C, (int32_t)lab[k]) : kNoLabel - (uint32_t)k;
+    if constexpr (W) {
+      rowsum = 0;
+      load_row<D, V4>(a.w, b, d, 0u, w);
+#pragma unroll
+      for (int k = 0; k < D; ++k) rowsum += w[k];
+    }
+    winner = row_winner<W>(lab, w, d);
   }
   lc.processed += 1;
   lc.edges += (unsigned long long)d;
   lc.overflow += rowsum >> 32 ? 1 : 0;
-  if (best && !(rowsum >> 32)) {
-    const uint32_t cstar = key_label(best);
-    if (cstar != own) {
-      record_change(a, v, cstar, lc);
-      if (sv.mark) {
-        // the row again (just read, so mostly from cache) for the flags
-        for (int k = 0; k < d; ++k) {
-          const int32_t j = a.cols[b + k];
-          if (!sv.nact[j]) sv.nact[j] = 1;
-        }
-        lc.marked += (unsigned long long)d;
-      }
+  if ((int32_t)winner < 0 || rowsum >> 32 || winner == own) return;
+  record_change(a, v, winner, lc);
+  if (sv.mark) {
+    // the row again (just read, so mostly from cache) for the flags
+    for (int k = 0; k < d; ++k) {
+      const int32_t j = a.cols[b + k];
+      if (!sv.nact[j]) sv.nact[j] = 1;
     }
+    lc.marked += (unsigned long long)d;
   }
 }
 
@@ -145,8 +192,10 @@ __device__ __forceinline__ void thread_vertex(const SweepArgs &a, const SweepVie
 // per call).
 constexpr int kAhead = 4;
 
+// Registers: weighted rows get as many wavefronts per SIMD as without the
+// first sweep's branch.
 template <int D, bool W, bool O32, bool V4>
-__global__ __launch_bounds__(256) void sweep_thread(SweepArgs a, const int32_t *__restrict__ list,
+__global__ __launch_bounds__(256, W ? (D <= 8 ? 7 : D <= 16 ? 4 : D <= 32 ? 3 : 1) : 1) void sweep_thread(SweepArgs a, const int32_t *__restrict__ list,
                                                     int64_t first, int64_t count) {
   __shared__ unsigned long long red[256 / kWave];
   SweepView sv;
@@ -158,6 +207,7 @@ __global__ __launch_bounds__(256) void sweep_thread(SweepArgs a, const int32_t *
     list = a.flist;
     count = *a.fcount;
   }
+  const bool ids = a.ids && sv.it == 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t idx0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx0 < count; idx0 += kAhead * stride) {
     int32_t vv[kAhead];
@@ -171,7 +221,7 @@ __global__ __launch_bounds__(256) void sweep_thread(SweepArgs a, const int32_t *
     for (int k = 0; k < kAhead; ++k) take[k] = vv[k] >= 0 && (sv.dense || front || sv.act[vv[k]]);
 #pragma unroll 1
     for (int k = 0; k < kAhead; ++k)
-      if (take[k]) thread_vertex<D, W, O32, V4>(a, sv, vv[k], lc);
+      if (take[k]) thread_vertex<D, W, O32, V4>(a, sv, vv[k], ids, lc);
   }
   flush_counts(a, lc, red);
 }
