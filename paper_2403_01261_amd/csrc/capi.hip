@@ -142,10 +142,10 @@ struct Scratch {
   gsl::GraphDesc *gdesc = nullptr;
   unsigned long long *gbad = nullptr;
   uint32_t *gflag = nullptr;  // per-graph: entry outside the graph's range
-  // fp32 weights: global hub tables (keys, fp64 sums)
-  uint32_t *fkeys = nullptr;
-  double *fsums = nullptr;
-  int64_t fslots_cap = -1;
+  // fp32 weights: staged labels and partition winners of a hub batch
+  uint32_t *flabels = nullptr;
+  double *fwon = nullptr;
+  int64_t flabels_cap = -1, fwon_cap = -1;
   int32_t *glab = nullptr;
   int64_t *goff = nullptr;
   int64_t gcols_cap = -1, gw_cap = -1, goff_cap = -1, batch_glab_cap = -1;
@@ -278,8 +278,8 @@ void free_scratch(Scratch &s) {
   hipFree(s.gdesc);
   hipFree(s.gbad);
   hipFree(s.gflag);
-  hipFree(s.fkeys);
-  hipFree(s.fsums);
+  hipFree(s.flabels);
+  hipFree(s.fwon);
   hipFree(s.glab);
   hipFree(s.goff);
   hipFree(s.gcols);
@@ -550,6 +550,20 @@ int prepare_hubs(Scratch &s, const int64_t *offsets, const int32_t *hubs, int64_
     }
     s.hub_hist_cap = need_hist;
   }
+  return GSL_OK;
+}
+
+template <class T>
+int ensure_array(T **p, int64_t *cap, int64_t count, const char *what) {
+  if (count <= *cap) return GSL_OK;
+  hipFree(*p);
+  *p = nullptr;
+  *cap = -1;
+  if (dmalloc(p, count) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(GSL_ENOMEM, "allocation of %s (%lld elements) failed", what, (long long)count);
+  }
+  *cap = count;
   return GSL_OK;
 }
 
@@ -982,20 +996,14 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
       s.ctrl, renumber ? reinterpret_cast<const unsigned long long *>(&s.ctr->first_flags) : nullptr, dn_arr,
       mk_arr, f32 ? 0 : 1, st));
   if (f32 && H > 0) {
-    const int64_t slots = gsl::hub_f32_slots(s.h_chunk[(size_t)H]);
-    if (slots > s.fslots_cap) {
-      hipFree(s.fkeys);
-      hipFree(s.fsums);
-      s.fkeys = nullptr;
-      s.fsums = nullptr;
-      s.fslots_cap = -1;
-      if (dmalloc(&s.fkeys, slots) != hipSuccess || dmalloc(&s.fsums, slots) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(GSL_ENOMEM, "hub table allocation (%lld slots) failed", (long long)slots);
-      }
-      s.fslots_cap = slots;
+    int64_t labels = 0, won = 0;  // of the largest batch
+    for (const auto &bt : s.hub_batches) {
+      const int64_t parts = s.h_part[(size_t)bt.second] - s.h_part[(size_t)bt.first];
+      labels = std::max(labels, (s.h_chunk[(size_t)bt.second] - s.h_chunk[(size_t)bt.first]) * gsl::kHubChunk + parts);
+      won = std::max(won, parts);
     }
-    HIP_TRY(gsl::launch_hub_f32_clear(s.fkeys, s.fsums, slots, st));
+    if ((rc = ensure_array(&s.flabels, &s.flabels_cap, labels, "hub labels"))) return rc;
+    if ((rc = ensure_array(&s.fwon, &s.fwon_cap, won, "hub winners"))) return rc;
   }
   if (batch)
     HIP_TRY(gsl::launch_batch_init(batch->vtx_base, batch->graphs, max_iters, tolerance, s.gid, s.glimit,
@@ -1074,10 +1082,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
         launches.push_back({t, k, 0, nev});
         if ((rc = rec(nev++))) return rc;
       }
-      if (t == gsl::kHubTier && f32) {
-        HIP_TRY(gsl::launch_hub_f32(a, g_list, s.hub_chunk_start, cnt, s.h_chunk[(size_t)cnt], s.fkeys, s.fsums,
-                                    cur));
-      } else if (t == gsl::kHubTier) {
+      if (t == gsl::kHubTier) {
         for (size_t bi = 0; bi < s.hub_batches.size(); ++bi) {
           const auto &bt = s.hub_batches[bi];
           for (int stage = 0; stage < 2; ++stage) {
@@ -1085,9 +1090,14 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
               launches.push_back({t, k, stage, nev});
               if ((rc = rec(nev++))) return rc;
             }
-            HIP_TRY(gsl::launch_hub_sweep(a, g_list, L, s.h_chunk.data(), s.h_part.data(), s.hub_staging,
-                                          s.hub_hist, s.hub_best, s.hub_rowsum, bt.first, bt.second,
-                                          s.hub_max_parts[bi], hub_lim.merge_cap, stage, cur));
+            if (f32)
+              HIP_TRY(gsl::launch_hub_f32(a, g_list, L, s.h_chunk.data(), s.h_part.data(), s.hub_staging, s.hub_hist,
+                                          s.flabels, s.fwon, bt.first, bt.second, s.hub_max_parts[bi],
+                                          hub_lim.merge_cap, stage, cur));
+            else
+              HIP_TRY(gsl::launch_hub_sweep(a, g_list, L, s.h_chunk.data(), s.h_part.data(), s.hub_staging,
+                                            s.hub_hist, s.hub_best, s.hub_rowsum, bt.first, bt.second,
+                                            s.hub_max_parts[bi], hub_lim.merge_cap, stage, cur));
           }
         }
       } else {
@@ -1145,7 +1155,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     const bool chunked = len < max_iters;
     std::vector<uint64_t> key = {(uint64_t)len, (uint64_t)n, (uint64_t)n_sweep, (uint64_t)nnz, (uint64_t)max_iters,
                                  (uint64_t)o.prune, (uint64_t)renumber, (uint64_t)a.inplace, (uint64_t)a.ids, (uint64_t)f32,
-                                 (uint64_t)(uintptr_t)s.fkeys, (uint64_t)(uintptr_t)s.fsums,
+                                 (uint64_t)(uintptr_t)s.flabels, (uint64_t)(uintptr_t)s.fwon,
                                  (uint64_t)(uintptr_t)g_off, (uint64_t)(uintptr_t)g_cols,
                                  (uint64_t)(uintptr_t)g_w, (uint64_t)(uintptr_t)C, (uint64_t)(uintptr_t)g_list,
                                  (uint64_t)(uintptr_t)s.Cn, (uint64_t)(uintptr_t)s.chg,
@@ -1486,20 +1496,6 @@ int ensure_batch(Scratch &s, int64_t N, int64_t G) {
     s.batch_g_cap = G;
   }
   if (!s.gbad && dmalloc(&s.gbad, 1) != hipSuccess) return fail(GSL_ENOMEM, "device allocation failed");
-  return GSL_OK;
-}
-
-template <class T>
-int ensure_array(T **p, int64_t *cap, int64_t count, const char *what) {
-  if (count <= *cap) return GSL_OK;
-  hipFree(*p);
-  *p = nullptr;
-  *cap = -1;
-  if (dmalloc(p, count) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(GSL_ENOMEM, "allocation of %s (%lld elements) failed", what, (long long)count);
-  }
-  *cap = count;
   return GSL_OK;
 }
 

@@ -293,6 +293,10 @@ hipError_t launch_hub_sweep(const SweepArgs &a, const int32_t *hubs, HubLayout L
                             unsigned long long *staging, int32_t *hist, unsigned long long *best,
                             unsigned long long *rowsum, int64_t k0, int64_t k1, int max_parts,
                             int merge_cap, int stage, hipStream_t s);
+// The neighbours of the hubs [k0, k1) that changed in this sweep are flagged
+// (the kernel returns at once unless the sweep marks).
+hipError_t launch_hub_mark(const SweepArgs &a, const int32_t *hubs, HubLayout L, const int64_t *chunk_start_h, int64_t k0,
+                           int64_t k1, hipStream_t s);
 // Copies changed labels into C and clears the consumed flags (this sweep's
 // active flags when it was sparse).  Batches (gdn != NULL): also adds each
 // graph's changes to gdn[graph].
@@ -317,13 +321,12 @@ hipError_t launch_loop_init(SweepCtrl *ctrl, const unsigned long long *first_fla
 // ---- fp32 weights summed in fp64 (sweep_f32.hip); SweepArgs::w holds floats ----
 hipError_t launch_sweep_tier_f32(int tier, const SweepArgs &a, const int32_t *list, int64_t first, int64_t count,
                                  int *grid_out, hipStream_t s);
-// Hub tier: per-chunk LDS sums folded into a global table per hub
-// (hub_f32_slots(chunks) slots in total, empty before the first sweep and
-// left empty by every sweep).
-hipError_t launch_hub_f32(const SweepArgs &a, const int32_t *hubs, const int64_t *chunk_start, int64_t H,
-                          int64_t chunks, uint32_t *gkeys, double *gsums, hipStream_t s);
-int64_t hub_f32_slots(int64_t chunks);
-hipError_t launch_hub_f32_clear(uint32_t *gkeys, double *gsums, int64_t slots, hipStream_t s);
+// Hub tier, the batch of hubs [k0, k1): stage 0 sums the chunks, stage 1
+// merges, decides and marks.  staging and hist as for launch_hub_sweep; labels
+// holds chunks * kHubChunk + partitions entries, won one per partition.
+hipError_t launch_hub_f32(const SweepArgs &a, const int32_t *hubs, HubLayout L, const int64_t *chunk_start_h,
+                          const int64_t *part_start_h, unsigned long long *staging, int32_t *hist, uint32_t *labels,
+                          double *won, int64_t k0, int64_t k1, int max_parts, int merge_cap, int stage, hipStream_t s);
 // *bad |= 1 if a weight is negative, NaN or infinite.
 hipError_t launch_check_f32(const float *w, int64_t nnz, unsigned long long *bad, hipStream_t s);
 // Batches: graph id per vertex, per-graph limits, sweep counts and stop flags.

@@ -20,49 +20,11 @@
 // still overflows is redone in 2, 4, ... sub-passes that each keep a hashed
 // share of the labels, so every input is handled exactly.  Tables stay at
 // 32 KB so several workgroups share a compute unit.
-#include "device_common.h"
-#include "gsl_internal.h"
+#include "hub.h"
 
 namespace gsl {
 
 namespace {
-
-constexpr int kHubBlock = 256;
-constexpr int kHubK = kHubChunk / kHubBlock;  // row entries per lane
-constexpr int kTabLog2 = 12;                  // 4096 LDS slots (2 per chunk entry)
-constexpr int kTabSlots = 1 << kTabLog2;
-constexpr int kMaxParts = kHubMaxParts;
-constexpr int kPartSize = 2048;               // expected distinct labels per partition
-constexpr int kMergeBlock = 256;
-constexpr int kHubFoldRounds = 1;  // label fold rounds per wave before the inserts (as in the tiers)
-// Claims before a merge pass gives up and the partition is split into
-// sub-passes: at most kHubMergeCapMax, so that a free slot always remains
-// (up to kMergeBlock threads may pass the check at once); a smaller cap can
-// be set at run time to exercise the sub-pass path on small graphs.
-static_assert(kHubMergeCapMax + kMergeBlock < kTabSlots, "a free slot must always remain");
-constexpr int kChunkGroup = 1024;                       // chunks whose slices one merge step indexes
-
-static_assert(kHubChunk % kHubBlock == 0, "chunk must split evenly over the block");
-static_assert(2 * kHubChunk <= kTabSlots, "insert table must hold every chunk entry");
-
-__device__ __forceinline__ int hub_parts(int64_t d) {
-  int64_t p = (d + kPartSize - 1) / kPartSize;
-  return (int)(p < 1 ? 1 : (p > kMaxParts ? kMaxParts : p));
-}
-
-// Label mixers independent of the Fibonacci slot hash (murmur3 finalizer).
-__device__ __forceinline__ uint32_t mix32(uint32_t h) {
-  h ^= h >> 16;
-  h *= 0x85ebca6bu;
-  h ^= h >> 13;
-  h *= 0xc2b2ae35u;
-  h ^= h >> 16;
-  return h;
-}
-__device__ __forceinline__ int part_of(uint32_t label, int P) {
-  return (int)(((uint64_t)mix32(label) * (uint64_t)P) >> 32);
-}
-__device__ __forceinline__ uint32_t sub_of(uint32_t label) { return mix32(label ^ 0x9e3779b9u); }
 
 // Per hub: insert chunks, partitions, histogram entries (chunks * (P + 1)).
 __global__ void hub_sizes(const int64_t *__restrict__ off, const int32_t *__restrict__ hubs, int64_t H,
@@ -107,44 +69,6 @@ __global__ __launch_bounds__(1024) void hub_scan_prefix(int64_t *a0, int64_t *a1
     if (threadIdx.x == 1023) a[H] = part[1023];
     __syncthreads();
   }
-}
-
-struct HubArgs {
-  const int32_t *hubs;           // hub vertex ids (NULL: hub k is vertex k)
-  HubLayout L;                   // [H+1] prefix arrays
-  unsigned long long *staging;   // chunk c of the batch at (c - chunk_start[k0]) * kHubChunk
-  int32_t *hist;                 // partition bounds, relative to hist_start[k0]
-  unsigned long long *best;      // [H] packed argmax keys
-  unsigned long long *rowsum;    // [H] summed row weights
-  int64_t k0, k1;                // hubs of this batch
-  int merge_cap;                 // claims before a merge pass splits (1 .. kHubMergeCapMax)
-};
-
-// Exclusive scan of a[0..n) (n <= kMaxParts) in LDS by the whole block;
-// a[n] receives the total.  `part` needs blockDim.x entries.  Ends with a
-// barrier.
-template <int BLOCK>
-__device__ void block_exclusive_scan(int *a, int n, int *part) {
-  const int per = (n + BLOCK - 1) / BLOCK;
-  const int lo = threadIdx.x * per, hi = lo + per < n ? lo + per : n;
-  int s = 0;
-  for (int i = lo; i < hi; ++i) s += a[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 1; o < BLOCK; o <<= 1) {
-    const int y = threadIdx.x >= o ? part[threadIdx.x - o] : 0;
-    __syncthreads();
-    part[threadIdx.x] += y;
-    __syncthreads();
-  }
-  int run = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0;
-  for (int i = lo; i < hi; ++i) {
-    const int c = a[i];
-    a[i] = run;
-    run += c;
-  }
-  if (threadIdx.x == BLOCK - 1) a[n] = part[BLOCK - 1];
-  __syncthreads();
 }
 
 // Dynamic LDS: the partition histogram, (largest P of the batch + 1) ints.
@@ -439,6 +363,14 @@ hipError_t launch_hub_sweep(const SweepArgs &a, const int32_t *hubs, HubLayout L
   hub_merge<<<(unsigned)parts, kMergeBlock, 0, s>>>(a, h);
   hub_decide<<<(unsigned)((k1 - k0 + 255) / 256), 256, 0, s>>>(a, h);
   hub_mark<<<(unsigned)chunks, kHubBlock, 0, s>>>(a, h);  // returns at once unless marking
+  return hipGetLastError();
+}
+
+hipError_t launch_hub_mark(const SweepArgs &a, const int32_t *hubs, HubLayout L, const int64_t *chunk_start_h, int64_t k0,
+                           int64_t k1, hipStream_t s) {
+  if (k1 <= k0) return hipSuccess;
+  HubArgs h{hubs, L, nullptr, nullptr, nullptr, nullptr, k0, k1, 1};
+  hub_mark<<<(unsigned)(chunk_start_h[k1] - chunk_start_h[k0]), kHubBlock, 0, s>>>(a, h);
   return hipGetLastError();
 }
 

@@ -10,11 +10,9 @@
 // like the oracle; LDS and hub tables add with atomics, so a sum may differ
 // from the entry-order sum in its last bits when weights span more than 2^29
 // in magnitude -- only exact ties can then resolve differently.  Hubs (rows
-// longer than the last tier) sum chunk by chunk in LDS and fold the distinct
-// labels into a global table per hub (the global-memory fallback), which one
-// workgroup per hub scans for the winner.
-#include "device_common.h"
-#include "gsl_internal.h"
+// longer than the last tier) are summed chunk by chunk and merged by hash
+// partition, as with whole-number weights.
+#include "hub.h"
 
 namespace gsl {
 
@@ -85,6 +83,48 @@ __device__ __forceinline__ int lds_insert_f64(uint32_t *keys, double *sums, int 
     }
     h = (h + 1u) & mask;
   }
+}
+
+// Folds the label of the wavefront's first entry: the weights of its other
+// entries with that label are added to it and those entries dropped (every lane
+// works on the same table).  On power-law graphs most entries of a long row
+// carry a few labels after the first sweeps, and each would be an atomic on
+// one LDS address.
+template <int K>
+__device__ __forceinline__ void wave_fold_f64(uint32_t (&lab)[K], double (&wt)[K]) {
+  const int lane = threadIdx.x % kWave;
+  int kk = -1, leader = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const unsigned long long b = __ballot(lab[k] != kNoLabel);
+    if (kk < 0 && b) {
+      kk = k;
+      leader = __ffsll((long long)b) - 1;
+    }
+  }
+  if (kk < 0) return;  // uniform
+  uint32_t mine = kNoLabel;
+#pragma unroll
+  for (int k = 0; k < K; ++k) mine = k == kk ? lab[k] : mine;
+  const uint32_t L = (uint32_t)__shfl((int)mine, leader);
+  int count = 0;
+  double sum = 0.0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    count += __popcll(__ballot(lab[k] == L));
+    sum += lab[k] == L ? wt[k] : 0.0;
+  }
+  if (count < 2) return;  // uniform
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (lab[k] == L) {
+      if (lane == leader && k == kk)
+        wt[k] = sum;
+      else
+        lab[k] = kNoLabel;
+    }
 }
 
 // Tier 1: a thread per vertex, row in registers, sums in entry order.
@@ -192,6 +232,7 @@ __global__ __launch_bounds__(BLOCK) void sweepf_lds(SweepArgs a, const int32_t *
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) lab[k] = (j[k] >= 0 && j[k] != v) ? (uint32_t)a.C[j[k]] : kNoLabel;
+    if constexpr (G >= kWave) wave_fold_f64<K>(lab, wt);  // one vertex per wave
 #pragma unroll
     for (int k = 0; k < K; ++k) slot[k] = lab[k] != kNoLabel ? lds_insert_f64(Tk, Ts, log2s, lab[k], wt[k]) : -1;
     __syncthreads();
@@ -247,105 +288,199 @@ __global__ __launch_bounds__(BLOCK) void sweepf_lds(SweepArgs a, const int32_t *
   flush(a, lc, red);
 }
 
-// Hubs.  Chunk c of hub k holds entries [c * kHubChunk, ...) of the row; the
-// hub's global table has kHubSlotsPerChunk slots per chunk (at least twice
-// the row length), starting at kHubSlotsPerChunk * chunk_start[k].
-constexpr int kHubBlockF = 256;
+// Hubs, as in hub.hip: a workgroup per chunk sums the chunk's labels in LDS and
+// stages the distinct (label, sum) pairs by hash partition, a workgroup per
+// partition (or group of them) merges what the hub's chunks staged there, and a
+// wavefront per hub picks the winner of its partitions.  A global table per hub
+// instead (one compare-and-swap and one fp64 add per pair, and a scan of all
+// its slots by one workgroup) took 0.48 + 0.33 ms per sweep of R-MAT scale 20,
+// edge factor 16 (33 M entries), against 0.09 + 0.29 + 0.02 ms here.
+// Labels are staged in `labels` and sums in `sums`, both indexed like
+// HubArgs::staging; won_* hold a winner per partition of the batch.
+struct HubF {
+  uint32_t *labels;
+  double *sums;
+  uint32_t *won_label;
+  double *won_sum;
+};
+constexpr int kHubBlockF = 512;
 constexpr int kHubKF = kHubChunk / kHubBlockF;
-constexpr int kHubSlotsPerChunk = 2 * kHubChunk;
-constexpr int kHubLdsLog2 = 12;
-static_assert((1 << kHubLdsLog2) >= 2 * kHubChunk, "chunk table must hold every chunk entry");
+// A merge workgroup's 12-byte slots leave room for two of them per compute
+// unit, so they are wide, and each lane has kMergeAhead records on the way.
+constexpr int kMergeBlockF = 512;
+constexpr int kMergeAhead = 4;
+constexpr int kMergeCapF = kTabSlots - kMergeBlockF - 1;  // a free slot always remains
 
-__device__ __forceinline__ int64_t owner_of(const int64_t *start, int64_t lo, int64_t hi, int64_t x) {
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) / 2;
-    if (start[mid] <= x)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
+// Partitions that one merge workgroup takes (see hub_merge).
+__device__ __forceinline__ int hubf_group(const HubArgs &h, unsigned long long records, int P) {
+  const unsigned long long fit = (unsigned long long)h.merge_cap * 3 / 4 * (unsigned long long)P;
+  return records <= (unsigned long long)h.merge_cap ? P
+         : (int)(fit / records < 1 ? 1 : (fit / records > (unsigned long long)P ? P : fit / records));
 }
 
-__global__ __launch_bounds__(kHubBlockF) void hubf_insert(SweepArgs a, const int32_t *__restrict__ hubs,
-                                                          const int64_t *__restrict__ chunk_start, int64_t H,
-                                                          uint32_t *gkeys, double *gsums) {
-  __shared__ uint32_t keys[1 << kHubLdsLog2];
-  __shared__ double sums[1 << kHubLdsLog2];
+// Dynamic LDS: the partition histogram, (largest P of the batch + 1) ints.
+__global__ __launch_bounds__(kHubBlockF) void hubf_insert(SweepArgs a, HubArgs h, HubF f) {
+  __shared__ uint32_t keys[kTabSlots];
+  __shared__ double sums[kTabSlots];
+  extern __shared__ int hist[];
+  __shared__ int scan_part[kHubBlockF];
   SweepView sv;
   if (!sweep_view(a, sv)) return;
-  const int64_t c = blockIdx.x;
-  const int64_t k = owner_of(chunk_start, 0, H, c);
-  const int32_t v = hubs ? hubs[k] : (int32_t)k;
+  const int64_t c = h.L.chunk_start[h.k0] + blockIdx.x;
+  const int64_t k = h.L.chunk_owner[c];
+  const int32_t v = h.hubs ? h.hubs[k] : (int32_t)k;
   if (!sweep_takes(a, sv, v)) return;  // uniform over the block
   const int64_t rb = a.off[v], re = a.off[v + 1];
-  const int64_t b = rb + (c - chunk_start[k]) * kHubChunk;
+  const int P = hub_parts(re - rb);
+  const int64_t cl = c - h.L.chunk_start[k];
+  const int64_t b = rb + cl * kHubChunk;
   const int64_t e = b + kHubChunk < re ? b + kHubChunk : re;
-  for (int s = threadIdx.x; s < (1 << kHubLdsLog2); s += kHubBlockF) {
-    keys[s] = kEmptyKey;
-    sums[s] = 0.0;
-  }
-  __syncthreads();
-  int slot[kHubKF];
+  int32_t j[kHubKF];
+  uint32_t lab[kHubKF];
+  double wt[kHubKF];
 #pragma unroll
   for (int q = 0; q < kHubKF; ++q) {
     const int64_t p = b + threadIdx.x + (int64_t)q * kHubBlockF;
-    slot[q] = -1;
-    if (p < e) {
-      const int32_t jj = a.cols[p];
-      if (jj != v) slot[q] = lds_insert_f64(keys, sums, kHubLdsLog2, (uint32_t)a.C[jj], (double)wf(a, p));
+    const bool in = p < e;
+    j[q] = in ? a.cols[p] : -1;
+    wt[q] = in ? (double)wf(a, p) : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < kHubKF; ++q) lab[q] = (j[q] >= 0 && j[q] != v) ? (uint32_t)a.C[j[q]] : kNoLabel;
+  for (int s = threadIdx.x; s < kTabSlots; s += kHubBlockF) {
+    keys[s] = kEmptyKey;
+    sums[s] = 0.0;
+  }
+  for (int i = threadIdx.x; i <= P; i += kHubBlockF) hist[i] = 0;
+  wave_fold_f64<kHubKF>(lab, wt);
+  __syncthreads();  // table and histogram initialised
+  int slot[kHubKF];
+#pragma unroll
+  for (int q = 0; q < kHubKF; ++q) slot[q] = lab[q] != kNoLabel ? lds_insert_f64(keys, sums, kTabLog2, lab[q], wt[q]) : -1;
+  __syncthreads();
+  int pp[kHubKF], rank[kHubKF];
+#pragma unroll
+  for (int q = 0; q < kHubKF; ++q) {
+    pp[q] = 0;
+    rank[q] = 0;
+    if (slot[q] >= 0) {
+      pp[q] = part_of(lab[q], P);
+      rank[q] = atomicAdd(&hist[pp[q]], 1);
     }
   }
   __syncthreads();
-  // fold the chunk's distinct labels into the hub's global table
-  const int64_t tbase = (int64_t)kHubSlotsPerChunk * chunk_start[k];
-  const uint64_t tsize = (uint64_t)kHubSlotsPerChunk * (uint64_t)(chunk_start[k + 1] - chunk_start[k]);
+  block_exclusive_scan<kHubBlockF>(hist, P, scan_part);
+  const int64_t stage = (c - h.L.chunk_start[h.k0]) * kHubChunk;
 #pragma unroll
-  for (int q = 0; q < kHubKF; ++q) {
-    if (slot[q] < 0) continue;
-    const uint32_t label = keys[slot[q]];
-    const double s = sums[slot[q]];
-    uint64_t h = ((uint64_t)(label * 2654435761u) * tsize) >> 32;
-    for (;;) {
-      uint32_t expected = kEmptyKey;
-      const bool won = __hip_atomic_compare_exchange_strong(gkeys + tbase + h, &expected, label, __ATOMIC_RELAXED,
-                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (won || expected == label) {
-        __hip_atomic_fetch_add(gsums + tbase + h, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        break;
-      }
-      h = h + 1 == tsize ? 0 : h + 1;
+  for (int q = 0; q < kHubKF; ++q)
+    if (slot[q] >= 0) {
+      f.labels[stage + hist[pp[q]] + rank[q]] = lab[q];
+      f.sums[stage + hist[pp[q]] + rank[q]] = sums[slot[q]];
     }
-  }
+  int32_t *gh = h.hist + (h.L.hist_start[k] - h.L.hist_start[h.k0]) + cl * (P + 1);
+  for (int i = threadIdx.x; i <= P; i += kHubBlockF) gh[i] = hist[i];
+  if (threadIdx.x == 0 && hist[P])
+    __hip_atomic_fetch_add(&h.L.records[k], (unsigned long long)hist[P], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One workgroup per hub: winner of the hub's table (which it clears),
-// decision and, when marking, the flags of the whole row.
-__global__ __launch_bounds__(kHubBlockF) void hubf_decide(SweepArgs a, const int32_t *__restrict__ hubs,
-                                                          const int64_t *__restrict__ chunk_start, uint32_t *gkeys,
-                                                          double *gsums) {
-  __shared__ double rw[kHubBlockF / kWave];
-  __shared__ uint32_t rl[kHubBlockF / kWave];
-  __shared__ int changed;
+__global__ __launch_bounds__(kMergeBlockF) void hubf_merge(SweepArgs a, HubArgs h, HubF f) {
+  __shared__ uint32_t keys[kTabSlots];
+  __shared__ double sums[kTabSlots];
+  __shared__ int pre[kChunkGroup + 1];
+  __shared__ int scan_part[kMergeBlockF];
+  __shared__ int claimed, overflow;
+  __shared__ double rw[kMergeBlockF / kWave];
+  __shared__ uint32_t rl[kMergeBlockF / kWave];
   SweepView sv;
   if (!sweep_view(a, sv)) return;
-  const int64_t k = blockIdx.x;
-  const int32_t v = hubs ? hubs[k] : (int32_t)k;
-  if (!sweep_takes(a, sv, v)) return;  // uniform; its table is empty
-  const int64_t tbase = (int64_t)kHubSlotsPerChunk * chunk_start[k];
-  const int64_t tsize = (int64_t)kHubSlotsPerChunk * (chunk_start[k + 1] - chunk_start[k]);
+  const int64_t gp = h.L.part_start[h.k0] + blockIdx.x;
+  const int64_t k = h.L.part_owner[gp];
+  const int p = (int)(gp - h.L.part_start[k]);
+  const int32_t v = h.hubs ? h.hubs[k] : (int32_t)k;
+  const int P = hub_parts(a.off[v + 1] - a.off[v]);
+  const int g = hubf_group(h, h.L.records[k], P);
+  if ((int64_t)p * g >= P) return;  // uniform
+  if (!sweep_takes(a, sv, v)) return;
+  const int64_t c0 = h.L.chunk_start[k], nc = h.L.chunk_start[k + 1] - c0;
+  const int32_t *gh = h.hist + (h.L.hist_start[k] - h.L.hist_start[h.k0]);
+  const int64_t stage = (c0 - h.L.chunk_start[h.k0]) * kHubChunk;
+  const int p_lo = p * g, p_hi = p_lo + g < P ? p_lo + g : P;  // partitions merged here
   double bw = -1.0;
   uint32_t bl = kNoLabel;
-  for (int64_t s = threadIdx.x; s < tsize; s += kHubBlockF) {
-    const uint32_t l = gkeys[tbase + s];
-    if (l == kEmptyKey) continue;
-    const double w = gsums[tbase + s];
-    if (better(w, l, bw, bl)) {
-      bw = w;
-      bl = l;
+  for (uint32_t R = 1;; R <<= 1) {
+    bool ok = true;
+    bw = -1.0;
+    bl = kNoLabel;
+    for (uint32_t r = 0; r < R && ok; ++r) {
+      for (int s = threadIdx.x; s < kTabSlots; s += kMergeBlockF) {
+        keys[s] = kEmptyKey;
+        sums[s] = 0.0;
+      }
+      if (threadIdx.x == 0) {
+        claimed = 0;
+        overflow = 0;
+      }
+      __syncthreads();
+      for (int64_t g0 = 0; g0 < nc; g0 += kChunkGroup) {
+        const int gn = (int)(nc - g0 < kChunkGroup ? nc - g0 : kChunkGroup);
+        for (int i = threadIdx.x; i < gn; i += kMergeBlockF) {
+          const int32_t *hc = gh + (g0 + i) * (P + 1);
+          pre[i] = hc[p_hi] - hc[p_lo];
+        }
+        __syncthreads();
+        block_exclusive_scan<kMergeBlockF>(pre, gn, scan_part);
+        const int total = pre[gn];
+        for (int t0 = 0; t0 < total; t0 += kMergeAhead * kMergeBlockF) {
+          uint32_t lab[kMergeAhead];
+          double wt[kMergeAhead];
+          int64_t at[kMergeAhead];
+#pragma unroll
+          for (int u = 0; u < kMergeAhead; ++u) {
+            const int t = t0 + u * kMergeBlockF + threadIdx.x;
+            int lo = 0, hi = gn;  // chunk i with pre[i] <= t < pre[i + 1]
+            while (hi - lo > 1) {
+              const int mid = (lo + hi) / 2;
+              if (pre[mid] <= t)
+                lo = mid;
+              else
+                hi = mid;
+            }
+            at[u] = t < total ? stage + (g0 + lo) * kHubChunk + (gh + (g0 + lo) * (P + 1))[p_lo] + (t - pre[lo]) : -1;
+          }
+#pragma unroll
+          for (int u = 0; u < kMergeAhead; ++u) {
+            lab[u] = at[u] >= 0 ? f.labels[at[u]] : kNoLabel;
+            wt[u] = at[u] >= 0 ? f.sums[at[u]] : 0.0;
+          }
+#pragma unroll
+          for (int u = 0; u < kMergeAhead; ++u)
+            if (R > 1 && lab[u] != kNoLabel && (sub_of(lab[u]) & (R - 1)) != r) lab[u] = kNoLabel;
+          wave_fold_f64<kMergeAhead>(lab, wt);
+#pragma unroll
+          for (int u = 0; u < kMergeAhead; ++u) {
+            if (lab[u] == kNoLabel) continue;
+            if (__hip_atomic_load(&overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) continue;
+            if (__hip_atomic_load(&claimed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= h.merge_cap) {
+              overflow = 1;
+              continue;
+            }
+            if (lds_insert_f64(keys, sums, kTabLog2, lab[u], wt[u]) >= 0) atomicAdd(&claimed, 1);
+          }
+        }
+        __syncthreads();
+      }
+      if (overflow) {
+        ok = false;  // uniform: read after the barrier
+      } else {
+        for (int s = threadIdx.x; s < kTabSlots; s += kMergeBlockF)
+          if (better(sums[s], keys[s], bw, bl)) {  // an empty key is no candidate
+            bw = sums[s];
+            bl = keys[s];
+          }
+      }
+      __syncthreads();
     }
-    gkeys[tbase + s] = kEmptyKey;
-    gsums[tbase + s] = 0.0;
+    if (ok) break;
   }
   shfl_best<kWave>(bw, bl);
   if (threadIdx.x % kWave == 0) {
@@ -354,35 +489,66 @@ __global__ __launch_bounds__(kHubBlockF) void hubf_decide(SweepArgs a, const int
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    bw = -1.0;
-    bl = kNoLabel;
-    for (int w = 0; w < kHubBlockF / kWave; ++w)
+    for (int w = 1; w < kMergeBlockF / kWave; ++w)
       if (better(rw[w], rl[w], bw, bl)) {
         bw = rw[w];
         bl = rl[w];
       }
+    f.won_sum[blockIdx.x] = bw;
+    f.won_label[blockIdx.x] = bl;
+  }
+}
+
+// A wavefront per hub: the winner of its merged groups and the decision.
+__global__ __launch_bounds__(256) void hubf_decide(SweepArgs a, HubArgs h, HubF f) {
+  __shared__ unsigned long long red[256 / kWave];
+  SweepView sv;
+  if (!sweep_view(a, sv)) return;
+  LocalCounts lc;
+  const int lane = threadIdx.x % kWave;
+  const int64_t k = h.k0 + (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+  const int32_t v = k < h.k1 ? (h.hubs ? h.hubs[k] : (int32_t)k) : -1;
+  if (v >= 0 && sweep_takes(a, sv, v)) {  // uniform over the wavefront
     const int64_t d = a.off[v + 1] - a.off[v];
-    const int sweep = sv.it;
-    const bool ch = bl != kNoLabel && bl != (uint32_t)a.C[v];
-    changed = ch ? 1 : 0;
-    LocalCounts lc;
-    if (ch) change(a, v, bl, lc);
-    atomicAdd(a.processed + sweep, 1ull);
-    atomicAdd(a.tier + 0, 1ull);
-    atomicAdd(a.edges + sweep, (unsigned long long)d);
-    atomicAdd(a.tier + 1, (unsigned long long)d);
-    if (ch) {
-      atomicAdd(a.dn + sweep, 1ull);
-      atomicAdd(a.tier + 2, 1ull);
-      if (sv.mark) atomicAdd(a.tier + 3, (unsigned long long)d);
+    const int P = hub_parts(d), g = hubf_group(h, h.L.records[k], P);
+    const int64_t first = h.L.part_start[k] - h.L.part_start[h.k0];
+    double bw = -1.0;
+    uint32_t bl = kNoLabel;
+    for (int p = lane; (int64_t)p * g < P; p += kWave)
+      if (better(f.won_sum[first + p], f.won_label[first + p], bw, bl)) {
+        bw = f.won_sum[first + p];
+        bl = f.won_label[first + p];
+      }
+    shfl_best<kWave>(bw, bl);
+    if (lane == 0) {
+      h.L.records[k] = 0;
+      lc.processed = 1;
+      lc.edges = (unsigned long long)d;
+      if (bl != kNoLabel && bl != (uint32_t)a.C[v]) {
+        change(a, v, bl, lc);
+        if (sv.mark) lc.marked = lc.edges;  // hub_mark flags the whole row
+      }
     }
   }
-  __syncthreads();
-  if (changed && sv.mark)
-    for (int64_t p = a.off[v] + threadIdx.x; p < a.off[v + 1]; p += kHubBlockF) {
-      const int32_t jj = a.cols[p];
-      if (!sv.nact[jj]) sv.nact[jj] = 1;
+  const unsigned long long dn = block_sum(lc.dn, red);
+  const unsigned long long pr = block_sum(lc.processed, red);
+  const unsigned long long ed = block_sum(lc.edges, red);
+  const unsigned long long mk = block_sum(lc.marked, red);
+  if (threadIdx.x == 0) {
+    if (mk) atomicAdd(a.tier + 3, mk);
+    if (dn) {
+      atomicAdd(a.dn + sv.it, dn);
+      atomicAdd(a.tier + 2, dn);
     }
+    if (pr) {
+      atomicAdd(a.processed + sv.it, pr);
+      atomicAdd(a.tier + 0, pr);
+    }
+    if (ed) {
+      atomicAdd(a.edges + sv.it, ed);
+      atomicAdd(a.tier + 1, ed);
+    }
+  }
 }
 
 __global__ void check_f32(const float *__restrict__ w, int64_t nnz, unsigned long long *bad) {
@@ -391,14 +557,6 @@ __global__ void check_f32(const float *__restrict__ w, int64_t nnz, unsigned lon
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz; e += stride)
     b |= (w[e] >= 0.0f && w[e] <= 3.4e38f) ? 0 : 1;
   if (__ballot(b) && threadIdx.x % kWave == 0) atomicOr(bad, 1ull);
-}
-
-__global__ void fill_keys(uint32_t *keys, double *sums, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    keys[i] = kEmptyKey;
-    sums[i] = 0.0;
-  }
 }
 
 int grid_f(int64_t items, int per_block) {
@@ -451,20 +609,21 @@ hipError_t launch_sweep_tier_f32(int tier, const SweepArgs &a, const int32_t *li
   return hipGetLastError();
 }
 
-hipError_t launch_hub_f32(const SweepArgs &a, const int32_t *hubs, const int64_t *chunk_start, int64_t H,
-                          int64_t chunks, uint32_t *gkeys, double *gsums, hipStream_t s) {
-  if (H <= 0) return hipSuccess;
-  hubf_insert<<<(unsigned)chunks, kHubBlockF, 0, s>>>(a, hubs, chunk_start, H, gkeys, gsums);
-  hubf_decide<<<(unsigned)H, kHubBlockF, 0, s>>>(a, hubs, chunk_start, gkeys, gsums);
-  return hipGetLastError();
-}
-
-int64_t hub_f32_slots(int64_t chunks) { return (int64_t)kHubSlotsPerChunk * chunks; }
-
-hipError_t launch_hub_f32_clear(uint32_t *gkeys, double *gsums, int64_t slots, hipStream_t s) {
-  if (slots <= 0) return hipSuccess;
-  fill_keys<<<grid_f(slots, 256), 256, 0, s>>>(gkeys, gsums, slots);
-  return hipGetLastError();
+hipError_t launch_hub_f32(const SweepArgs &a, const int32_t *hubs, HubLayout L, const int64_t *chunk_start_h,
+                          const int64_t *part_start_h, unsigned long long *staging, int32_t *hist, uint32_t *labels,
+                          double *won, int64_t k0, int64_t k1, int max_parts, int merge_cap, int stage, hipStream_t s) {
+  if (k1 <= k0) return hipSuccess;
+  if (merge_cap < 1 || merge_cap > kHubMergeCapMax) return hipErrorInvalidValue;
+  const int64_t chunks = chunk_start_h[k1] - chunk_start_h[k0], parts = part_start_h[k1] - part_start_h[k0];
+  HubArgs h{hubs, L, nullptr, hist, nullptr, nullptr, k0, k1, merge_cap < kMergeCapF ? merge_cap : kMergeCapF};
+  HubF f{labels, reinterpret_cast<double *>(staging), labels + chunks * kHubChunk, won};
+  if (stage == 0) {
+    hubf_insert<<<(unsigned)chunks, kHubBlockF, (size_t)(max_parts + 1) * sizeof(int), s>>>(a, h, f);
+    return hipGetLastError();
+  }
+  hubf_merge<<<(unsigned)parts, kMergeBlockF, 0, s>>>(a, h, f);
+  hubf_decide<<<(unsigned)((k1 - k0 + 3) / 4), 256, 0, s>>>(a, h, f);
+  return launch_hub_mark(a, hubs, L, chunk_start_h, k0, k1, s);
 }
 
 hipError_t launch_check_f32(const float *w, int64_t nnz, unsigned long long *bad, hipStream_t s) {
