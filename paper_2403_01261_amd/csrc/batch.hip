@@ -72,16 +72,42 @@ __global__ __launch_bounds__(kBlock) void globalize_cols(const int32_t *__restri
   }
 }
 
-// Separate graphs: entry counts offsets[n] - offsets[0], or -1 when the
-// offsets decrease somewhere (block per graph).
-__global__ __launch_bounds__(kBlock) void graph_entries(const GraphDesc *__restrict__ d, int64_t G,
-                                                        int64_t *__restrict__ cnt) {
+// Workgroups that share one graph of a batch or session (blockIdx.y): its rows
+// are a few hundred to a few hundred thousand, and one workgroup alone took
+// 297 us over the largest of 117 graphs (200 to 200,000 vertices), 17 now.
+constexpr unsigned kParts = 32;
+
+// Separate graphs: cnt[g] = offsets[n] - offsets[0], negative when the offsets
+// decrease somewhere, and cnt[G + g] the longest row.
+__global__ void graph_entries_init(int64_t *cnt, int64_t G) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g < 2 * G) cnt[g] = g < G ? 0x7fffffffffffffffll : 0;
+}
+
+__global__ __launch_bounds__(kBlock) void graph_entries(const GraphDesc *__restrict__ d, int64_t G, int64_t *cnt) {
+  __shared__ unsigned long long red[kBlock / kWave];
   for (int64_t g = blockIdx.x; g < G; g += gridDim.x) {
     const GraphDesc x = d[g];
+    if (blockIdx.y > 0 && (int64_t)blockIdx.y * kBlock >= x.n) continue;  // uniform
     int bad = 0;
-    for (int64_t i = threadIdx.x; i < x.n; i += kBlock) bad |= x.offsets[i] > x.offsets[i + 1] ? 1 : 0;
+    unsigned long long longest = 0;
+    for (int64_t i = (int64_t)blockIdx.y * kBlock + threadIdx.x; i < x.n; i += (int64_t)gridDim.y * kBlock) {
+      const int64_t r = x.offsets[i + 1] - x.offsets[i];
+      bad |= r < 0 ? 1 : 0;
+      longest = r > 0 && (unsigned long long)r > longest ? (unsigned long long)r : longest;
+    }
     bad = __syncthreads_or(bad);
-    if (threadIdx.x == 0) cnt[g] = bad ? -1 : (x.n > 0 ? x.offsets[x.n] - x.offsets[0] : 0);
+    longest = group_max<kWave>(longest);
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = longest;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < kBlock / kWave; ++w) longest = red[w] > longest ? red[w] : longest;
+      if (longest) atomicMax(reinterpret_cast<unsigned long long *>(&cnt[G + g]), longest);
+      if (bad) atomicMin(reinterpret_cast<long long *>(&cnt[g]), -1ll);
+      if (blockIdx.y == 0)
+        atomicMin(reinterpret_cast<long long *>(&cnt[g]), (long long)(x.n > 0 ? x.offsets[x.n] - x.offsets[0] : 0));
+    }
+    __syncthreads();
   }
 }
 
@@ -191,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void check_graph(const int64_t *__restrict_
 }
 
 // ---- sessions (continuous batching) ----
-// Block per range (grid-stride): the vertices of a newly admitted graph get
+// kParts blocks per range: the vertices of a newly admitted graph get
 // its slot, their own global id as label and the active flag of both sweeps
 // parities (its first sweep processes every vertex, whatever the pruning
 // state of the others).
@@ -200,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void session_admit(const SessionRange *__re
                                                         uint8_t *__restrict__ act0, uint8_t *__restrict__ act1) {
   for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
     const SessionRange x = r[i];
-    for (int64_t v = x.vb + threadIdx.x; v < x.vb + x.n; v += kBlock) {
+    for (int64_t v = x.vb + (int64_t)blockIdx.y * kBlock + threadIdx.x; v < x.vb + x.n; v += (int64_t)gridDim.y * kBlock) {
       gid[v] = x.slot;
       lab[v] = (int32_t)v;
       act0[v] = 1;
@@ -235,21 +261,21 @@ __global__ __launch_bounds__(kBlock) void session_split_labels(const int32_t *__
     out[v] = sel[gid[v]] ? lab[v] : (int32_t)v;
 }
 
-// Block per finishing graph: its split labels as local ids into its output,
+// kParts blocks per finishing graph: its split labels as local ids into its output,
 // its vertices handed to the dead slot.
 __global__ __launch_bounds__(kBlock) void session_finish(const SessionRange *__restrict__ r, int64_t count,
                                                          const int32_t *__restrict__ split,
                                                          int32_t *__restrict__ gid, int32_t dead) {
   for (int64_t i = blockIdx.x; i < count; i += gridDim.x) {
     const SessionRange x = r[i];
-    for (int64_t k = threadIdx.x; k < x.n; k += kBlock) {
+    for (int64_t k = (int64_t)blockIdx.y * kBlock + threadIdx.x; k < x.n; k += (int64_t)gridDim.y * kBlock) {
       x.labels_out[k] = split[x.vb + k] - (int32_t)x.vb;
       gid[x.vb + k] = dead;
     }
   }
 }
 
-// Block per live graph: its CSR rows, entries, weights and labels copied from
+// kParts blocks per live graph: its CSR rows, entries, weights and labels copied from
 // one arena buffer to the other at its new position (ids shifted by the
 // vertex move, offsets by the entry move), its vertices given its slot and
 // both active flags.
@@ -264,19 +290,35 @@ __global__ __launch_bounds__(kBlock) void session_move(const SessionRange *__res
     const SessionRange x = r[i];
     const int32_t dv = (int32_t)(x.new_vb - x.vb);
     const int64_t de = x.new_eb - x.eb;
-    for (int64_t k = threadIdx.x; k < x.n; k += kBlock) {
+    for (int64_t k = (int64_t)blockIdx.y * kBlock + threadIdx.x; k < x.n; k += (int64_t)gridDim.y * kBlock) {
       off2[x.new_vb + k] = off[x.vb + k] + de;
       lab2[x.new_vb + k] = lab[x.vb + k] + dv;
       gid[x.new_vb + k] = x.slot;
       act0[x.new_vb + k] = 1;
       act1[x.new_vb + k] = 1;
     }
-    for (int64_t e = threadIdx.x; e < x.nnz; e += kBlock) {
+    for (int64_t e = (int64_t)blockIdx.y * kBlock + threadIdx.x; e < x.nnz; e += (int64_t)gridDim.y * kBlock) {
       cols2[x.new_eb + e] = cols[x.eb + e] + dv;
       if (w) w2[x.new_eb + e] = w[x.eb + e];
     }
   }
 }
+
+// What a step of a session must be able to go back to.
+__global__ __launch_bounds__(kBlock) void session_keep(const int32_t *__restrict__ lab, int64_t n, int32_t *__restrict__ lab2,
+                                                       const int32_t *__restrict__ giters, const uint8_t *__restrict__ gdone,
+                                                       int64_t G, int32_t *__restrict__ giters2, uint8_t *__restrict__ gdone2) {
+  const int64_t stride = (int64_t)gridDim.x * kBlock;
+  for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n || v < G; v += stride) {
+    if (v < n) lab2[v] = lab[v];
+    if (v < G) {
+      giters2[v] = giters[v];
+      gdone2[v] = gdone[v];
+    }
+  }
+}
+
+dim3 graph_grid(int64_t G) { return dim3((unsigned)(G < 4096 ? G : 4096), kParts); }
 
 unsigned tiles(int64_t count) {
   const int64_t t = (count + kTile - 1) / kTile;
@@ -310,7 +352,8 @@ hipError_t launch_check_bases(const int64_t *vtx_base, const int64_t *edge_base,
 
 hipError_t launch_graph_entries(const GraphDesc *d, int64_t G, int64_t *cnt, hipStream_t s) {
   if (G <= 0) return hipSuccess;
-  graph_entries<<<(unsigned)(G < 4096 ? G : 4096), kBlock, 0, s>>>(d, G, cnt);
+  graph_entries_init<<<(unsigned)((2 * G + 255) / 256), 256, 0, s>>>(cnt, G);
+  graph_entries<<<graph_grid(G), kBlock, 0, s>>>(d, G, cnt);
   return hipGetLastError();
 }
 
@@ -327,7 +370,13 @@ hipError_t launch_gather(const GraphDesc *d, const int64_t *vtx_base, const int6
 hipError_t launch_session_admit(const SessionRange *r, int64_t count, int32_t *gid, int32_t *lab, uint8_t *act0,
                                 uint8_t *act1, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  session_admit<<<(unsigned)(count < 4096 ? count : 4096), kBlock, 0, s>>>(r, count, gid, lab, act0, act1);
+  session_admit<<<graph_grid(count), kBlock, 0, s>>>(r, count, gid, lab, act0, act1);
+  return hipGetLastError();
+}
+
+hipError_t launch_session_keep(const int32_t *lab, int64_t n, int32_t *lab2, const int32_t *giters, const uint8_t *gdone,
+                               int64_t G, int32_t *giters2, uint8_t *gdone2, hipStream_t s) {
+  session_keep<<<tiles(n > G ? n : G), kBlock, 0, s>>>(lab, n, lab2, giters, gdone, G, giters2, gdone2);
   return hipGetLastError();
 }
 
@@ -348,7 +397,7 @@ hipError_t launch_session_split_labels(const int32_t *lab, const int32_t *gid, c
 hipError_t launch_session_finish(const SessionRange *r, int64_t count, const int32_t *split, int32_t *gid,
                                  int32_t dead, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  session_finish<<<(unsigned)(count < 4096 ? count : 4096), kBlock, 0, s>>>(r, count, split, gid, dead);
+  session_finish<<<graph_grid(count), kBlock, 0, s>>>(r, count, split, gid, dead);
   return hipGetLastError();
 }
 
@@ -356,7 +405,7 @@ hipError_t launch_session_move(const SessionRange *r, int64_t count, const int64
                                const uint32_t *w, const int32_t *lab, int64_t *off2, int32_t *cols2, uint32_t *w2,
                                int32_t *lab2, int32_t *gid, uint8_t *act0, uint8_t *act1, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  session_move<<<(unsigned)(count < 4096 ? count : 4096), kBlock, 0, s>>>(r, count, off, cols, w, lab, off2, cols2,
+  session_move<<<graph_grid(count), kBlock, 0, s>>>(r, count, off, cols, w, lab, off2, cols2,
                                                                          w2, lab2, gid, act0, act1);
   return hipGetLastError();
 }

@@ -235,6 +235,11 @@ struct SmallArgs {
   const int64_t *glimit;
   int32_t *giters;
   int64_t graphs;
+  // sessions: the last graph is the dead slot, only the graphs that have
+  // stopped are split, and the host reads the stops and sweep counts here
+  int32_t session;
+  uint8_t *gdone_host;
+  int32_t *giters_host;
   // meetings of the workgroups
   unsigned long long *slots, *release;
   uint32_t epoch;         // 24 bits, another for each launch on these slots
@@ -353,7 +358,8 @@ hipError_t launch_check_bases(const int64_t *vtx_base, const int64_t *edge_base,
 // out[e] = cols[e] + vtx_base[graph of entry e].
 hipError_t launch_globalize_cols(const int32_t *cols, const int64_t *edge_base, const int64_t *vtx_base,
                                  int64_t G, int64_t nnz, int32_t *out, hipStream_t s);
-// cnt[g] = offsets[n] - offsets[0] of graph g, -1 if its offsets decrease.
+// cnt[g] = offsets[n] - offsets[0] of graph g, negative if its offsets decrease;
+// cnt[G + g] = its longest row (2 G entries in all).
 hipError_t launch_graph_entries(const GraphDesc *d, int64_t G, int64_t *cnt, hipStream_t s);
 // Separate graphs -> one global CSR (off [N + 1], cols [nnz], w [nnz] or NULL),
 // vertex ids shifted by vshift and entry positions by eshift (the position
@@ -375,6 +381,9 @@ struct SessionRange {
 };
 hipError_t launch_session_admit(const SessionRange *r, int64_t count, int32_t *gid, int32_t *lab, uint8_t *act0,
                                 uint8_t *act1, hipStream_t s);
+// lab, giters and gdone copied to lab2, giters2 and gdone2 (or back).
+hipError_t launch_session_keep(const int32_t *lab, int64_t n, int32_t *lab2, const int32_t *giters, const uint8_t *gdone,
+                               int64_t G, int32_t *giters2, uint8_t *gdone2, hipStream_t s);
 hipError_t launch_session_slots(const SessionRange *r, int64_t count, int32_t max_iters, double tol, int64_t *glimit,
                                 int32_t *giters, uint8_t *gdone, int64_t *gdn, hipStream_t s);
 hipError_t launch_session_split_labels(const int32_t *lab, const int32_t *gid, const uint8_t *sel, int64_t n,

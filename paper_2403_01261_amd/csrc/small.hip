@@ -41,6 +41,9 @@
 // leaves, as does every other one that sees the mark, and the host runs the
 // call on the general path.
 //
+// A session's step is such a launch too, from the labels, flags and counts that
+// the step before left (`init` clear), with the split of the graphs that stop.
+//
 // Results are those of the general path: the labels of a sweep depend on the
 // labels of the one before only, and the same vertices are processed.
 #include "device_common.h"
@@ -680,6 +683,14 @@ struct Forest {
   }
 };
 
+// The split takes vertex v: in a session, if its graph has just stopped (or
+// stopped before and waits to be collected).
+__device__ __forceinline__ bool splits(const SmallArgs &a, int64_t v) {
+  if (!a.session) return true;
+  const int32_t g = a.gid[v];
+  return g != a.graphs - 1 && a.gdone[g];
+}
+
 constexpr int kLinkScanS = 16;  // entries scanned for the two that are linked
 
 // First pass: the first two intra-community entries among a row's first 16,
@@ -688,7 +699,7 @@ template <int BLOCK>
 __device__ __forceinline__ void split_link(const SmallArgs &a, Shared<BLOCK> &s, const Forest<BLOCK> &f, const int32_t *L,
                                            int64_t base) {
   const int64_t v = base + threadIdx.x / kLanes;
-  if (v >= a.n) return;
+  if (v >= a.n || !splits(a, v)) return;
   const int64_t b = a.off[v], e = a.off[v + 1];
   const int32_t cu = BLOCK == kOneBlock ? s.root[v] : L[v];
   uint32_t u[kLinkScanS];
@@ -733,7 +744,7 @@ __device__ __forceinline__ void split_hooks(const SmallArgs &a, Shared<BLOCK> &s
   const int lane = threadIdx.x % kWave;
   unsigned long long x = 0;
   int64_t b = 0, e = 0;
-  if (v < a.n) {
+  if (v < a.n && splits(a, v)) {
     x = a.cp[v];
     const int32_t rep = BLOCK == kOneBlock ? s.rep[x >> 32] : a.rep[x >> 32];
     if (rep != (int32_t)(uint32_t)x) {
@@ -920,6 +931,7 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
     if (ok && a.stats) small_totals(a, s, it - it0);
     if (ok) {
       for (int64_t v = v0; v < a.n; v += stride) {
+        if (!splits(a, v)) continue;
         const int32_t q = f.root((int32_t)v), l = kOne ? s.root[v] : L[v];
         f.p[v] = q;
         a.cp[v] = ((unsigned long long)(uint32_t)l << 32) | (uint32_t)q;
@@ -935,7 +947,8 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
       ok = small_meet(a, s, m++);
     }
     if (ok)
-      for (int64_t v = v0; v < a.n; v += stride) a.out[v] = f.root((int32_t)v);
+      for (int64_t v = v0; v < a.n; v += stride)
+        if (splits(a, v)) a.out[v] = f.root((int32_t)v);
   } else {
     for (int64_t v = v0; v < a.n; v += stride) {
       if constexpr (kOne)
@@ -949,6 +962,11 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
     }
   }
   if (blockIdx.x != 0) return;
+  if (a.session)
+    for (int64_t g = threadIdx.x; g < a.graphs; g += BLOCK) {
+      a.gdone_host[g] = a.gdone[g];
+      a.giters_host[g] = a.giters[g];
+    }
   for (int q = threadIdx.x; a.stats && q < it - it0; q += BLOCK) {
     a.result->changed[q] = s.dn_of[q];
     a.result->marked[q] = s.marked[q];
