@@ -784,10 +784,10 @@ int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t
   a.cols = cols;
   a.w = weights;
   a.n = n;
-  a.lab[0] = labels_out;
-  a.lab[1] = s.Cn;
-  a.act[0] = s.act[0];
-  a.act[1] = s.act[1];
+  a.lab0 = labels_out;
+  a.lab1 = s.Cn;
+  a.act0 = s.act[0];
+  a.act1 = s.act[1];
   a.parent = s.parent;
   a.rep = s.rep;
   a.cp = s.sigma;
@@ -1912,7 +1912,7 @@ int session_plan(gsl_session &S, const gsl::TierConfig &cfg, const HubLimits &li
 // The sweeps of a step and the split of the graphs that stop, in one launch,
 // where the arena is small enough (*ran set): a step of 16 sweeps is otherwise
 // some 110 launches of a few microseconds each (48 graphs of up to 20,000
-// vertices that join in four groups: 5.2 -> 3.3 ms).  A launch whose wait
+// vertices that join in four groups: 5.2 -> 2.9 ms).  A launch whose wait
 // ran out leaves the session as it was before, its flags no longer exact: the
 // next sweep takes every vertex.
 int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, bool *ran) {
@@ -1933,10 +1933,10 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, bo
   a.cols = S.cols[S.cur];
   a.w = S.weighted ? S.w[S.cur] : nullptr;
   a.n = N;
-  a.lab[p] = S.lab[S.cur];
-  a.lab[p ^ 1] = s.Cn;
-  a.act[0] = s.act[0];
-  a.act[1] = s.act[1];
+  a.lab0 = p ? s.Cn : S.lab[S.cur];
+  a.lab1 = p ? S.lab[S.cur] : s.Cn;
+  a.act0 = s.act[0];
+  a.act1 = s.act[1];
   a.parent = s.parent;
   a.rep = s.rep;
   a.cp = s.sigma;

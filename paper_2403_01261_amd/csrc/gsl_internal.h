@@ -77,6 +77,7 @@ struct TierBounds {
 // (t = 1 .. kNumTiers - 2), kNumTiers - 1 (hubs) above the last.
 __host__ __device__ __forceinline__ int tier_of(int64_t d, const TierBounds &tb) {
   if (d <= 0) return 0;
+#pragma unroll
   for (int t = 1; t < kNumTiers - 1; ++t)
     if (d <= tb.b[t]) return t;
   return kNumTiers - 1;
@@ -218,8 +219,9 @@ struct SmallArgs {
   const int32_t *cols;
   const uint32_t *w;      // NULL: unit weights
   int64_t n, max_nnz;
-  int32_t *lab[2];        // sweep t reads lab[t & 1] and writes the other
-  uint8_t *act[2];        // active flags, as in SweepArgs
+  // Sweep t reads lab<t & 1> and writes the other (two members, not an array: see small.hip).
+  int32_t *lab0, *lab1;
+  uint8_t *act0, *act1;   // active flags, as in SweepArgs
   int32_t *parent, *rep;  // split
   unsigned long long *cp;
   int32_t *out;           // labels out: split, or as they are after the last sweep

@@ -26,9 +26,12 @@
 //  - The split needs three more meetings: link, flatten, hook, write out.
 //
 // Measured (MI355X, whole calls, general path -> here): planted graphs of 200
-// vertices 675 -> 140 us (16 sweeps), 10,000 vertices 611 -> 167 us, 28,901
-// vertices (no allocation) 660 -> 222 us, 199,999 weighted vertices with rows
-// of 20 - 57 entries 1,123 -> 781 us.  A sweep of the 10,000 vertices takes 3.9
+// vertices 675 -> 102 us (16 sweeps), 10,000 vertices 611 -> 153 us, 28,901
+// vertices (no allocation) 660 -> 187 us, 199,999 weighted vertices with rows
+// of 20 - 57 entries 1,123 -> 734 us.  All device functions are inlined and no
+// member of the arguments is indexed by a variable: a call by reference or such
+// an index moves the arguments to scratch memory, where every use reads them
+// (the same calls took 137, 190, 223 and 787 us that way).  A sweep of the 10,000 vertices takes 3.9
 // us of work (1.6 us gather and sort, the rest flags, counts and barriers) and
 // 3 us of meeting; the launches of such a sweep took about 25 us.  What bounds
 // it is latency: the label gathers after a meeting miss both caches.
@@ -102,10 +105,6 @@ struct Shared {
   int32_t lab[2][ONE], parent[ONE], root[ONE], rep[ONE];
   uint8_t act[2][ONE];
 };
-
-__device__ __forceinline__ int32_t agent_load(const int32_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 __device__ __forceinline__ unsigned long long word_of(const SmallArgs &a, uint32_t meeting, uint32_t payload) {
   return ((unsigned long long)a.epoch << 40) | ((unsigned long long)meeting << 32) | payload;
@@ -585,7 +584,7 @@ __device__ __forceinline__ void small_window(const SmallArgs &a, Shared<BLOCK> &
 // Entries in rows of degree above 64 (workgroup 0, after the first meeting):
 // where they are most of the graph, the general path renumbers it.
 template <int BLOCK>
-__device__ int64_t small_heavy(const SmallArgs &a, Shared<BLOCK> &s) {
+__device__ __forceinline__ int64_t small_heavy(const SmallArgs &a, Shared<BLOCK> &s) {
   unsigned long long h = 0;
   for (unsigned int b = threadIdx.x; b < gridDim.x; b += BLOCK) h += a.heavy[b];
   h = block_sum(h, s.red);
@@ -599,7 +598,7 @@ __device__ int64_t small_heavy(const SmallArgs &a, Shared<BLOCK> &s) {
 // After a sweep (every slot in): per-graph stops of a batch (workgroup 0) and
 // the next sweep's mode, the rules of graph_end and sweep_end.
 template <int BLOCK>
-__device__ void small_decide(const SmallArgs &a, Shared<BLOCK> &s, SweepCtrl &c) {
+__device__ __forceinline__ void small_decide(const SmallArgs &a, Shared<BLOCK> &s, SweepCtrl &c) {
   if (a.gdn) {
     unsigned long long active = 0;
     for (int64_t g = threadIdx.x; g < a.graphs; g += BLOCK) {
@@ -765,7 +764,7 @@ __device__ __forceinline__ void split_hooks(const SmallArgs &a, Shared<BLOCK> &s
 // Totals of the statistics over the workgroups, a wavefront of the grid per
 // count (one workgroup: its own counts).
 template <int BLOCK>
-__device__ void small_totals(const SmallArgs &a, Shared<BLOCK> &s, int sweeps) {
+__device__ __forceinline__ void small_totals(const SmallArgs &a, Shared<BLOCK> &s, int sweeps) {
   constexpr int F = kNumTiers * kSmallTierFields;
   if constexpr (BLOCK == kOneBlock) {
     for (int f = threadIdx.x; f < F; f += BLOCK)
@@ -831,16 +830,17 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
   SweepCtrl c = a.ctrl;
   const int it0 = c.it;
   // the call's own state (one workgroup: into LDS)
+  const int32_t *labels_in = it0 & 1 ? a.lab1 : a.lab0;
   if constexpr (kOne) {
     for (int v = threadIdx.x; v < a.n; v += BLOCK) {
-      s.lab[it0 & 1][v] = a.init ? v : a.lab[it0 & 1][v];
-      s.act[0][v] = a.init ? 0 : a.act[0][v];
-      s.act[1][v] = a.init ? 0 : a.act[1][v];
+      s.lab[it0 & 1][v] = a.init ? v : labels_in[v];
+      s.act[0][v] = a.init ? 0 : a.act0[v];
+      s.act[1][v] = a.init ? 0 : a.act1[v];
       s.parent[v] = v;
     }
   } else {
     for (int64_t v = (int64_t)blockIdx.x * BLOCK + threadIdx.x; v < a.n; v += (int64_t)gridDim.x * BLOCK) {
-      if (a.init) a.act[0][v] = a.act[1][v] = 0;
+      if (a.init) a.act0[v] = a.act1[v] = 0;
       a.parent[v] = (int32_t)v;
     }
   }
@@ -849,10 +849,10 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
   int it = it0;
   while (c.max_iters > it0) {
     Sweep<BLOCK> md;
-    md.C = a.init && it == it0 ? nullptr : a.lab[it & 1];
-    md.Cn = a.lab[(it + 1) & 1];
-    md.act = a.act[it & 1];
-    md.nact = a.act[(it + 1) & 1];
+    md.C = a.init && it == it0 ? nullptr : it & 1 ? a.lab1 : a.lab0;
+    md.Cn = it & 1 ? a.lab0 : a.lab1;
+    md.act = it & 1 ? a.act1 : a.act0;
+    md.nact = it & 1 ? a.act0 : a.act1;
     md.par = it & 1;
     md.dense = c.dense != 0;
     md.mark = c.mark != 0;
@@ -873,6 +873,7 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
     }
     if (it == it0 && a.init && a.layout_auto && threadIdx.x == kWave) {
       unsigned long long heavy = 0;
+#pragma unroll
       for (int t = 1; t < kNumTiers; ++t)
         if (a.tiers.b[t - 1] >= 64) heavy += s.tstat[t][5];
       a.heavy[blockIdx.x] = heavy;
@@ -912,7 +913,7 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
   // this workgroup's counts of the whole call, summed after the next meeting
   if (!kOne && a.stats)
     for (int i = threadIdx.x; i < F; i += BLOCK) a.tier_rec[(size_t)blockIdx.x * F + i] = (&s.tstat[0][0])[i];
-  const int32_t *L = a.lab[it & 1];
+  const int32_t *L = it & 1 ? a.lab1 : a.lab0;
   const int64_t v0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x, stride = (int64_t)gridDim.x * BLOCK;
   Forest<BLOCK> f;
   if constexpr (kOne) {
