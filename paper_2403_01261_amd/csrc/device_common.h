@@ -169,6 +169,19 @@ __device__ __forceinline__ void wave_fold_labels(uint32_t (&lab)[K], uint32_t (&
   }
 }
 
+// LDS written by the lanes of a group becomes visible to the others.  A slice of
+// a wavefront needs no barrier: its LDS operations run in order, so it is enough
+// that the compiler keeps them so.
+template <int G>
+__device__ __forceinline__ void group_sync() {
+  if constexpr (G > kWave) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // Max over the G lanes of a group (G a power of two <= 64, groups aligned).
 template <int G>
 __device__ __forceinline__ unsigned long long group_max(unsigned long long x) {

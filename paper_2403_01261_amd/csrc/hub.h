@@ -58,29 +58,34 @@ struct HubArgs {
 };
 
 // Exclusive scan of a[0..n) (n <= kMaxParts) in LDS by the whole block;
-// a[n] receives the total.  `part` needs blockDim.x entries.  Ends with a
-// barrier.
+// a[n] receives the total.  `part` needs blockDim.x / 64 entries.  The threads'
+// sums are scanned within each wavefront first: two barriers in all (with a scan
+// of them in LDS, two barriers per doubling, float weights on R-MAT scale 20
+// took 8.20 ms a call instead of 7.86, scale 26 224.4 instead of 223.9).
 template <int BLOCK>
 __device__ void block_exclusive_scan(int *a, int n, int *part) {
   const int per = (n + BLOCK - 1) / BLOCK;
   const int lo = threadIdx.x * per, hi = lo + per < n ? lo + per : n;
+  const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
   int s = 0;
   for (int i = lo; i < hi; ++i) s += a[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 1; o < BLOCK; o <<= 1) {
-    const int y = threadIdx.x >= o ? part[threadIdx.x - o] : 0;
-    __syncthreads();
-    part[threadIdx.x] += y;
-    __syncthreads();
+  int incl = s;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int y = __shfl_up(incl, o, kWave);
+    incl += lane >= o ? y : 0;
   }
-  int run = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0;
+  if (lane == kWave - 1) part[wid] = incl;
+  __syncthreads();
+  int run = incl - s;
+#pragma unroll
+  for (int w = 0; w < BLOCK / kWave; ++w) run += w < wid ? part[w] : 0;
   for (int i = lo; i < hi; ++i) {
     const int c = a[i];
     a[i] = run;
     run += c;
   }
-  if (threadIdx.x == BLOCK - 1) a[n] = part[BLOCK - 1];
+  if (threadIdx.x == BLOCK - 1) a[n] = run;
   __syncthreads();
 }
 

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(1024) void hub_scan_prefix(int64_t *a0, int64_t *a1
 __global__ __launch_bounds__(kHubBlock) void hub_insert(SweepArgs a, HubArgs h) {
   __shared__ unsigned long long tab[kTabSlots];
   extern __shared__ int hist[];
-  __shared__ int scan_part[kHubBlock];
+  __shared__ int scan_part[kHubBlock / kWave];
   __shared__ unsigned long long red[kHubBlock / kWave];
   SweepView sv;
   if (!sweep_view(a, sv)) return;
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kHubBlock) void hub_insert(SweepArgs a, HubArgs h) 
 __global__ __launch_bounds__(kMergeBlock) void hub_merge(SweepArgs a, HubArgs h) {
   __shared__ unsigned long long tab[kTabSlots];
   __shared__ int pre[kChunkGroup + 1];
-  __shared__ int scan_part[kMergeBlock];
+  __shared__ int scan_part[kMergeBlock / kWave];
   __shared__ int claimed, overflow;
   __shared__ unsigned long long red[kMergeBlock / kWave];
   SweepView sv;

@@ -268,8 +268,10 @@ void launch_thread(const SweepArgs &a, const int32_t *list, int64_t first, int64
 // batch), the taken vertices are packed into LDS in list order, and the
 // groups then work through the packed vertices only.  A sparse sweep thus
 // costs one flag check per thread instead of one per group, and one after
-// few changes walks the frontier (every entry taken).  All groups of a block
-// move through the insert / read phases together.
+// few changes walks the frontier (every entry taken).  Groups within a wavefront
+// meet at no barrier between the windows (1,024 planted graphs 25.62 -> 25.46
+// ms, R-MAT scale 22 8.89 -> 8.82 ms, scale 26 225.4 -> 224.4 ms, float weights
+// 8.39 -> 8.24 ms against all groups moving through the phases together).
 // ---------------------------------------------------------------------------
 template <int G, int LOG2S, int BLOCK, int K>
 __global__ __launch_bounds__(BLOCK) void sweep_lds(SweepArgs a, const int32_t *__restrict__ list,
@@ -351,7 +353,7 @@ __global__ __launch_bounds__(BLOCK) void sweep_lds(SweepArgs a, const int32_t *_
       if constexpr (G >= kWave) wave_fold_labels<K>(lab, wt, kFoldRounds);  // one vertex per wave
 #pragma unroll
       for (int k = 0; k < K; ++k) slot[k] = lab[k] != kNoLabel ? lds_insert(T, log2s, lab[k], wt[k]) : -1;
-      __syncthreads();
+      group_sync<G>();
       unsigned long long best = 0;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
@@ -405,7 +407,7 @@ __global__ __launch_bounds__(BLOCK) void sweep_lds(SweepArgs a, const int32_t *_
           }
         }
       }
-      __syncthreads();
+      group_sync<G>();
     }
   }
   flush_counts(a, lc, red);

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(BLOCK) void sweepf_lds(SweepArgs a, const int32_t *
     if constexpr (G >= kWave) wave_fold_f64<K>(lab, wt);  // one vertex per wave
 #pragma unroll
     for (int k = 0; k < K; ++k) slot[k] = lab[k] != kNoLabel ? lds_insert_f64(Tk, Ts, log2s, lab[k], wt[k]) : -1;
-    __syncthreads();
+    group_sync<G>();
     double bw = -1.0;
     uint32_t bl = kNoLabel;
 #pragma unroll
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(BLOCK) void sweepf_lds(SweepArgs a, const int32_t *
             }
       }
     }
-    __syncthreads();
+    group_sync<G>();
   }
   flush(a, lc, red);
 }
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kHubBlockF) void hubf_insert(SweepArgs a, HubArgs h
   __shared__ uint32_t keys[kTabSlots];
   __shared__ double sums[kTabSlots];
   extern __shared__ int hist[];
-  __shared__ int scan_part[kHubBlockF];
+  __shared__ int scan_part[kHubBlockF / kWave];
   SweepView sv;
   if (!sweep_view(a, sv)) return;
   const int64_t c = h.L.chunk_start[h.k0] + blockIdx.x;
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(kMergeBlockF) void hubf_merge(SweepArgs a, HubArgs 
   __shared__ uint32_t keys[kTabSlots];
   __shared__ double sums[kTabSlots];
   __shared__ int pre[kChunkGroup + 1];
-  __shared__ int scan_part[kMergeBlockF];
+  __shared__ int scan_part[kMergeBlockF / kWave];
   __shared__ int claimed, overflow;
   __shared__ double rw[kMergeBlockF / kWave];
   __shared__ uint32_t rl[kMergeBlockF / kWave];
