@@ -491,11 +491,15 @@ __global__ __launch_bounds__(256) void apply_changes(SweepArgs a, int32_t *__res
   }
 }
 
-// Frontier of a sparse sweep (see launch_frontier): one thread per vertex of
-// a 1,024-vertex chunk, ranks within the chunk by ballot per tier, one atomic
-// per tier and chunk.  The grid is capped (chunks in a grid-stride loop), so
-// the launch costs little in the sweeps that do not build one.
+// Frontier of a sparse sweep (see launch_frontier): four vertices per thread of
+// a 4,096-vertex chunk, whose flags are one word; a chunk without a flag, most
+// of them late in the loop, costs one load.  Ranks within a quarter of the
+// chunk by ballot per tier, one atomic per tier and quarter.  The grid is
+// capped (chunks in a grid-stride loop), so the launch costs little in the
+// sweeps that do not build one.  A flag per thread took 63 us over 30 M
+// vertices with next to none set, 39 now.
 constexpr int kFrontierBlock = 1024;
+constexpr int kFrontierChunk = 4 * kFrontierBlock;
 constexpr int kFrontierGrid = 1024;
 
 __global__ __launch_bounds__(kFrontierBlock) void frontier_build(SweepArgs a, int64_t n, TierBounds tb,
@@ -508,35 +512,42 @@ __global__ __launch_bounds__(kFrontierBlock) void frontier_build(SweepArgs a, in
   if (!sweep_view(a, sv) || sv.dense || !sv.front) return;  // uniform
   const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
   const unsigned long long below = (1ull << lane) - 1ull;
-  for (int64_t c0 = (int64_t)blockIdx.x * kFrontierBlock; c0 < n; c0 += (int64_t)gridDim.x * kFrontierBlock) {
-    const int64_t v = c0 + threadIdx.x;
-    int t = -1;
-    if (v < n && sv.act[v] && !(a.gid && a.gdone[a.gid[v]])) {
-      t = tier_of(a.off[v + 1] - a.off[v], tb);
-      if (t == 0 || t == kNumTiers - 1) t = -1;  // no entries / a hub (the hub kernels read the flags)
-    }
-    int rank = 0;
+  for (int64_t c0 = (int64_t)blockIdx.x * kFrontierChunk; c0 < n; c0 += (int64_t)gridDim.x * kFrontierChunk) {
+    // the flag arrays are padded to whole words
+    const int64_t v0 = c0 + 4 * (int64_t)threadIdx.x;
+    const uint32_t flags = v0 < n ? *reinterpret_cast<const uint32_t *>(sv.act + v0) : 0u;
+    if (!__syncthreads_or(flags != 0)) continue;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      const int64_t v = v0 + q;
+      int t = -1;
+      if (v < n && ((flags >> (8 * q)) & 0xffu) && !(a.gid && a.gdone[a.gid[v]])) {
+        t = tier_of(a.off[v + 1] - a.off[v], tb);
+        if (t == 0 || t == kNumTiers - 1) t = -1;  // no entries / a hub (the hub kernels read the flags)
+      }
+      int rank = 0;
 #pragma unroll
-    for (int k = 1; k < kNumTiers - 1; ++k) {
-      const unsigned long long m = __ballot(t == k);
-      if (t == k) rank = __popcll(m & below);
-      if (lane == 0) wcnt[wid][k] = __popcll(m);
+      for (int k = 1; k < kNumTiers - 1; ++k) {
+        const unsigned long long m = __ballot(t == k);
+        if (t == k) rank = __popcll(m & below);
+        if (lane == 0) wcnt[wid][k] = __popcll(m);
+      }
+      __syncthreads();
+      if (threadIdx.x > 0 && threadIdx.x < kNumTiers - 1) {
+        int total = 0;
+        for (int w = 0; w < W; ++w) total += wcnt[w][threadIdx.x];
+        base[threadIdx.x] = total ? atomicAdd(reinterpret_cast<unsigned long long *>(&fcount[threadIdx.x]),
+                                              (unsigned long long)total)
+                                  : 0ull;
+      }
+      __syncthreads();
+      if (t >= 0) {
+        int before = 0;
+        for (int w = 0; w < wid; ++w) before += wcnt[w][t];
+        flist[start.b[t] + (int64_t)base[t] + before + rank] = (int32_t)v;
+      }
+      __syncthreads();  // wcnt and base are rewritten next
     }
-    __syncthreads();
-    if (threadIdx.x > 0 && threadIdx.x < kNumTiers - 1) {
-      int total = 0;
-      for (int w = 0; w < W; ++w) total += wcnt[w][threadIdx.x];
-      base[threadIdx.x] = total ? atomicAdd(reinterpret_cast<unsigned long long *>(&fcount[threadIdx.x]),
-                                            (unsigned long long)total)
-                                : 0ull;
-    }
-    __syncthreads();
-    if (t >= 0) {
-      int before = 0;
-      for (int w = 0; w < wid; ++w) before += wcnt[w][t];
-      flist[start.b[t] + (int64_t)base[t] + before + rank] = (int32_t)v;
-    }
-    __syncthreads();  // wcnt and base are rewritten by the next chunk
   }
 }
 
@@ -636,11 +647,14 @@ hipError_t launch_sweep_tier(int variant, const SweepArgs &a, const int32_t *lis
 }
 
 namespace {
-__global__ void reduce_counts(const unsigned long long *__restrict__ part, TierGrids g,
+// 1,024 threads a tier: 256 took 11 us for the 4,096 records of a large tier,
+// in every sweep; 8 now.
+constexpr int kReduceBlock = 1024;
+__global__ __launch_bounds__(kReduceBlock) void reduce_counts(const unsigned long long *__restrict__ part, TierGrids g,
                               unsigned long long (*tier_stats)[4], const SweepCtrl *ctrl,
                               unsigned long long *dn, unsigned long long *processed,
                               unsigned long long *edges, unsigned long long *overflow) {
-  __shared__ unsigned long long red[256 / kWave];
+  __shared__ unsigned long long red[kReduceBlock / kWave];
   const int t = blockIdx.x;
   const int nb = g.g[t];
   if (nb <= 0 || ctrl->done) return;
@@ -672,7 +686,7 @@ hipError_t launch_reduce_counts(const unsigned long long *part, TierGrids g,
                                 unsigned long long (*tier_stats)[4], const SweepCtrl *ctrl,
                                 unsigned long long *dn, unsigned long long *processed,
                                 unsigned long long *edges, unsigned long long *overflow, hipStream_t s) {
-  reduce_counts<<<kNumTiers, 256, 0, s>>>(part, g, tier_stats, ctrl, dn, processed, edges, overflow);
+  reduce_counts<<<kNumTiers, kReduceBlock, 0, s>>>(part, g, tier_stats, ctrl, dn, processed, edges, overflow);
   return hipGetLastError();
 }
 
@@ -684,7 +698,7 @@ hipError_t launch_frontier(const SweepArgs &a, int64_t n, const TierConfig &cfg,
     tb.b[t] = cfg.bound[t];
     start.b[t] = tier_start_h[t];
   }
-  const int64_t chunks = (n + kFrontierBlock - 1) / kFrontierBlock;
+  const int64_t chunks = (n + kFrontierChunk - 1) / kFrontierChunk;
   frontier_build<<<(unsigned)(chunks < kFrontierGrid ? chunks : kFrontierGrid), kFrontierBlock, 0, s>>>(
       a, n, tb, start, flist, fcount);
   return hipGetLastError();
