@@ -437,12 +437,14 @@ int read_nnz(const int64_t *offsets, int64_t n, int64_t *nnz, hipStream_t st) {
 
 // Runs the degree plan and copies the counters block to the host mirror;
 // with `ends` (2 words of pinned host memory) also offsets[0] and offsets[n],
-// in the same round trip.  The plan reads offsets only, so it may run before
+// in the same round trip, and with `spread_cols` (the columns of offsets that
+// were checked before) the spread of the entries.  The plan reads offsets only, so it may run before
 // they are validated.
 int run_plan(Scratch &s, const int64_t *offsets, int64_t n, const gsl::TierConfig &cfg, hipStream_t st,
-             int64_t *ends = nullptr) {
+             int64_t *ends = nullptr, const int32_t *spread_cols = nullptr) {
   HIP_TRY(gsl::launch_fill_u64(reinterpret_cast<uint64_t *>(s.ctr), 0, s.ctr_bytes / 8, st));
   HIP_TRY(gsl::launch_plan(offsets, n, s.list, s.blk_counts, s.ctr, cfg, st));
+  if (spread_cols) HIP_TRY(gsl::launch_spread(offsets, spread_cols, n, s.ctr->spread, st));
   HIP_TRY(hipMemcpyAsync(s.ctr_host, s.ctr, sizeof(Counters), hipMemcpyDeviceToHost, st));
   if (ends) {
     HIP_TRY(hipMemcpyAsync(&ends[0], offsets, sizeof(int64_t), hipMemcpyDeviceToHost, st));
@@ -876,30 +878,26 @@ int thread_variant(int variant, int64_t longest) {
 
 // Cluster order (see launch_cluster_order): for graphs of short rows (at most
 // four entries a row on average, seven of eight rows in tier 1) whose
-// neighbours lie far apart in the caller's ids -- more than kClusterFar ids,
+// neighbours lie far apart in the caller's ids -- more than kSpreadFar ids,
 // half an XCD's L2 of labels, for over half of a sample -- and whose sweeps
 // may repeat often enough to pay for the order and the copy, about three
 // sweeps' time.  Such graphs (roads, long paths) converge slowly.  Measured on
 // shuffled road graphs, original layout -> cluster order, 20 sweeps, ms per
-// call: 2 M vertices 2.23 -> 1.86, 4 M 4.62 -> 3.06, 12 M 15.1 -> 8.0, 24 M
-// 27.4 -> 15.4; below 2 M vertices the labels are near enough to L2's size.
+// call: 2 M vertices 2.23 -> 1.86, 4 M 4.62 -> 3.13, 12 M 15.1 -> 8.5, 24 M
+// 27.4 -> 16.8; below 2 M vertices the labels are near enough to L2's size.
 constexpr int64_t kClusterMinVertices = 2000000;
-constexpr int64_t kClusterFar = int64_t(1) << 19;
 constexpr int32_t kClusterMinSweeps = 8;
-
-int wants_clusters(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, int64_t n, int64_t nnz,
-                   int32_t max_iters, const Counters &plan, bool *wanted) {
-  *wanted = false;
+bool wants_clusters(int64_t n, int64_t nnz, int32_t max_iters, const Counters &plan) {
   const int64_t np = n - plan.tier_count[0];
-  if (n < kClusterMinVertices || max_iters < kClusterMinSweeps || nnz > 4 * np || 8 * plan.tier_count[1] < 7 * np)
-    return GSL_OK;
-  unsigned long long *out = reinterpret_cast<unsigned long long *>(&s.ctr->pad[0]);
-  HIP_TRY(gsl::launch_spread(offsets, cols, n, kClusterFar, out, st));
-  HIP_TRY(hipMemcpyAsync(s.pin, out, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  *wanted = s.pin[0] > 0 && 2 * s.pin[1] > s.pin[0];
-  return GSL_OK;
+  return n >= kClusterMinVertices && max_iters >= kClusterMinSweeps && nnz <= 4 * np &&
+         8 * plan.tier_count[1] >= 7 * np && plan.spread[0] > 0 && 2 * plan.spread[1] > plan.spread[0];
 }
+
+// Windows of near labels in LDS: for graphs whose sampled entries are mostly
+// near.  The labels of 7 M vertices (256 planted graphs, 8.0 ms either way) or
+// fewer stay in the L2s well enough; 15 M 14.7 -> 13.9 ms, 30 M 28.8 -> 25.7.
+constexpr int64_t kNearMinVertices = int64_t(1) << 23;
+bool wants_near(const Counters &plan) { return plan.spread[0] > 0 && 2 * plan.spread[2] > plan.spread[0]; }
 
 // f32: `weights` holds fp32 values (summed in fp64) instead of uint32.
 int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
@@ -931,7 +929,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     if ((rc = ensure_events(s))) return rc;
     HIP_TRY(hipEventRecord(s.ev[0], st));
   }
-  if ((rc = run_plan(s, offsets, n, cfg, st, s.pin))) return rc;
+  if ((rc = run_plan(s, offsets, n, cfg, st, s.pin, batch && n >= kNearMinVertices ? cols : nullptr))) return rc;
   if (s.pin[0] != 0) return fail(GSL_EINVAL, "offsets[0] must be 0 (got %lld)", (long long)s.pin[0]);
   if (s.pin[1] < 0) return fail(GSL_EINVAL, "offsets[n] must be >= 0");
   const int64_t nnz = s.pin[1];
@@ -953,8 +951,15 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   const int64_t np = n - plan.tier_count[0];  // non-isolated vertices
   bool renumber = !batch && (o.layout == 1 || (o.layout == 0 && 2 * heavy > nnz));
   bool clustered = false;
-  if (!batch && o.layout == 0 && !renumber && (rc = wants_clusters(s, st, offsets, cols, n, nnz, max_iters, plan, &clustered)))
-    return rc;
+  // A sample of the entries' spread, for graphs large enough to use it (a
+  // batch's was taken with its plan).
+  if (!batch && !renumber && n >= std::min(kNearMinVertices, kClusterMinVertices) && nnz > 0) {
+    HIP_TRY(gsl::launch_spread(offsets, cols, n, s.ctr->spread, st));
+    HIP_TRY(hipMemcpyAsync(s.pin, s.ctr->spread, sizeof(plan.spread), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    memcpy(plan.spread, s.pin, sizeof(plan.spread));
+  }
+  clustered = !batch && o.layout == 0 && !renumber && wants_clusters(n, nnz, max_iters, plan);
   if (clustered) {
     // without memory for the copy the sweeps run on the caller's graph
     const int64_t rows = plan.tier_count[1];
@@ -1048,6 +1053,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   a.gdone = batch ? s.gdone : nullptr;
   a.inplace = o.async_sweeps ? 1 : 0;
   a.ids = !renumber && !a.inplace ? 1 : 0;
+  a.near = !a.inplace && !f32 && !renumber && wants_near(plan) ? 1 : 0;
   a.n = n;
   // Sparse sweeps walk a frontier of the active vertices per tier, built at
   // the start of the sweep into the split's parent array (unused until the
@@ -1172,7 +1178,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     if ((int64_t)len * sweep_launches > kMaxGraphLaunches) len = (int)(kMaxGraphLaunches / sweep_launches);
     const bool chunked = len < max_iters;
     std::vector<uint64_t> key = {(uint64_t)len, (uint64_t)n, (uint64_t)n_sweep, (uint64_t)nnz, (uint64_t)max_iters,
-                                 (uint64_t)o.prune, (uint64_t)renumber, (uint64_t)a.inplace, (uint64_t)a.ids, (uint64_t)f32,
+                                 (uint64_t)o.prune, (uint64_t)renumber, (uint64_t)a.inplace, (uint64_t)a.ids, (uint64_t)a.near, (uint64_t)f32,
                                  (uint64_t)(uintptr_t)s.flabels, (uint64_t)(uintptr_t)s.fwon,
                                  (uint64_t)(uintptr_t)g_off, (uint64_t)(uintptr_t)g_cols,
                                  (uint64_t)(uintptr_t)g_w, (uint64_t)(uintptr_t)C, (uint64_t)(uintptr_t)g_list,

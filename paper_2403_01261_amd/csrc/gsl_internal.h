@@ -95,7 +95,7 @@ struct Counters {
   uint64_t two_m, intra;    // modularity integer parts
   uint64_t s2_lo, s2_hi;
   double q;
-  uint64_t pad[3];
+  uint64_t spread[3];       // launch_spread
   int64_t tier_edges[16];   // row entries per tier
   int64_t fcount[16];       // sparse sweeps: active vertices of each tier (the frontier)
   int64_t ftotal[16];       // frontier entries per tier, summed over the sweeps
@@ -156,6 +156,7 @@ struct SweepArgs {
   // in-place lpaMove); results then depend on timing.
   int32_t inplace;
   int32_t ids;  // 1: in sweep 0 every label is its vertex's id (and stays so while the sweep reads it)
+  int32_t near;  // 1: most row entries lie within a few thousand ids of their vertex
   int64_t n;  // vertices (labels C[0..n))
   // Frontier of a sparse sweep: this tier's taking part vertices are
   // flist[first + i], i < *fcount (the tier's own range of the list layout).
@@ -447,10 +448,11 @@ hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_
                           unsigned long long *hub_rowsum, unsigned long long *flags,
                           unsigned long long *dn0, int apply_first, const TierConfig &cfg, int64_t max_degree,
                           const ClusterRow *rows, bool f32, hipStream_t s);
-// out[0] row entries of a sample of the vertices, out[1] those whose column
-// is more than `far` ids from its vertex.
-hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, int64_t far, unsigned long long *out,
-                         hipStream_t s);
+// Added to out (3 entries): row entries of a sample of the vertices, those whose
+// column is more than kSpreadFar ids from its vertex, those at most kSpreadNear.
+constexpr int64_t kSpreadFar = int64_t(1) << 19;
+constexpr int64_t kSpreadNear = 4096;
+hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, uint64_t *out, hipStream_t s);
 // The rows of tier 1 (up to `longest` entries) in cluster order, which
 // launch_reorder then lists, and the inverse of the whole list.  A cluster is a vertex that is the smallest
 // neighbour of its members or of theirs, so members are within four edges of

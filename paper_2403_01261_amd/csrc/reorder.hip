@@ -108,30 +108,32 @@ void scan_inclusive(T *a, int64_t n, int64_t *sums, hipStream_t s) {
 
 // ---- cluster order of the short rows (launch_cluster_order) ----
 
-// Of up to kSpreadSamples vertices spread over the graph: entries seen (the
-// first and last of each row) and those more than `far` ids from their vertex.
+// Two entries of each of up to kSpreadSamples vertices spread over
+// the graph (not the ends of the row: sorted rows have their farthest there).
 constexpr int64_t kSpreadSamples = 1 << 16;
 __global__ __launch_bounds__(256) void sample_spread(const int64_t *__restrict__ off, const int32_t *__restrict__ cols,
-                                                     int64_t n, int64_t samples, int64_t far,
-                                                     unsigned long long *out) {
+                                                     int64_t n, int64_t samples, unsigned long long *out) {
   __shared__ unsigned long long red[256 / kWave];
-  unsigned long long seen = 0, spread = 0;
+  unsigned long long seen = 0, far = 0, near = 0;
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k < samples) {
     const int64_t v = (int64_t)((unsigned long long)k * (unsigned long long)n / (unsigned long long)samples);
     const int64_t b = off[v], e = off[v + 1];
     if (e > b) {
-      const int64_t x = cols[b], y = cols[e - 1];
+      const int64_t p = cols[b + (e - b) / 4], q = cols[b + (e - b) * 3 / 4];
+      const int64_t x = p > v ? p - v : v - p, y = q > v ? q - v : v - q;
       seen = 2;
-      spread = (x > v ? x - v : v - x) > far;
-      spread += (y > v ? y - v : v - y) > far;
+      far = (x > kSpreadFar) + (y > kSpreadFar);
+      near = (x <= kSpreadNear) + (y <= kSpreadNear);
     }
   }
   seen = block_sum(seen, red);
-  spread = block_sum(spread, red);
+  far = block_sum(far, red);
+  near = block_sum(near, red);
   if (threadIdx.x == 0 && seen) {
     atomicAdd(&out[0], seen);
-    atomicAdd(&out[1], spread);
+    atomicAdd(&out[1], far);
+    atomicAdd(&out[2], near);
   }
 }
 
@@ -464,12 +466,11 @@ hipError_t launch_reorder(const int64_t *off, const int32_t *cols, const uint32_
   return hipGetLastError();
 }
 
-hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, int64_t far, unsigned long long *out,
-                         hipStream_t s) {
-  hipError_t e = launch_fill_u64(reinterpret_cast<uint64_t *>(out), 0, 2, s);
-  if (e != hipSuccess) return e;
+hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, uint64_t *out, hipStream_t s) {
   const int64_t samples = n < kSpreadSamples ? n : kSpreadSamples;
-  sample_spread<<<grid_of(samples, 256, 1 << 20), 256, 0, s>>>(off, cols, n, samples, far, out);
+  if (samples <= 0) return hipSuccess;
+  sample_spread<<<grid_of(samples, 256, 1 << 20), 256, 0, s>>>(off, cols, n, samples,
+                                                               reinterpret_cast<unsigned long long *>(out));
   return hipGetLastError();
 }
 

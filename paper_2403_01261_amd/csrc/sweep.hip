@@ -118,10 +118,34 @@ __device__ __forceinline__ uint32_t row_winner(uint32_t (&lab)[D], uint32_t (&w)
   return sorted_winner<D, W>(lab, w);
 }
 
+// Labels [lo, lo + kNearLabels) in LDS (NEAR, sweeps over the list): where most of a
+// row's entries lie near its vertex, most gathers read these.  What bounds the
+// sweep of graphs like the planted batches is the one lane address per cycle
+// that the vector memory path takes, and LDS takes about ten.  A workgroup
+// takes kNearRows list positions around one window: 1,024 planted graphs (30 M
+// vertices), dense sweeps after the first: 1,600 -> 1,170 us per sweep; the batch
+// 28.8 -> 25.7 ms per call, 512 graphs 14.7 -> 13.9.
+constexpr int kNearBlock = 512;
+constexpr int kNearLabels = 16384;
+constexpr int kNearRows = 4096;
+struct Near {
+  const uint32_t *labels;
+  uint32_t lo;
+};
+
+template <bool O32, bool NEAR>
+__device__ __forceinline__ uint32_t near_label(const SweepArgs &a, const Near &w, uint32_t c) {
+  if constexpr (NEAR) {
+    const uint32_t o = c - w.lo;
+    if (o < (uint32_t)kNearLabels) return w.labels[o];
+  }
+  return gather_label<O32>(a.C, (int32_t)c);
+}
+
 // One listed vertex v that takes part in the sweep.
-template <int D, bool W, bool O32, bool V4>
+template <int D, bool W, bool O32, bool V4, bool NEAR>
 __device__ __forceinline__ void thread_vertex(const SweepArgs &a, const SweepView &sv, int32_t v, bool ids,
-                                              LocalCounts &lc) {
+                                              const Near &nw, LocalCounts &lc) {
   // Everything that depends on v alone is loaded at once (absent arrays read
   // constants instead of branching: a branch would make the wave wait for
   // every load issued before it), so a vertex of a dense sweep waits for four
@@ -161,7 +185,7 @@ __device__ __forceinline__ void thread_vertex(const SweepArgs &a, const SweepVie
   } else {
 #pragma unroll
     for (int k = 0; k < D; ++k)
-      lab[k] = lab[k] != (uint32_t)v ? gather_label<O32>(a.C, (int32_t)lab[k]) : kNoLabel - (uint32_t)k;
+      lab[k] = lab[k] != (uint32_t)v ? near_label<O32, NEAR>(a, nw, lab[k]) : kNoLabel - (uint32_t)k;
     if constexpr (W) {
       rowsum = 0;
       load_row<D, V4>(a.w, b, d, 0u, w);
@@ -194,20 +218,50 @@ constexpr int kAhead = 4;
 
 // Registers: weighted rows get as many wavefronts per SIMD as without the
 // first sweep's branch.
-template <int D, bool W, bool O32, bool V4>
-__global__ __launch_bounds__(256, W ? (D <= 8 ? 7 : D <= 16 ? 4 : D <= 32 ? 3 : 1) : 1) void sweep_thread(SweepArgs a, const int32_t *__restrict__ list,
-                                                    int64_t first, int64_t count) {
-  __shared__ unsigned long long red[256 / kWave];
+template <int D, bool W, bool O32, bool V4, bool NEAR>
+__global__ __launch_bounds__(NEAR ? kNearBlock : 256, W ? (D <= 8 ? 7 : D <= 16 ? 4 : D <= 32 ? 3 : 1) : NEAR ? 4 : 1) void
+sweep_thread(SweepArgs a, const int32_t *__restrict__ list, int64_t first, int64_t count, int frontier_only) {
+  constexpr int BLOCK = NEAR ? kNearBlock : 256;
+  __shared__ unsigned long long red[BLOCK / kWave];
+  __shared__ __align__(16) uint32_t window[NEAR ? kNearLabels : 1];
   SweepView sv;
   if (!sweep_view(a, sv)) return;
   LocalCounts lc;
+  const bool ids = a.ids && sv.it == 0;
   // a sparse sweep with a frontier walks the frontier instead of the tier
   const bool front = !sv.dense && sv.front && a.fcount;
+  if (NEAR ? front : frontier_only && !front) return;
+  if constexpr (NEAR) {
+    using Global = const __attribute__((address_space(1))) uint32_t;
+    using Local = __attribute__((address_space(3))) uint32_t;
+    for (int64_t t0 = (int64_t)blockIdx.x * kNearRows; t0 < count; t0 += (int64_t)gridDim.x * kNearRows) {
+      const int64_t tend = t0 + kNearRows < count ? t0 + kNearRows : count, mid = (t0 + tend) / 2;
+      int64_t lo = (list ? (int64_t)list[first + mid] : first + mid) - kNearLabels / 2;
+      lo = lo < 0 ? 0 : lo > a.n - kNearLabels ? a.n - kNearLabels : lo;
+      lo &= ~int64_t(3);  // 16-byte loads of a 16-byte aligned array of at least lo + kNearLabels labels
+      // the first sweep's labels are the ids: its few gathers go to memory
+      const Near nw{window, ids ? 0x80000000u : (uint32_t)lo};
+      if (!ids) {
+        __syncthreads();  // the window before is not read any more
+        const int wave = threadIdx.x / kWave * kWave;
+        for (int q = 4 * wave; q < kNearLabels; q += 4 * BLOCK)
+          __builtin_amdgcn_global_load_lds((Global *)(reinterpret_cast<const uint32_t *>(a.C) + lo + q + 4 * (threadIdx.x % kWave)),
+                                           (Local *)(window + q), 16, 0, 0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part is in LDS
+        __syncthreads();
+      }
+      for (int64_t idx = t0 + threadIdx.x; idx < tend; idx += BLOCK) {
+        const int32_t v = list ? list[first + idx] : (int32_t)(first + idx);
+        if (sv.dense || sv.act[v]) thread_vertex<D, W, O32, V4, true>(a, sv, v, ids, nw, lc);
+      }
+    }
+    flush_counts(a, lc, red);
+    return;
+  }
   if (front) {
     list = a.flist;
     count = *a.fcount;
   }
-  const bool ids = a.ids && sv.it == 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t idx0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx0 < count; idx0 += kAhead * stride) {
     int32_t vv[kAhead];
@@ -221,37 +275,59 @@ __global__ __launch_bounds__(256, W ? (D <= 8 ? 7 : D <= 16 ? 4 : D <= 32 ? 3 : 
     for (int k = 0; k < kAhead; ++k) take[k] = vv[k] >= 0 && (sv.dense || front || sv.act[vv[k]]);
 #pragma unroll 1
     for (int k = 0; k < kAhead; ++k)
-      if (take[k]) thread_vertex<D, W, O32, V4>(a, sv, vv[k], ids, lc);
+      if (take[k]) thread_vertex<D, W, O32, V4, false>(a, sv, vv[k], ids, Near{}, lc);
   }
   flush_counts(a, lc, red);
 }
 
-template <int D, bool V4>
+int grid_for(int64_t items, int per_block, int cap) {
+  int64_t g = (items + per_block - 1) / per_block;
+  if (g < 1) g = 1;
+  return (int)(g > cap ? cap : g);
+}
+
+template <int D, bool V4, bool NEAR>
 void launch_thread_rows(const SweepArgs &a, const int32_t *list, int64_t first, int64_t count, int grid,
-                        hipStream_t s) {
+                        hipStream_t s, int frontier_only = 0) {
+  constexpr int BLOCK = NEAR ? kNearBlock : 256;
   const bool o32 = a.n < (int64_t(1) << 30);
-  if (a.w) {
-    if (o32)
-      sweep_thread<D, true, true, V4><<<grid, 256, 0, s>>>(a, list, first, count);
-    else
-      sweep_thread<D, true, false, V4><<<grid, 256, 0, s>>>(a, list, first, count);
-  } else {
-    if (o32)
-      sweep_thread<D, false, true, V4><<<grid, 256, 0, s>>>(a, list, first, count);
-    else
-      sweep_thread<D, false, false, V4><<<grid, 256, 0, s>>>(a, list, first, count);
+  if constexpr (!NEAR) {
+    if (a.w) {
+      if (o32)
+        sweep_thread<D, true, true, V4, false><<<grid, BLOCK, 0, s>>>(a, list, first, count, frontier_only);
+      else
+        sweep_thread<D, true, false, V4, false><<<grid, BLOCK, 0, s>>>(a, list, first, count, frontier_only);
+      return;
+    }
   }
+  if (o32)
+    sweep_thread<D, false, true, V4, NEAR><<<grid, BLOCK, 0, s>>>(a, list, first, count, frontier_only);
+  else
+    sweep_thread<D, false, false, V4, NEAR><<<grid, BLOCK, 0, s>>>(a, list, first, count, frontier_only);
 }
 
 // 16-byte row loads when the column (and weight) arrays are 16-byte aligned
-// (the library's own copies always are; a caller's array may not be).
+// (the library's own copies always are; a caller's array may not be); windows
+// of near labels when the label array is and holds one.
 template <int D>
-void launch_thread(const SweepArgs &a, const int32_t *list, int64_t first, int64_t count, int grid,
-                   hipStream_t s) {
-  if (((uintptr_t)a.cols & 15) == 0 && ((uintptr_t)a.w & 15) == 0)
-    launch_thread_rows<D, true>(a, list, first, count, grid, s);
+int launch_thread(const SweepArgs &a, const int32_t *list, int64_t first, int64_t count, hipStream_t s) {
+  const bool v4 = ((uintptr_t)a.cols & 15) == 0 && ((uintptr_t)a.w & 15) == 0;
+  const int grid = grid_for(count, 256, kMaxTierGrid);
+  if constexpr (D == 32) {
+    if (a.near && !a.w && v4 && ((uintptr_t)a.C & 15) == 0 && a.n >= kNearLabels) {
+      // the sweeps that walk a frontier are left to a second launch without
+      // windows, whose workgroups are not held to two per compute unit; each
+      // returns at once from the other's sweeps, and both write `grid` records
+      launch_thread_rows<D, true, true>(a, list, first, count, grid, s);
+      launch_thread_rows<D, true, false>(a, list, first, count, grid, s, 1);
+      return grid;
+    }
+  }
+  if (v4)
+    launch_thread_rows<D, true, false>(a, list, first, count, grid, s);
   else
-    launch_thread_rows<D, false>(a, list, first, count, grid, s);
+    launch_thread_rows<D, false, false>(a, list, first, count, grid, s);
+  return grid;
 }
 
 // ---------------------------------------------------------------------------
@@ -491,13 +567,13 @@ __global__ __launch_bounds__(256) void apply_changes(SweepArgs a, int32_t *__res
   }
 }
 
-// Frontier of a sparse sweep (see launch_frontier): four vertices per thread of
-// a 4,096-vertex chunk, whose flags are one word; a chunk without a flag, most
-// of them late in the loop, costs one load.  Ranks within a quarter of the
-// chunk by ballot per tier, one atomic per tier and quarter.  The grid is
-// capped (chunks in a grid-stride loop), so the launch costs little in the
-// sweeps that do not build one.  A flag per thread took 63 us over 30 M
-// vertices with next to none set, 39 now.
+// Frontier of a sparse sweep (see launch_frontier): a workgroup takes a chunk of
+// 4,096 vertices, four per thread, whose flags it reads at once; a chunk
+// without a flag, most of them late in the loop, costs those loads.  Each
+// quarter keeps its order (the sweep's lanes then read neighbouring rows): ranks
+// by ballot per tier, one atomic per tier and quarter.  The grid is capped
+// (chunks in a grid-stride loop), so the launch costs little in the sweeps that
+// do not build one.
 constexpr int kFrontierBlock = 1024;
 constexpr int kFrontierChunk = 4 * kFrontierBlock;
 constexpr int kFrontierGrid = 1024;
@@ -513,15 +589,17 @@ __global__ __launch_bounds__(kFrontierBlock) void frontier_build(SweepArgs a, in
   const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
   const unsigned long long below = (1ull << lane) - 1ull;
   for (int64_t c0 = (int64_t)blockIdx.x * kFrontierChunk; c0 < n; c0 += (int64_t)gridDim.x * kFrontierChunk) {
-    // the flag arrays are padded to whole words
-    const int64_t v0 = c0 + 4 * (int64_t)threadIdx.x;
-    const uint32_t flags = v0 < n ? *reinterpret_cast<const uint32_t *>(sv.act + v0) : 0u;
+    const int64_t v0 = c0 + threadIdx.x;
+    uint32_t flags = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (v0 + q * kFrontierBlock < n && sv.act[v0 + q * kFrontierBlock]) flags |= 1u << q;
     if (!__syncthreads_or(flags != 0)) continue;
 #pragma unroll 1
     for (int q = 0; q < 4; ++q) {
-      const int64_t v = v0 + q;
+      const int64_t v = v0 + q * kFrontierBlock;
       int t = -1;
-      if (v < n && ((flags >> (8 * q)) & 0xffu) && !(a.gid && a.gdone[a.gid[v]])) {
+      if ((flags >> q & 1u) && !(a.gid && a.gdone[a.gid[v]])) {
         t = tier_of(a.off[v + 1] - a.off[v], tb);
         if (t == 0 || t == kNumTiers - 1) t = -1;  // no entries / a hub (the hub kernels read the flags)
       }
@@ -574,12 +652,6 @@ __global__ void fill_u8(uint8_t *p, uint8_t v, int64_t count) {
     p[i] = v;
 }
 
-int grid_for(int64_t items, int per_block, int cap) {
-  int64_t g = (items + per_block - 1) / per_block;
-  if (g < 1) g = 1;
-  return (int)(g > cap ? cap : g);
-}
-
 // Window of list entries per block iteration for a tier of `count` vertices
 // handled by groups of G lanes: as large as the block (one flag check per
 // thread), but small enough that the tier still spreads over about
@@ -608,18 +680,9 @@ hipError_t launch_sweep_tier(int variant, const SweepArgs &a, const int32_t *lis
   if (count <= 0) return hipSuccess;
   int grid = 0;
   switch (variant) {
-    case 0:
-      grid = grid_for(count, 256, kMaxTierGrid);
-      launch_thread<8>(a, list, first, count, grid, s);
-      break;
-    case 15:
-      grid = grid_for(count, 256, kMaxTierGrid);
-      launch_thread<16>(a, list, first, count, grid, s);
-      break;
-    case 16:
-      grid = grid_for(count, 256, kMaxTierGrid);
-      launch_thread<32>(a, list, first, count, grid, s);
-      break;
+    case 0: grid = launch_thread<8>(a, list, first, count, s); break;
+    case 15: grid = launch_thread<16>(a, list, first, count, s); break;
+    case 16: grid = launch_thread<32>(a, list, first, count, s); break;
     case 1: grid = launch_lds<8, 5, 256, 2>(a, list, first, count, s); break;
     case 2: grid = launch_lds<4, 5, 256, 4>(a, list, first, count, s); break;
     case 3: grid = launch_lds<16, 6, 256, 2>(a, list, first, count, s); break;
@@ -635,10 +698,7 @@ hipError_t launch_sweep_tier(int variant, const SweepArgs &a, const int32_t *lis
     case 13: grid = launch_lds<512, 13, 512, 8>(a, list, first, count, s); break;
     case 14: grid = launch_lds<1024, 14, 1024, 8>(a, list, first, count, s); break;
     case 17: grid = launch_lds<256, 11, 256, 4>(a, list, first, count, s); break;
-    case 18:
-      grid = grid_for(count, 256, kMaxTierGrid);
-      launch_thread<64>(a, list, first, count, grid, s);
-      break;
+    case 18: grid = launch_thread<64>(a, list, first, count, s); break;
     default:
       return hipErrorInvalidValue;
   }
