@@ -1270,12 +1270,14 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   if (renumber) {
     if (o.split)
       HIP_TRY(gsl::launch_split(g_off, g_cols, np, C, s.parent, labels_out, nullptr, plan.tier_count,
-                                plan.tier_start, s.list, s.minorig, n, s.rep, s.sigma, clipped(cfg, plan), st));
+                                plan.tier_start, s.list, s.minorig, n, s.rep, s.sigma, clipped(cfg, plan), st,
+                                clustered));
     else
       HIP_TRY(gsl::launch_reorder_scatter(s.list, C, np, n, labels_out, st));
   } else if (o.split) {
     HIP_TRY(gsl::launch_split(offsets, cols, n, C, s.parent, labels_out, s.list, plan.tier_count,
-                              plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st));
+                              plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st,
+                              batch != nullptr || wants_near(plan)));
   }
   if (batch && (rc = finish_batch(s, st, batch, n, labels_out))) return rc;
   if (timed) HIP_TRY(hipEventRecord(s.ev[3], st));
@@ -2106,7 +2108,7 @@ int session_step(gsl_session &S, int32_t sweeps, int64_t capacity, int64_t *done
     HIP_TRY(hipMemcpyAsync(S.sel, sel.data(), sel.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(gsl::launch_session_split_labels(S.lab[S.cur], s.gid, S.sel, N, S.split_in, st));
     HIP_TRY(gsl::launch_split(off, S.cols[S.cur], N, S.split_in, s.parent, S.split_out, s.list, S.plan.tier_count,
-                              S.plan.tier_start, nullptr, nullptr, N, s.rep, s.sigma, cfg, st, s.gid, S.sel));
+                              S.plan.tier_start, nullptr, nullptr, N, s.rep, s.sigma, cfg, st, false, s.gid, S.sel));
   }
   HIP_TRY(gsl::launch_session_finish(S.ranges, (int64_t)r.size(), S.split_out, s.gid, S.cap_g, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -2332,7 +2334,7 @@ int gsl_split(const int64_t *offsets, const int32_t *cols, int64_t n, const int3
   if ((rc = run_plan(s, offsets, n, cfg, st))) return rc;
   Counters plan = *s.ctr_host;
   HIP_TRY(gsl::launch_split(offsets, cols, n, labels_in, s.parent, labels_out, s.list,
-                            plan.tier_count, plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st));
+                            plan.tier_count, plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st, false));
   HIP_TRY(hipStreamSynchronize(st));
   return GSL_OK;
 }
@@ -2366,7 +2368,7 @@ int gsl_split_ex(const int64_t *offsets, const int32_t *cols, int64_t n, const i
   int32_t rounds = 0;
   if (technique == GSL_SPLIT_UNION_FIND) {
     HIP_TRY(gsl::launch_split(offsets, cols, n, labels_in, s.parent, labels_out, s.list, plan.tier_count,
-                              plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, cfg, st));
+                              plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, cfg, st, false));
     rounds = 1;
   } else {
     const bool prune = technique == GSL_SPLIT_LPP;
@@ -2414,7 +2416,7 @@ int gsl_disconnected(const int64_t *offsets, const int32_t *cols, int64_t n, con
   Counters plan = *s.ctr_host;
   // split labels into Cn, then piece counts per community in parent
   HIP_TRY(gsl::launch_split(offsets, cols, n, labels, s.parent, s.Cn, s.list, plan.tier_count, plan.tier_start,
-                            nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st));
+                            nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st, false));
   unsigned long long *cnt = reinterpret_cast<unsigned long long *>(&s.ctr->split_changed);
   HIP_TRY(hipMemsetAsync(cnt, 0, sizeof(*cnt), st));
   HIP_TRY(gsl::launch_disconnected(labels, s.Cn, n, s.parent, flags_out, cnt, st));

@@ -120,6 +120,95 @@ __global__ __launch_bounds__(256) void split_link_first(const int64_t *__restric
   }
 }
 
+// The same first pass where a row's neighbours mostly lie near its vertex
+// (batches of small graphs, cluster order): a workgroup takes kLinkTile
+// consecutive vertices, joins the linked entries that fall among them in an LDS
+// forest, writes every vertex's root in the tile as its parent, and leaves the
+// entries that lead out of the tile to split_link_rest.  The pass above waits
+// on the global forest, a chain of loads and a device-scope compare-and-swap
+// for nearly every vertex; here most of them are LDS accesses (1,024 planted
+// graphs, 30 M vertices: 3.18 ms, 1.88 here; 24 M road vertices in cluster order
+// 1.44, 0.85).
+constexpr int kLinkTile = 4096;
+constexpr int kLinkTileBlock = 512;
+
+__device__ __forceinline__ int32_t lds_root(int32_t *par, int32_t x) {
+  for (;;) {
+    const int32_t p = __hip_atomic_load(par + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (p == x) return x;
+    const int32_t gp = __hip_atomic_load(par + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (gp != p) __hip_atomic_store(par + x, gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    x = gp;
+  }
+}
+
+__device__ __forceinline__ void lds_unite(int32_t *par, int32_t a, int32_t b) {
+  a = lds_root(par, a);
+  b = lds_root(par, b);
+  while (a != b) {
+    const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
+    int32_t expected = hi;
+    if (__hip_atomic_compare_exchange_strong(par + hi, &expected, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP))
+      return;
+    a = lds_root(par, expected);
+    b = lds_root(par, lo);
+  }
+}
+
+__global__ __launch_bounds__(kLinkTileBlock) void split_link_tile(const int64_t *__restrict__ off,
+                                                                  const int32_t *__restrict__ cols,
+                                                                  const int32_t *__restrict__ C, int32_t *parent,
+                                                                  int64_t n, unsigned long long *__restrict__ rest) {
+  __shared__ int32_t par[kLinkTile];
+  for (int64_t base = (int64_t)blockIdx.x * kLinkTile; base < n; base += (int64_t)gridDim.x * kLinkTile) {
+    for (int i = threadIdx.x; i < kLinkTile; i += kLinkTileBlock) par[i] = i;
+    __syncthreads();
+    for (int i = threadIdx.x; i < kLinkTile && base + i < n; i += kLinkTileBlock) {
+      const int64_t u = base + i, b = off[u];
+      const int64_t e = off[u + 1] < b + kLinkScan ? off[u + 1] : b + kLinkScan;
+      const int32_t cu = C[u];
+      uint32_t out[kLinkFirst] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+      int seen = 0;
+      for (int64_t p0 = b; p0 < e && seen < kLinkFirst; p0 += kLinkChunk) {
+        int32_t v[kLinkChunk];
+        bool hit[kLinkChunk];
+#pragma unroll
+        for (int k = 0; k < kLinkChunk; ++k) v[k] = p0 + k < e ? cols[p0 + k] : (int32_t)u;
+#pragma unroll
+        for (int k = 0; k < kLinkChunk; ++k) hit[k] = v[k] != (int32_t)u && C[v[k]] == cu;
+#pragma unroll
+        for (int k = 0; k < kLinkChunk; ++k)
+          if (hit[k] && seen < kLinkFirst) {
+            const int64_t at = v[k] - base;
+            if (at >= 0 && at < kLinkTile)
+              lds_unite(par, i, (int32_t)at);
+            else if (seen == 0)
+              out[0] = (uint32_t)v[k];
+            else
+              out[1] = (uint32_t)v[k];
+            ++seen;
+          }
+      }
+      rest[u] = (unsigned long long)out[1] << 32 | out[0];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kLinkTile && base + i < n; i += kLinkTileBlock)
+      parent[base + i] = (int32_t)(base + lds_root(par, i));
+    __syncthreads();  // par is written again
+  }
+}
+
+__global__ __launch_bounds__(256) void split_link_rest(int32_t *parent, int64_t n,
+                                                       const unsigned long long *__restrict__ rest) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += stride) {
+    const unsigned long long r = rest[u];
+    if ((int32_t)(uint32_t)r >= 0) unite(parent, (int32_t)u, (int32_t)(uint32_t)r);
+    if ((int32_t)(r >> 32) >= 0) unite(parent, (int32_t)u, (int32_t)(r >> 32));
+  }
+}
+
 __global__ void split_flatten(int32_t *parent, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
@@ -475,6 +564,7 @@ hipError_t launch_disconnected(const int32_t *labels, const int32_t *comp, int64
 // Split on a graph whose vertices are grouped by tier (tier t occupies
 // [tier_start[t], tier_start[t] + tier_count[t]) of `list`, or of the ids
 // themselves when list is NULL).
+//  near: most entries lie near their vertex (speed only).
 //  orig == NULL : the graph is in caller ids; out[i] = smallest id of i's piece.
 //  orig != NULL : the graph is the renumbered copy of its n non-isolated
 //                 vertices, orig[p] the caller id of vertex p (orig holds
@@ -484,12 +574,17 @@ hipError_t launch_split(const int64_t *off, const int32_t *cols, int64_t n, cons
                         int32_t *parent, int32_t *out, const int32_t *list,
                         const int64_t *tier_count_host, const int64_t *tier_start_host,
                         const int32_t *orig, int32_t *minorig, int64_t n_total, int32_t *rep,
-                        unsigned long long *cp, const TierConfig &cfg, hipStream_t s, const int32_t *gid,
+                        unsigned long long *cp, const TierConfig &cfg, hipStream_t s, bool near, const int32_t *gid,
                         const uint8_t *sel) {
   constexpr int kCap = 256 * 16;
   if (n > 0) {
-    split_init<<<grid_cap(n, 256, kCap), 256, 0, s>>>(parent, n);
-    split_link_first<<<grid_cap(n, 256, kCap), 256, 0, s>>>(off, cols, C, parent, n, gid, sel);
+    if (near && !gid) {
+      split_link_tile<<<grid_cap(n, kLinkTile, kCap), kLinkTileBlock, 0, s>>>(off, cols, C, parent, n, cp);
+      split_link_rest<<<grid_cap(n, 256, kCap), 256, 0, s>>>(parent, n, cp);
+    } else {
+      split_init<<<grid_cap(n, 256, kCap), 256, 0, s>>>(parent, n);
+      split_link_first<<<grid_cap(n, 256, kCap), 256, 0, s>>>(off, cols, C, parent, n, gid, sel);
+    }
     split_flatten<<<grid_cap(n, 256, kCap), 256, 0, s>>>(parent, n);
     split_rep<<<grid_cap(n, 256, kCap), 256, 0, s>>>(C, parent, n, rep);
     split_pack<<<grid_cap(n, 256, kCap), 256, 0, s>>>(C, parent, n, cp);
