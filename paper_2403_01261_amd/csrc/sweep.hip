@@ -69,8 +69,8 @@ __device__ __forceinline__ void flush_counts(const SweepArgs &a, const LocalCoun
 // and the largest seen with its label.  A run's partial sums never exceed its
 // total, so the largest is that of the label with the largest total (the
 // smallest such label on ties, which comes first).  Entries j == i and the
-// padding beyond the row carry values above every label, one of each, which
-// sort last and win only where there is no label.  W: weighted rows; without
+// padding beyond the row carry values above every label, one of each and
+// without weight, which sort last and win only where there is no label.  W: weighted rows; without
 // it every entry weighs 1.
 //
 // The sweep waits on its vector memory instructions (row loads and label
@@ -190,7 +190,10 @@ __device__ __forceinline__ void thread_vertex(const SweepArgs &a, const SweepVie
       rowsum = 0;
       load_row<D, V4>(a.w, b, d, 0u, w);
 #pragma unroll
-      for (int k = 0; k < D; ++k) rowsum += w[k];
+      for (int k = 0; k < D; ++k) {
+        rowsum += w[k];
+        w[k] = (int32_t)lab[k] >= 0 ? w[k] : 0u;  // an entry of the row's own vertex counts for no label
+      }
     }
     winner = row_winner<W>(lab, w, d);
   }

@@ -49,7 +49,7 @@ def circulant(longest, weighted, odd, seed):
     if not odd:
         perm = np.arange(N)
     u, v = perm[rows], perm[cols]
-    w = (np.minimum(u, v) * 31 + np.maximum(u, v)) % 4 if weighted else None
+    w = np.where(u == v, 9, (np.minimum(u, v) * 31 + np.maximum(u, v)) % 4) if weighted else None
     order = np.argsort(rng.random(u.size), kind="stable") if odd else np.lexsort((v, u))
     return graphgen.from_entries(N, u[order], v[order], None if w is None else w[order])
 
