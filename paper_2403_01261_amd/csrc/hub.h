@@ -16,13 +16,14 @@ constexpr int kTabSlots = 1 << kTabLog2;
 constexpr int kMaxParts = kHubMaxParts;
 constexpr int kPartSize = 2048;               // expected distinct labels per partition
 constexpr int kMergeBlock = 256;
+constexpr int kMergeAhead = 4;                // staged records each lane of a merge has on the way
 constexpr int kHubFoldRounds = 1;  // label fold rounds per wave before the inserts (as in the tiers)
 // Claims before a merge pass gives up and the partition is split into
 // sub-passes: at most kHubMergeCapMax, so that a free slot always remains
 // (up to kMergeBlock threads may pass the check at once); a smaller cap can
 // be set at run time to exercise the sub-pass path on small graphs.
 static_assert(kHubMergeCapMax + kMergeBlock < kTabSlots, "a free slot must always remain");
-constexpr int kChunkGroup = 1024;                       // chunks whose slices one merge step indexes
+constexpr int kChunkGroup = 512;                        // chunks whose slices one merge step indexes
 
 static_assert(kHubChunk % kHubBlock == 0, "chunk must split evenly over the block");
 static_assert(2 * kHubChunk <= kTabSlots, "insert table must hold every chunk entry");

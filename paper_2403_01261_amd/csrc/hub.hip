@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kHubBlock) void hub_insert(SweepArgs a, HubArgs h) 
 
 __global__ __launch_bounds__(kMergeBlock) void hub_merge(SweepArgs a, HubArgs h) {
   __shared__ unsigned long long tab[kTabSlots];
-  __shared__ int pre[kChunkGroup + 1];
+  __shared__ int pre[kChunkGroup + 1], slice[kChunkGroup];
   __shared__ int scan_part[kMergeBlock / kWave];
   __shared__ int claimed, overflow;
   __shared__ unsigned long long red[kMergeBlock / kWave];
@@ -185,30 +185,39 @@ __global__ __launch_bounds__(kMergeBlock) void hub_merge(SweepArgs a, HubArgs h)
         const int gn = (int)(nc - g0 < kChunkGroup ? nc - g0 : kChunkGroup);
         for (int i = threadIdx.x; i < gn; i += kMergeBlock) {
           const int32_t *hc = gh + (g0 + i) * (P + 1);
-          pre[i] = hc[p_hi] - hc[p_lo];
+          slice[i] = hc[p_lo];  // kept: the records' loads below would wait for it again
+          pre[i] = hc[p_hi] - slice[i];
         }
         __syncthreads();
         block_exclusive_scan<kMergeBlock>(pre, gn, scan_part);
         const int total = pre[gn];
-        for (int t = threadIdx.x; t < total; t += kMergeBlock) {
-          int lo = 0, hi = gn;  // chunk i with pre[i] <= t < pre[i + 1]
-          while (hi - lo > 1) {
-            const int mid = (lo + hi) / 2;
-            if (pre[mid] <= t)
-              lo = mid;
-            else
-              hi = mid;
+        for (int t0 = threadIdx.x; t0 < total; t0 += kMergeAhead * kMergeBlock) {
+          unsigned long long xv[kMergeAhead];
+#pragma unroll
+          for (int u = 0; u < kMergeAhead; ++u) {
+            const int t = t0 + u * kMergeBlock;
+            int lo = 0, hi = gn;  // chunk i with pre[i] <= t < pre[i + 1]
+            while (hi - lo > 1) {
+              const int mid = (lo + hi) / 2;
+              if (pre[mid] <= t)
+                lo = mid;
+              else
+                hi = mid;
+            }
+            xv[u] = t < total ? stage[(g0 + lo) * kHubChunk + slice[lo] + (t - pre[lo])] : kEmptySlot;
           }
-          const int32_t *hc = gh + (g0 + lo) * (P + 1);
-          const unsigned long long xv = stage[(g0 + lo) * kHubChunk + hc[p_lo] + (t - pre[lo])];
-          const uint32_t label = (uint32_t)(xv >> 32);
-          if (R > 1 && (sub_of(label) & (R - 1)) != r) continue;
-          if (__hip_atomic_load(&overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) continue;
-          if (__hip_atomic_load(&claimed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= h.merge_cap) {
-            overflow = 1;
-            continue;
+#pragma unroll
+          for (int u = 0; u < kMergeAhead; ++u) {
+            if (xv[u] == kEmptySlot) continue;
+            const uint32_t label = (uint32_t)(xv[u] >> 32);
+            if (R > 1 && (sub_of(label) & (R - 1)) != r) continue;
+            if (__hip_atomic_load(&overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) continue;
+            if (__hip_atomic_load(&claimed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= h.merge_cap) {
+              overflow = 1;
+              continue;
+            }
+            if (lds_insert(tab, kTabLog2, label, (uint32_t)xv[u]) >= 0) atomicAdd(&claimed, 1);
           }
-          if (lds_insert(tab, kTabLog2, label, (uint32_t)xv) >= 0) atomicAdd(&claimed, 1);
         }
         __syncthreads();
       }

@@ -308,7 +308,6 @@ constexpr int kHubKF = kHubChunk / kHubBlockF;
 // A merge workgroup's 12-byte slots leave room for two of them per compute
 // unit, so they are wide, and each lane has kMergeAhead records on the way.
 constexpr int kMergeBlockF = 512;
-constexpr int kMergeAhead = 4;
 constexpr int kMergeCapF = kTabSlots - kMergeBlockF - 1;  // a free slot always remains
 
 // Partitions that one merge workgroup takes (see hub_merge).
@@ -386,7 +385,7 @@ __global__ __launch_bounds__(kHubBlockF) void hubf_insert(SweepArgs a, HubArgs h
 __global__ __launch_bounds__(kMergeBlockF) void hubf_merge(SweepArgs a, HubArgs h, HubF f) {
   __shared__ uint32_t keys[kTabSlots];
   __shared__ double sums[kTabSlots];
-  __shared__ int pre[kChunkGroup + 1];
+  __shared__ int pre[kChunkGroup + 1], slice[kChunkGroup];
   __shared__ int scan_part[kMergeBlockF / kWave];
   __shared__ int claimed, overflow;
   __shared__ double rw[kMergeBlockF / kWave];
@@ -425,7 +424,8 @@ __global__ __launch_bounds__(kMergeBlockF) void hubf_merge(SweepArgs a, HubArgs 
         const int gn = (int)(nc - g0 < kChunkGroup ? nc - g0 : kChunkGroup);
         for (int i = threadIdx.x; i < gn; i += kMergeBlockF) {
           const int32_t *hc = gh + (g0 + i) * (P + 1);
-          pre[i] = hc[p_hi] - hc[p_lo];
+          slice[i] = hc[p_lo];
+          pre[i] = hc[p_hi] - slice[i];
         }
         __syncthreads();
         block_exclusive_scan<kMergeBlockF>(pre, gn, scan_part);
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(kMergeBlockF) void hubf_merge(SweepArgs a, HubArgs 
               else
                 hi = mid;
             }
-            at[u] = t < total ? stage + (g0 + lo) * kHubChunk + (gh + (g0 + lo) * (P + 1))[p_lo] + (t - pre[lo]) : -1;
+            at[u] = t < total ? stage + (g0 + lo) * kHubChunk + slice[lo] + (t - pre[lo]) : -1;
           }
 #pragma unroll
           for (int u = 0; u < kMergeAhead; ++u) {
