@@ -867,6 +867,10 @@ gsl::TierConfig clipped(gsl::TierConfig cfg, const Counters &plan) {
   return cfg;
 }
 
+// Rows of 33 - 64 entries from which a thread each fills the device: with the
+// 6,000 of a planted graph of 1.9 M vertices a call took 3.10 ms instead of 2.98.
+constexpr int64_t kThread64Rows = int64_t(1) << 16;
+
 // The smallest thread-per-vertex variant for rows of up to `longest` entries
 // in place of a larger one; other variants stay.
 int thread_variant(int variant, int64_t longest) {
@@ -1071,6 +1075,12 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   int variant[gsl::kNumTiers];
   for (int t = 0; t < gsl::kNumTiers; ++t)
     variant[t] = is_default_tiers(cfg) ? thread_variant(cfg.variant[t], (int64_t)plan.max_degree) : cfg.variant[t];
+  // ... and, in the caller's layout with unit weights, its rows of 33 - 64
+  // entries a thread each too, instead of 16 lanes and a table (1,024 planted
+  // graphs 24.2 -> 22.4 ms, 117 graphs 3.85 -> 3.65 ms; weighted R-MAT scale 22
+  // 8.67 -> 8.81 with it, and power-law graphs' rows are few there).
+  if (is_default_tiers(cfg) && !f32 && !weights && !renumber && plan.tier_count[2] >= kThread64Rows)
+    variant[2] = 18;
 
   // Timing records (timing mode only).
   std::vector<Launch> launches;
