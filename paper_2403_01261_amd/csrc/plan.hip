@@ -17,50 +17,52 @@ namespace {
 
 constexpr int kPlanBlock = 1024;
 
+// The row entries per tier and the longest row are added once per workgroup, of
+// which at most kPlanGrid share the blocks of vertices: an atomic per tier and
+// block of 1,024 vertices on the same few words took most of the 388 us of a
+// launch over 30 M vertices, 166 now.
+constexpr int64_t kPlanGrid = 2048;
 __global__ __launch_bounds__(kPlanBlock) void plan_count(const int64_t *__restrict__ off, int64_t n,
                                                          int64_t *__restrict__ blk_counts,
                                                          Counters *ctr, TierBounds tb) {
   __shared__ int cnt[kNumTiers];
   __shared__ unsigned long long ecnt[kNumTiers];
   __shared__ unsigned long long dmax[kPlanBlock / kWave];
-  if (threadIdx.x < kNumTiers) {
-    cnt[threadIdx.x] = 0;
-    ecnt[threadIdx.x] = 0;
-  }
-  __syncthreads();
-  const int64_t v = (int64_t)blockIdx.x * kPlanBlock + threadIdx.x;
+  if (threadIdx.x < kNumTiers) ecnt[threadIdx.x] = 0;
   const int lane = threadIdx.x % kWave;
-  int64_t d = 0;
-  int t = -1;
-  if (v < n) {
-    d = off[v + 1] - off[v];
-    t = tier_of(d, tb);
-  }
-  // Per wave: one LDS add per tier present (ballot), with the wave's sum of
-  // the degrees of that tier -- not one contended LDS atomic per vertex.
-  for (int k = 0; k < kNumTiers; ++k) {
-    const unsigned long long m = __ballot(t == k);
-    if (!m) continue;
-    unsigned long long e = t == k && d > 0 ? (unsigned long long)d : 0ull;
-    e = wave_sum(e);
-    if (lane == 0) {
-      atomicAdd(&cnt[k], __popcll(m));
-      if (e) atomicAdd(&ecnt[k], e);
+  unsigned long long mx = 0;
+  const int64_t nblk = (n + kPlanBlock - 1) / kPlanBlock;
+  for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+    if (threadIdx.x < kNumTiers) cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t v = blk * kPlanBlock + threadIdx.x;
+    int64_t d = 0;
+    int t = -1;
+    if (v < n) {
+      d = off[v + 1] - off[v];
+      t = tier_of(d, tb);
     }
+    // Per wave: one LDS add per tier present (ballot), with the wave's sum of
+    // the degrees of that tier -- not one contended LDS atomic per vertex.
+    for (int k = 0; k < kNumTiers; ++k) {
+      const unsigned long long m = __ballot(t == k);
+      if (!m) continue;
+      unsigned long long e = t == k && d > 0 ? (unsigned long long)d : 0ull;
+      e = wave_sum(e);
+      if (lane == 0) {
+        atomicAdd(&cnt[k], __popcll(m));
+        if (e) atomicAdd(&ecnt[k], e);
+      }
+    }
+    mx = d > 0 && (unsigned long long)d > mx ? (unsigned long long)d : mx;
+    __syncthreads();
+    if (threadIdx.x < kNumTiers) blk_counts[blk * kNumTiers + threadIdx.x] = cnt[threadIdx.x];
   }
-  unsigned long long mx = (unsigned long long)(d > 0 ? d : 0);
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    const unsigned long long y = __shfl_xor(mx, o, kWave);
-    mx = y > mx ? y : mx;
-  }
+  mx = group_max<kWave>(mx);
   if (lane == 0) dmax[threadIdx.x / kWave] = mx;
   __syncthreads();
-  if (threadIdx.x < kNumTiers) {
-    blk_counts[(int64_t)blockIdx.x * kNumTiers + threadIdx.x] = cnt[threadIdx.x];
-    if (ecnt[threadIdx.x])
-      atomicAdd(reinterpret_cast<unsigned long long *>(&ctr->tier_edges[threadIdx.x]), ecnt[threadIdx.x]);
-  }
+  if (threadIdx.x < kNumTiers && ecnt[threadIdx.x])
+    atomicAdd(reinterpret_cast<unsigned long long *>(&ctr->tier_edges[threadIdx.x]), ecnt[threadIdx.x]);
   if (threadIdx.x == 0) {
     unsigned long long mm = 0;
     for (int k = 0; k < kPlanBlock / kWave; ++k) mm = dmax[k] > mm ? dmax[k] : mm;
@@ -204,7 +206,7 @@ hipError_t launch_plan(const int64_t *off, int64_t n, int32_t *list, int64_t *bl
   for (int t = 0; t < kNumTiers; ++t) tb.b[t] = cfg.bound[t];
   const int64_t ngrp = plan_blocks(nblk);
   int64_t *grp = blk_counts + nblk * kNumTiers;  // group totals (plan_scratch)
-  plan_count<<<(unsigned)nblk, kPlanBlock, 0, s>>>(off, n, blk_counts, ctr, tb);
+  plan_count<<<(unsigned)(nblk < kPlanGrid ? nblk : kPlanGrid), kPlanBlock, 0, s>>>(off, n, blk_counts, ctr, tb);
   plan_scan_sums<<<(unsigned)ngrp, kPlanBlock, 0, s>>>(blk_counts, nblk, grp);
   plan_scan<<<1, kPlanBlock, 0, s>>>(grp, ngrp, ctr);
   plan_scan_add<<<(unsigned)ngrp, kPlanBlock, 0, s>>>(blk_counts, nblk, grp);
