@@ -151,6 +151,38 @@ __global__ __launch_bounds__(kBlock) void gather_entries(const GraphDesc *__rest
                                                          uint32_t *__restrict__ w, uint32_t *__restrict__ bad) {
   for (int64_t t0 = (int64_t)blockIdx.x * kTile; t0 < nnz; t0 += (int64_t)gridDim.x * kTile) {
     int64_t g = tile_graph(edge_base, G, t0);
+    const int64_t tend = t0 + kTile < nnz ? t0 + kTile : nnz;
+    if (edge_base[g + 1] >= tend) {
+      // the whole tile lies in graph g (most tiles): one descriptor, all loads
+      // at once (117 graphs, 70 M entries: 235 us entry by entry, 91 here)
+      const GraphDesc x = d[g];
+      const int64_t src = x.offsets[0] + (t0 - edge_base[g]);
+      const uint64_t most = (uint64_t)(vtx_base[g + 1] - vtx_base[g]);
+      const int32_t vb = (int32_t)(vshift + vtx_base[g]);
+      int32_t c[kPerThread];
+      bool out = false;
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j) {
+        const int64_t k = (int64_t)j * kBlock + threadIdx.x;
+        c[j] = t0 + k < tend ? x.cols[src + k] : 0;
+      }
+#pragma unroll
+      for (int j = 0; j < kPerThread; ++j) {
+        const int64_t k = (int64_t)j * kBlock + threadIdx.x;
+        const bool bad_entry = (uint64_t)(uint32_t)c[j] >= most;
+        out = out || (bad_entry && t0 + k < tend);
+        if (t0 + k < tend) cols[t0 + k] = (bad_entry ? 0 : c[j]) + vb;
+      }
+      if (out) atomicOr(&bad[g], 1u);
+      if (w) {
+#pragma unroll 4
+        for (int j = 0; j < kPerThread; ++j) {
+          const int64_t k = (int64_t)j * kBlock + threadIdx.x;
+          if (t0 + k < tend) w[t0 + k] = x.weights ? x.weights[src + k] : 1u;
+        }
+      }
+      continue;
+    }
 #pragma unroll 4
     for (int j = 0; j < kPerThread; ++j) {
       const int64_t e = t0 + (int64_t)j * kBlock + threadIdx.x;
