@@ -62,8 +62,13 @@ typedef struct gsl_options {
   int32_t layout; /* 0 (default): automatic; 1: always sweep a degree-ordered
                      renumbered copy of the graph (hubs first), which packs
                      the labels of high-degree vertices together; 2: never.
+                     Automatic takes that copy where rows of degree > 64 hold
+                     most entries, and a copy in another order for graphs of
+                     2 M vertices and more with few entries a row that lie far
+                     from it (road graphs under a random numbering).
                      The copy costs nnz * 4 (+ nnz * 4 with weights) bytes of
-                     device memory.  Results are identical either way. */
+                     device memory and up to 48 a vertex.  Results are
+                     identical either way. */
   int32_t async_sweeps; /* nonzero: asynchronous sweeps as the paper's lpaMove
                      runs them (Alg. 3) -- a changed label is written in
                      place at once, so later vertices of the same sweep may
