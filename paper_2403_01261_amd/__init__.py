@@ -567,10 +567,11 @@ def variant_kernel_name(v: dict, weighted: bool = False, n: int = 0, aligned: bo
     the thread variants have weighted and unit-weight kernels, each with
     32-bit gather offsets for fewer than 2^30 vertices or 64-bit ones, and
     16-byte row loads when the column and weight arrays are 16-byte aligned,
-    as the library's own copies always are)."""
+    as the library's own copies always are; graphs whose rows name near
+    vertices only run the kernel whose last argument is true)."""
     if v["group"] == 1:
         t = lambda x: "true" if x else "false"  # noqa: E731
-        return "sweep_thread<%d, %s, %s, %s>" % (v["per_lane"], t(weighted), t(n < (1 << 30)), t(aligned))
+        return "sweep_thread<%d, %s, %s, %s, false>" % (v["per_lane"], t(weighted), t(n < (1 << 30)), t(aligned))
     return "sweep_lds<%d, %d, %d, %d>" % (v["group"], v["table_log2"], v["block"], v["per_lane"])
 
 

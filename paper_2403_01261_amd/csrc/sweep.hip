@@ -70,8 +70,8 @@ __device__ __forceinline__ void flush_counts(const SweepArgs &a, const LocalCoun
 // total, so the largest is that of the label with the largest total (the
 // smallest such label on ties, which comes first).  Entries j == i and the
 // padding beyond the row carry values above every label, one of each and
-// without weight, which sort last and win only where there is no label.  W: weighted rows; without
-// it every entry weighs 1.
+// without weight, which sort last and win only where there is no label.
+// W: weighted rows; without it every entry weighs 1.
 //
 // The sweep waits on its vector memory instructions (row loads and label
 // gathers, one lane access each; the texture addresser is busy 85 % of the
