@@ -602,10 +602,10 @@ __device__ __forceinline__ int64_t small_heavy(const SmallArgs &a, Shared<BLOCK>
 // meeting or a barrier.  Such a sweep takes 60 us (2^16 vertices of an R-MAT
 // graph) to 120 us (2^18), which the general path then repeats; the sample
 // takes 6 us (whole calls of 2^12, 2^16 and 2^18 vertices: 766 -> 734, 1,092 ->
-// 1,023 and 1,586 -> 1,477 us; accepted calls within 1 us).  Near
-// a half the share is not clear from 512 rows, and a call turned away wrongly
-// loses more (400 us and up) than one let through: the line is three fifths.  The rows are spread by a multiplicative hash: no period
-// of the ids meets it.
+// 1,023 and 1,586 -> 1,477 us; accepted calls within 1 us).  Near a half
+// the share is not clear from 512 rows, and a call turned away wrongly loses
+// more (400 us and up) than one let through: the line is three fifths.  The
+// rows are spread by a multiplicative hash: no period of the ids meets it.
 constexpr int kSampleRows = 8;  // rows per lane
 
 template <int BLOCK>
