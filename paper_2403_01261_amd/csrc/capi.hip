@@ -646,16 +646,20 @@ struct Launch {
 };
 
 // ---- small graphs: the whole call in one launch (small.hip) ----
-// Vertices up to which a call runs as one launch.
-constexpr int64_t kSmallMaxVertices = int64_t(1) << 18;
+// Vertices up to which a call runs as one launch.  With weights a CU holds one
+// workgroup only: 199,999 vertices of degree 32 take 990 us that way and 915 us
+// on the general path (unit weights are faster here throughout).
+constexpr int64_t kSmallMaxVertices = int64_t(1) << 18, kSmallMaxWeighted = int64_t(1) << 17;
+constexpr int64_t small_vertices(bool weighted) { return weighted ? kSmallMaxWeighted : kSmallMaxVertices; }
 constexpr int64_t kSmallMaxEntries = int64_t(1) << 24;
 constexpr int64_t kSmallMaxGraphs = 4096;
-// Ticks (100 MHz) after which a workgroup's wait for the others gives up: 1 s,
-// unless GSL_SMALL_WAIT_TICKS says otherwise when the library is first used.
+// Ticks (100 MHz) after which a workgroup's wait for the others gives up: 50 ms,
+// far above any meeting and what other streams' kernels hold a CU for, unless
+// GSL_SMALL_WAIT_TICKS says otherwise when the library is first used.
 long long small_wait_ticks() {
   static const long long ticks = [] {
     const char *e = getenv("GSL_SMALL_WAIT_TICKS");
-    return e ? atoll(e) : 100000000ll;
+    return e ? atoll(e) : 5000000ll;
   }();
   return ticks;
 }
@@ -922,7 +926,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   // bounds only)
   const gsl::TierConfig cfg = f32 ? gsl::kF32Tiers : current_tiers();
   const HubLimits hub_lim = current_hub_limits();
-  if (n <= kSmallMaxVertices && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
+  if (n <= small_vertices(weights != nullptr) && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
       !o.async_sweeps && o.layout != 1 && (!batch || batch->graphs <= kSmallMaxGraphs) &&
       is_default_tiers(cfg)) {
     rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch);
@@ -1951,7 +1955,7 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, bo
   Scratch &s = S.s;
   const hipStream_t st = S.stream;
   const int64_t N = S.vtop, G = (int64_t)S.cap_g + 1;
-  if (N > kSmallMaxVertices || S.etop > kSmallMaxEntries || G > kSmallMaxGraphs || !is_default_tiers(cfg)) return GSL_OK;
+  if (N > small_vertices(S.weighted) || S.etop > kSmallMaxEntries || G > kSmallMaxGraphs || !is_default_tiers(cfg)) return GSL_OK;
   for (const SessionSlot &x : S.slot)
     if (x.live && x.longest > gsl::kSmallMaxDegree) return GSL_OK;
   const int grid = gsl::small_grid(N, S.weighted, true);

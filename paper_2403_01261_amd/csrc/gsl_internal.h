@@ -198,7 +198,15 @@ struct TierGrids {
 };
 
 // ---- small graphs: the whole call in one launch (small.hip) ----
-constexpr int kSmallGrid = 1024;          // most workgroups of a launch (all resident at once)
+// Most workgroups of a launch, all resident at once: two per CU, with weights
+// one.  Registers and LDS are given out in one piece, so what a CU has room for
+// is what fits however the workgroups there lie, other streams' kernels having
+// come and gone between them: beside one of 128 registers (or of 256) a second
+// of 128 always fits, a third need not, nor a second of 256.  Four and two per
+// CU, which fit an idle device exactly, left one of two concurrent launches
+// waiting for its limit (a server with two slots: p50 805 ms at 2,000 requests
+// a second).
+constexpr int kSmallGrid = 512;
 constexpr int64_t kSmallOne = 256;        // graphs up to here run in one workgroup, in LDS
 constexpr int kSmallMaxSweeps = 100;
 constexpr int kSmallMaxDegree = 2048;     // rows above: the general path
