@@ -653,13 +653,13 @@ constexpr int64_t kSmallMaxVertices = int64_t(1) << 18, kSmallMaxWeighted = int6
 constexpr int64_t small_vertices(bool weighted) { return weighted ? kSmallMaxWeighted : kSmallMaxVertices; }
 constexpr int64_t kSmallMaxEntries = int64_t(1) << 24;
 constexpr int64_t kSmallMaxGraphs = 4096;
-// Ticks (100 MHz) after which a workgroup's wait for the others gives up: 50 ms,
-// far above any meeting and what other streams' kernels hold a CU for, unless
-// GSL_SMALL_WAIT_TICKS says otherwise when the library is first used.
+// Ticks (100 MHz) after which a workgroup's wait for the others gives up: 5 ms,
+// far above any meeting (3 us) and what a window of the longest rows takes (1
+// ms), unless GSL_SMALL_WAIT_TICKS says otherwise when the library is first used.
 long long small_wait_ticks() {
   static const long long ticks = [] {
     const char *e = getenv("GSL_SMALL_WAIT_TICKS");
-    return e ? atoll(e) : 5000000ll;
+    return e ? atoll(e) : 500000ll;
   }();
   return ticks;
 }
@@ -672,16 +672,35 @@ static_assert(kSmallRecBytes + kSmallTierRecBytes + (int64_t)gsl::kSmallGrid * 8
 
 // Workgroups of small-graph launches in flight per device (a weighted one
 // counts twice, for its registers).  They wait for each other, so together
-// they must fit the device: a call that would pass kSmallGrid takes the
-// general path instead.
+// they must fit the device.  Beside another call of the library a launch is
+// taken up to kSmallShared of them only, half a workgroup per CU: each launch
+// deals its workgroups out over the XCDs from the first one on, so two that just
+// fit the device may not fit an XCD, and a workgroup of another call that needs
+// much LDS holds up those queued behind it.  Other calls take the general path.
+constexpr int kSmallShared = 128;
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_small_blocks[kMaxDevices];
+std::atomic<int> g_calls[kMaxDevices];  // calls in flight, on either path
+
+struct InFlight {  // one call, until it returns
+  int dev;
+  bool alone = false;
+  explicit InFlight(int device) : dev(device >= 0 && device < kMaxDevices ? device : -1) {
+    if (dev >= 0) alone = g_calls[dev].fetch_add(1) == 0;
+  }
+  ~InFlight() {
+    if (dev >= 0) g_calls[dev].fetch_sub(1);
+  }
+  InFlight(const InFlight &) = delete;
+  InFlight &operator=(const InFlight &) = delete;
+};
 
 struct SmallSlots {  // the share of one call, given back when it returns
   int dev = -1, blocks = 0;
-  bool take(int device, int want) {
+  bool take(int device, int want, bool alone) {
     if (device < 0 || device >= kMaxDevices) return false;
-    if (g_small_blocks[device].fetch_add(want) + want > gsl::kSmallGrid) {
+    const int before = g_small_blocks[device].fetch_add(want);
+    if (before + want > (alone && before == 0 ? gsl::kSmallGrid : kSmallShared)) {
       g_small_blocks[device].fetch_sub(want);
       return false;
     }
@@ -781,12 +800,10 @@ bool is_default_tiers(const gsl::TierConfig &c) {
 // path has to run it (nothing but scratch and outputs has been written then).
 int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
                int64_t n, int32_t max_iters, double tolerance, const gsl_options &o, gsl_stats *stats,
-               int32_t *labels_out, const Batch *batch) {
-  int dev = 0;
-  HIP_TRY(hipGetDevice(&dev));
+               int32_t *labels_out, const Batch *batch, const InFlight &call) {
   const int grid = gsl::small_grid(n, weights != nullptr, batch != nullptr);
   SmallSlots share;
-  if (!share.take(dev, weights ? 2 * grid : grid)) return kGeneral;
+  if (!share.take(call.dev, weights ? 2 * grid : grid, call.alone)) return kGeneral;
   gsl::SmallArgs a;
   memset(&a, 0, sizeof(a));
   a.off = offsets;
@@ -926,10 +943,13 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   // bounds only)
   const gsl::TierConfig cfg = f32 ? gsl::kF32Tiers : current_tiers();
   const HubLimits hub_lim = current_hub_limits();
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  const InFlight call(dev);
   if (n <= small_vertices(weights != nullptr) && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
       !o.async_sweeps && o.layout != 1 && (!batch || batch->graphs <= kSmallMaxGraphs) &&
       is_default_tiers(cfg)) {
-    rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch);
+    rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch, call);
     if (rc != kGeneral) return rc;
   }
   if (o.timing) {
@@ -1950,7 +1970,7 @@ int session_plan(gsl_session &S, const gsl::TierConfig &cfg, const HubLimits &li
 // vertices that join in four groups: 5.2 -> 2.9 ms).  A launch whose wait
 // ran out leaves the session as it was before, its flags no longer exact: the
 // next sweep takes every vertex.
-int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, bool *ran) {
+int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, const InFlight &call, bool *ran) {
   *ran = false;
   Scratch &s = S.s;
   const hipStream_t st = S.stream;
@@ -1960,7 +1980,7 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, bo
     if (x.live && x.longest > gsl::kSmallMaxDegree) return GSL_OK;
   const int grid = gsl::small_grid(N, S.weighted, true);
   SmallSlots share;
-  if (!share.take(S.device, S.weighted ? 2 * grid : grid)) return GSL_OK;
+  if (!share.take(S.device, S.weighted ? 2 * grid : grid, call.alone)) return GSL_OK;
   const int p = S.ctrl.it & 1;
   gsl::SmallArgs a;
   memset(&a, 0, sizeof(a));
@@ -2098,7 +2118,8 @@ int session_step(gsl_session &S, int32_t sweeps, int64_t capacity, int64_t *done
   bool split_done = false;
   std::vector<uint8_t> gdone((size_t)S.cap_g);
   std::vector<int32_t> giters((size_t)S.cap_g);
-  if ((rc = session_small(S, sweeps, cfg, &split_done))) return rc;
+  const InFlight call(S.device);
+  if ((rc = session_small(S, sweeps, cfg, call, &split_done))) return rc;
   if (split_done) {
     std::copy_n(S.gdone_host, S.cap_g, gdone.begin());
     std::copy_n(S.giters_host, S.cap_g, giters.begin());
