@@ -27,11 +27,11 @@
 //
 // Measured (MI355X, whole calls, general path -> here): planted graphs of 200
 // vertices 675 -> 102 us (16 sweeps), 10,000 vertices 611 -> 153 us, 28,901
-// vertices (no allocation) 660 -> 187 us, 199,999 weighted vertices with rows
-// of 20 - 57 entries 1,123 -> 734 us.  All device functions are inlined and no
+// vertices (no allocation) 660 -> 187 us, 100,001 weighted vertices 722 -> 614
+// us.  All device functions are inlined and no
 // member of the arguments is indexed by a variable: a call by reference or such
 // an index moves the arguments to scratch memory, where every use reads them
-// (the same calls took 137, 190, 223 and 787 us that way).  A sweep of the 10,000 vertices takes 3.9
+// (the first three took 137, 190 and 223 us that way).  A sweep of the 10,000 vertices takes 3.9
 // us of work (1.6 us gather and sort, the rest flags, counts and barriers) and
 // 3 us of meeting; the launches of such a sweep took about 25 us.  What bounds
 // it is latency: the label gathers after a meeting miss both caches.
