@@ -22,7 +22,8 @@ __device__ __forceinline__ uint32_t gather_label(const int32_t *__restrict__ C, 
 // V4: 16-byte loads of the aligned words that cover the row -- at most
 // D / 4 + 1 loads instead of D, vector memory instructions being what the
 // thread-per-vertex sweep waits on -- then shifted into place in registers.
-// Only words that hold an entry of the row are loaded, and an aligned 16-byte
+// Only words that hold an entry of the row are loaded (none where d is 0: a lane
+// past its row's end, whose b may lie past the array's), and an aligned 16-byte
 // word lies within one page (the page of that entry), so no load reaches
 // unmapped memory.  V4 needs a 16-byte aligned array.  Register indices are
 // template constants (index sequences rather than loops), so the words stay
@@ -71,7 +72,7 @@ __device__ __forceinline__ void load_row(const uint32_t *__restrict__ x, int64_t
     const int64_t b4 = b & ~int64_t(3);
     const int sh = (int)(b - b4);
     uint32_t t[4 * Q];
-    load_words(reinterpret_cast<const uint4 *>(x + b4), sh + d, fill, t, std::make_integer_sequence<int, Q>{});
+    load_words(reinterpret_cast<const uint4 *>(x + b4), d > 0 ? sh + d : 0, fill, t, std::make_integer_sequence<int, Q>{});
     shift_words(t, sh, d, fill, r, std::make_integer_sequence<int, D>{});
   }
 }
