@@ -19,6 +19,7 @@
 
 #include "../../include/gsl_lpa.h"
 #include "gsl_internal.h"
+#include "meeting.h"
 
 // Scratch of gsl_lpa_noalloc: one array per device, loaded with the code
 // object and held until the process ends.  Host code never uses this name as
@@ -663,7 +664,8 @@ long long small_wait_ticks() {
   }();
   return ticks;
 }
-constexpr int64_t kSmallSyncWords = gsl::kSmallGrid + 32;  // the release word on a cache line of its own
+constexpr int64_t kSmallSlotWords = (int64_t)gsl::kMeetingCopies * gsl::kSmallGrid;
+constexpr int64_t kSmallSyncWords = kSmallSlotWords + 32;  // the release word on a cache line of its own
 constexpr int64_t kSmallRecBytes = (int64_t)gsl::kSmallMaxSweeps * gsl::kSmallGrid * 8;
 constexpr int64_t kSmallTierRecBytes = (int64_t)gsl::kSmallGrid * gsl::kNumTiers * gsl::kSmallTierFields * 4;
 static_assert(kSmallRecBytes + kSmallTierRecBytes + (int64_t)gsl::kSmallGrid * 8 <=
@@ -748,7 +750,7 @@ int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, gsl::SmallResult *h
   a.heavy = reinterpret_cast<unsigned long long *>(rec + kSmallRecBytes);
   a.tier_rec = reinterpret_cast<unsigned int *>(rec + kSmallRecBytes + (int64_t)gsl::kSmallGrid * 8);
   a.slots = s.small_sync;
-  a.release = s.small_sync + gsl::kSmallGrid + 16;
+  a.release = s.small_sync + kSmallSlotWords + 16;
   a.epoch = s.small_epoch;
   a.spin_limit = small_wait_ticks();
   a.result = s.small_result;

@@ -258,7 +258,7 @@ struct SmallArgs {
   uint8_t *gdone_host;
   int32_t *giters_host;
   // meetings of the workgroups
-  unsigned long long *slots, *release;
+  unsigned long long *slots, *release;  // [kMeetingCopies][kSmallGrid]; one word
   uint32_t epoch;         // 24 bits, another for each launch on these slots
   long long spin_limit;   // ticks (100 MHz) after which a wait gives up
   unsigned long long *rec;    // [kSmallMaxSweeps][kSmallGrid] processed, edges

@@ -16,11 +16,11 @@
 //    of every vertex, changed or not, to the other array), so one meeting per
 //    sweep replaces the sweep / copy / decide launches.
 //  - A meeting is a slot per workgroup: its count of changed labels and the
-//    meeting's number in one word, a plain store without contention.  Up to
-//    kDirect workgroups read every slot and each draws the same conclusion;
-//    more of them (and batches, whose graphs stop one by one) leave that to
-//    workgroup 0, which publishes it in the release word.  The rules are
-//    those of sweep_end and graph_end.
+//    meeting's number in one word, a plain store without contention (two words
+//    in turn, meeting.h).  Up to kDirect workgroups read every slot and each
+//    draws the same conclusion; more of them (and batches, whose graphs stop
+//    one by one) leave that to workgroup 0, which publishes it in the release
+//    word.  The rules are those of sweep_end and graph_end.
 //  - Up to kSmallOne vertices run in one workgroup with labels, flags and the
 //    split's forest in LDS; its meetings are barriers.
 //  - The split needs three more meetings: link, flatten, hook, write out.
@@ -51,6 +51,7 @@
 // labels of the one before only, and the same vertices are processed.
 #include "device_common.h"
 #include "gsl_internal.h"
+#include "meeting.h"
 #include "rows.h"
 
 namespace gsl {
@@ -107,7 +108,7 @@ struct Shared {
 };
 
 __device__ __forceinline__ unsigned long long word_of(const SmallArgs &a, uint32_t meeting, uint32_t payload) {
-  return ((unsigned long long)a.epoch << 40) | ((unsigned long long)meeting << 32) | payload;
+  return meeting_word(a.epoch, meeting, payload);
 }
 
 __device__ __forceinline__ bool spun_out(const SmallArgs &a, long long t0) {
@@ -131,10 +132,11 @@ template <int BLOCK>
 __device__ __forceinline__ void small_collect(const SmallArgs &a, Shared<BLOCK> &s, uint32_t m) {
   const long long t0 = wall_clock64();
   uint32_t sum = 0, ev = 0;
+  const unsigned long long *slots = a.slots + meeting_copy(m) * kSmallGrid;
   for (unsigned int b = threadIdx.x; b < gridDim.x; b += BLOCK) {
     for (int spins = 0;; ++spins) {
-      const unsigned long long x = __hip_atomic_load(a.slots + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((x >> 32) == (word_of(a, m, 0) >> 32)) {
+      const unsigned long long x = __hip_atomic_load(slots + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (meeting_posted(x, a.epoch, m)) {
         sum += (uint32_t)x & kDnMask;
         ev |= (uint32_t)x & ~kDnMask;
         break;
@@ -177,7 +179,8 @@ __device__ __forceinline__ uint32_t small_arrive(const SmallArgs &a, Shared<BLOC
   __syncthreads();
   if (threadIdx.x == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_store(a.slots + blockIdx.x, word_of(a, m, payload), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.slots + meeting_copy(m) * kSmallGrid + blockIdx.x, word_of(a, m, payload), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   }
   if (all || blockIdx.x == 0) {
     small_collect(a, s, m);
@@ -191,7 +194,7 @@ __device__ __forceinline__ uint32_t small_arrive(const SmallArgs &a, Shared<BLOC
     uint32_t got = kAbort;
     for (;;) {
       const unsigned long long x = __hip_atomic_load(a.release, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((x >> 32) == (word_of(a, m, 0) >> 32)) {
+      if (meeting_posted(x, a.epoch, m)) {
         got = (uint32_t)x;
         break;
       }
