@@ -9,7 +9,9 @@ namespace gsl {
 // A workgroup posts meeting m in its own word and waits until every other has
 // posted m.  It may post m + 1 while another still looks for its m, so each
 // has two words, taken in turn: m + 2, which overwrites m, comes after all have
-// posted m + 1 and so have read m.
+// posted m + 1 and so have read m.  The sums that a workgroup keeps of a
+// meeting's words in LDS have two copies for the same reason: thread 0 clears
+// those of m + 1 while a slower wavefront still reads those of m.
 constexpr uint32_t kMeetingCopies = 2;
 constexpr uint32_t meeting_copy(uint32_t meeting) { return meeting % kMeetingCopies; }
 

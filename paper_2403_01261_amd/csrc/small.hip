@@ -96,7 +96,7 @@ struct Shared {
   unsigned int events;
   unsigned int tstat[kNumTiers][kSmallTierFields];
   unsigned long long red[NW], red2[NW];
-  unsigned int acc[2];       // a meeting's sums: changed vertices, events
+  unsigned int acc[kMeetingCopies][2];  // a meeting's sums (meeting_copy): changed vertices, events
   unsigned long long active;
   uint32_t word;
   // workgroup 0: changes of every sweep, whether it marked, and (one workgroup) its rows
@@ -127,7 +127,7 @@ __device__ __forceinline__ bool given_up(const SmallArgs &a) {
 }
 
 // The slots of every workgroup at meeting m, read by all threads of this one:
-// their sums are added to s.acc.
+// their sums are added to the meeting's s.acc.
 template <int BLOCK>
 __device__ __forceinline__ void small_collect(const SmallArgs &a, Shared<BLOCK> &s, uint32_t m) {
   const long long t0 = wall_clock64();
@@ -156,8 +156,9 @@ __device__ __forceinline__ void small_collect(const SmallArgs &a, Shared<BLOCK> 
     }
   }
   sum = wave_sum_u32(sum);
-  if (threadIdx.x % kWave == 0 && sum) atomicAdd(&s.acc[0], sum);
-  if (ev) atomicOr(&s.acc[1], ev);
+  unsigned int *acc = s.acc[meeting_copy(m)];
+  if (threadIdx.x % kWave == 0 && sum) atomicAdd(&acc[0], sum);
+  if (ev) atomicOr(&acc[1], ev);
 }
 
 // This workgroup's part of meeting m: what it wrote becomes visible, then its
@@ -166,16 +167,19 @@ __device__ __forceinline__ void small_collect(const SmallArgs &a, Shared<BLOCK> 
 // the payload that the others return.  Returns kAbort: leave.
 template <int BLOCK>
 __device__ __forceinline__ uint32_t small_arrive(const SmallArgs &a, Shared<BLOCK> &s, uint32_t m, uint32_t payload, bool all) {
+  // no barrier before the sums are written: their last readers were at meeting
+  // m - 2, and everyone has been through m - 1's barriers since
+  unsigned int *acc = s.acc[meeting_copy(m)];
   if constexpr (BLOCK == kOneBlock) {
     __syncthreads();
     if (threadIdx.x == 0) {
-      s.acc[0] = payload & kDnMask;
-      s.acc[1] = payload & ~kDnMask;
+      acc[0] = payload & kDnMask;
+      acc[1] = payload & ~kDnMask;
     }
     __syncthreads();
     return 0;
   }
-  if (threadIdx.x == 0) s.acc[0] = s.acc[1] = 0;
+  if (threadIdx.x == 0) acc[0] = acc[1] = 0;
   __syncthreads();
   if (threadIdx.x == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -187,7 +191,7 @@ __device__ __forceinline__ uint32_t small_arrive(const SmallArgs &a, Shared<BLOC
     __syncthreads();
     if (threadIdx.x == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     __syncthreads();
-    return s.acc[1] & kAbort;
+    return acc[1] & kAbort;
   }
   if (threadIdx.x == 0) {
     const long long t0 = wall_clock64();
@@ -636,10 +640,11 @@ __device__ __forceinline__ bool small_sampled_out(const SmallArgs &a) {
   return 5 * (unsigned long long)heavy > 3 * (unsigned long long)sum;
 }
 
-// After a sweep (every slot in): per-graph stops of a batch (workgroup 0) and
+// After a sweep (every slot in at meeting m): per-graph stops of a batch (workgroup 0) and
 // the next sweep's mode, the rules of graph_end and sweep_end.
 template <int BLOCK>
-__device__ __forceinline__ void small_decide(const SmallArgs &a, Shared<BLOCK> &s, SweepCtrl &c) {
+__device__ __forceinline__ void small_decide(const SmallArgs &a, Shared<BLOCK> &s, uint32_t m, SweepCtrl &c) {
+  const unsigned int *acc = s.acc[meeting_copy(m)];
   if (a.gdn) {
     unsigned long long active = 0;
     for (int64_t g = threadIdx.x; g < a.graphs; g += BLOCK) {
@@ -657,14 +662,14 @@ __device__ __forceinline__ void small_decide(const SmallArgs &a, Shared<BLOCK> &
     if (threadIdx.x == 0) s.active = active;
     __syncthreads();
   }
-  const long long d = (long long)s.acc[0];
+  const long long d = (long long)acc[0];
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     s.dn_of[c.it - a.ctrl.it] = (uint32_t)d;
     s.marked[c.it - a.ctrl.it] = (uint8_t)c.mark;
   }
   const int marked = c.mark;
   c.it += 1;
-  if (s.acc[1] & kOverflow) {
+  if (acc[1] & kOverflow) {
     c.error = 1;
     c.done = 1;
     return;
@@ -931,10 +936,10 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
     uint32_t leave = got & (kAbort | kDecline);
     if (kOne || all || blockIdx.x == 0) {
       if (!leave) {
-        if ((s.acc[1] & kDecline) || (it == it0 && a.init && a.layout_auto && 2 * small_heavy(a, s) > nnz))
+        if ((s.acc[meeting_copy(m)][1] & kDecline) || (it == it0 && a.init && a.layout_auto && 2 * small_heavy(a, s) > nnz))
           leave = kDecline;
         else
-          small_decide(a, s, c);
+          small_decide(a, s, m, c);
       }
       if (!kOne && !all) {
         __syncthreads();

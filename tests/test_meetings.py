@@ -97,3 +97,44 @@ def test_every_order_of_the_meetings_ends(copies, groups, kinds):
     assert ends, "the meetings end at all"
     for words, _, at in ends:
         assert all(m == len(kinds) for m, _ in at), "a workgroup waits for ever: %s, words %s" % (at, words)
+
+
+def sum_steps(meetings, copies, threads):
+    """State: the sums by copy, the threads that wait at the barrier, and per
+    thread (meeting, step, whether it has seen every sum whole).  The steps of a
+    meeting: thread 0 clears the sums, a barrier, everyone adds one, a barrier,
+    everyone reads the sum."""
+    n_copies = max(copies) + 1
+
+    def steps(state):
+        sums, waiting, at = state
+        out = []
+
+        def put(w, m, step, whole, sums=sums, waiting=waiting):
+            out.append((sums, waiting, at[:w] + ((m, step, whole),) + at[w + 1:]))
+
+        if all(waiting):
+            return [(sums, (False,) * threads, tuple((m, step + 1, whole) for m, step, whole in at))]
+        for w in range(threads):
+            m, step, whole = at[w]
+            if m == meetings or waiting[w]:
+                continue
+            c = copies[m]
+            if step == 0:
+                put(w, m, 1, whole, sums=sums[:c] + (0,) + sums[c + 1:] if w == 0 else sums)
+            elif step in (1, 3):
+                put(w, m, step, whole, waiting=waiting[:w] + (True,) + waiting[w + 1:])
+            elif step == 2:
+                put(w, m, 3, whole, sums=sums[:c] + (sums[c] + 1,) + sums[c + 1:])
+            else:
+                put(w, m + 1, 0, whole and sums[c] == threads)
+        return out
+
+    return (tuple([0] * n_copies), (False,) * threads, tuple([(0, 0, True)] * threads)), steps
+
+
+@pytest.mark.parametrize("threads", [2, 3])
+def test_every_thread_reads_a_meetings_whole_sum(copies, threads):
+    seen, ends = explore(*sum_steps(4, copies, threads))
+    assert ends and all(m == 4 for _, _, at in ends for m, _, _ in at)
+    assert all(whole for _, _, at in seen for _, _, whole in at), "a sum was cleared before its last reader"
