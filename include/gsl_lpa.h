@@ -494,6 +494,27 @@ int gsl_set_hub_limits(int64_t staging_bytes, int32_t merge_claims);
  * null stream). */
 int gsl_set_stream(void *hip_stream);
 
+/*
+ * gsl_route_counts -- how this process's calls ran since the library was
+ * loaded, over all devices and threads.  Results never depend on the route;
+ * the counts tell a program (or a test) that watches call times which one a
+ * call took.
+ */
+typedef enum gsl_route {
+  GSL_ROUTE_ONE_LAUNCH = 0, /* label-propagation calls and session steps that ran in one launch */
+  GSL_ROUTE_DECLINED = 1,   /* such launches that left the call to the general path: a long row, many
+                               entries, or a graph that the layout rule renumbers */
+  GSL_ROUTE_RAN_OUT = 2,    /* such launches given up because their workgroups waited too long for
+                               each other; the general path ran the call */
+  GSL_ROUTE_BUSY = 3,       /* small enough for one launch, not tried beside other calls */
+  GSL_ROUTE_WINDOWS = 4,    /* calls whose sweeps read near labels from windows in LDS */
+  GSL_ROUTE_ROWS64 = 5,     /* calls that gave their rows of 33 - 64 entries a thread each */
+  GSL_ROUTE_CLUSTERED = 6,  /* calls that swept a copy in cluster order (automatic layout) */
+  GSL_ROUTES = 7
+} gsl_route;
+/* The counts into counts_out[GSL_ROUTES]. */
+int gsl_route_counts(int64_t *counts_out);
+
 /* Message of the last failed call on this thread ("" if none). */
 const char *gsl_last_error(void);
 

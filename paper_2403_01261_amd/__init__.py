@@ -17,7 +17,7 @@ import torch
 __all__ = ["gsl_lpa", "gsl_lpa_ex", "gsl_lpa_f32", "gsl_lpa_batched", "gsl_lpa_graphs", "gsl_check_graph", "Context",
            "gsl_split", "gsl_split_ex", "gsl_disconnected", "gsl_set_tiers", "gsl_get_tiers",
            "gsl_tier_variants",
-           "gsl_modularity", "gsl_convergence_limit", "gsl_set_stream", "gsl_release", "gsl_version",
+           "gsl_modularity", "gsl_convergence_limit", "gsl_set_stream", "gsl_route_counts", "gsl_release", "gsl_version",
            "GslError", "LIB_PATH", "load"]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libgsl_lpa.so")
@@ -142,6 +142,7 @@ def load(path: str = None):
                                      ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int64)]
     lib.gsl_session_info.argtypes = [_VP] + [ctypes.POINTER(ctypes.c_int64)] * 6
     lib.gsl_set_stream.argtypes = [_VP]
+    lib.gsl_route_counts.argtypes = [ctypes.POINTER(ctypes.c_int64)]
     lib.gsl_last_error.restype = ctypes.c_char_p
     lib.gsl_version.restype = ctypes.c_char_p
     lib.gsl_release.restype = None
@@ -150,7 +151,7 @@ def load(path: str = None):
               lib.gsl_lpa_graphs, lib.gsl_check_graph, lib.gsl_disconnected, lib.gsl_set_tiers,
               lib.gsl_get_tiers, lib.gsl_tier_variant, lib.gsl_split_ex, lib.gsl_lpa_f32,
               lib.gsl_set_hub_limits, lib.gsl_lpa_noalloc, lib.gsl_session_create, lib.gsl_session_add,
-              lib.gsl_session_step, lib.gsl_session_info):
+              lib.gsl_session_step, lib.gsl_session_info, lib.gsl_route_counts):
         f.restype = ctypes.c_int
     _lib = lib
     return lib
@@ -592,6 +593,17 @@ def gsl_set_stream(stream) -> None:
 
 def gsl_release() -> None:
     load().gsl_release()
+
+
+_ROUTES = ("one_launch", "declined", "ran_out", "busy", "windows", "rows64", "clustered")
+
+
+def gsl_route_counts() -> dict:
+    """How this process's calls ran since the library was loaded (gsl_route in
+    include/gsl_lpa.h): a count per route.  Results never depend on it."""
+    counts = (ctypes.c_int64 * len(_ROUTES))()
+    _check(load().gsl_route_counts(counts))
+    return dict(zip(_ROUTES, counts))
 
 
 def gsl_version() -> str:

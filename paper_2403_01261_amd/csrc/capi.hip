@@ -47,6 +47,9 @@ struct HubLimits {
 };
 HubLimits g_hub_limits;
 
+std::atomic<int64_t> g_routes[GSL_ROUTES];  // gsl_route_counts
+void took(gsl_route r) { g_routes[r].fetch_add(1, std::memory_order_relaxed); }
+
 gsl::TierConfig current_tiers() {
   std::lock_guard<std::mutex> lk(g_tier_mu);
   return g_tiers;
@@ -704,6 +707,7 @@ struct SmallSlots {  // the share of one call, given back when it returns
     const int before = g_small_blocks[device].fetch_add(want);
     if (before + want > (alone && before == 0 ? gsl::kSmallGrid : kSmallShared)) {
       g_small_blocks[device].fetch_sub(want);
+      took(GSL_ROUTE_BUSY);
       return false;
     }
     dev = device;
@@ -768,6 +772,9 @@ int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, gsl::SmallResult *h
   if (!s.fixed) memcpy(head, s.small_result, kHead);
   if (head->aborted == a.epoch) head->status = gsl::kSmallAborted;
   if (head->status == gsl::kSmallPending) return fail(GSL_EDEVICE, "the small-graph kernel reported nothing");
+  if (head->status == gsl::kSmallOk) took(GSL_ROUTE_ONE_LAUNCH);
+  if (head->status == gsl::kSmallDeclined) took(GSL_ROUTE_DECLINED);
+  if (head->status == gsl::kSmallAborted) took(GSL_ROUTE_RAN_OUT);
   return GSL_OK;
 }
 
@@ -1085,6 +1092,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   a.ids = !renumber && !a.inplace ? 1 : 0;
   a.near = !a.inplace && !f32 && !renumber && wants_near(plan) ? 1 : 0;
   a.n = n;
+  if (clustered) took(GSL_ROUTE_CLUSTERED);
   // Sparse sweeps walk a frontier of the active vertices per tier, built at
   // the start of the sweep into the split's parent array (unused until the
   // split) with the counts in the counters block; fp32 weights keep the scan,
@@ -1105,8 +1113,14 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   // entries a thread each too, instead of 16 lanes and a table (1,024 planted
   // graphs 24.2 -> 22.4 ms, 117 graphs 3.85 -> 3.65 ms; weighted R-MAT scale 22
   // 8.67 -> 8.81 with it, and power-law graphs' rows are few there).
-  if (is_default_tiers(cfg) && !f32 && !weights && !renumber && plan.tier_count[2] >= kThread64Rows)
+  if (is_default_tiers(cfg) && !f32 && !weights && !renumber && plan.tier_count[2] >= kThread64Rows) {
     variant[2] = 18;
+    took(GSL_ROUTE_ROWS64);
+  }
+  bool windows = false;
+  for (int t = 1; t < gsl::kNumTiers - 1; ++t)
+    windows = windows || (!f32 && plan.tier_count[t] > 0 && gsl::sweep_has_windows(variant[t], a));
+  if (windows) took(GSL_ROUTE_WINDOWS);
 
   // Timing records (timing mode only).
   std::vector<Launch> launches;
@@ -2564,6 +2578,12 @@ int64_t gsl_convergence_limit(int64_t n, double tolerance) {
 int gsl_set_stream(void *hip_stream) {
   std::lock_guard<std::mutex> lk(g_mu);
   g_stream = reinterpret_cast<hipStream_t>(hip_stream);
+  return GSL_OK;
+}
+
+int gsl_route_counts(int64_t *counts_out) {
+  if (!counts_out) return fail(GSL_EINVAL, "counts_out must not be NULL");
+  for (int r = 0; r < GSL_ROUTES; ++r) counts_out[r] = g_routes[r].load(std::memory_order_relaxed);
   return GSL_OK;
 }
 

@@ -281,6 +281,9 @@ int64_t plan_scratch(int64_t n);
 // Sweep kernel of one tier with the given variant (kVariants index).
 hipError_t launch_sweep_tier(int variant, const SweepArgs &a, const int32_t *list, int64_t first,
                              int64_t count, int *grid_out, hipStream_t s);
+// Whether that kernel reads near labels from windows in LDS: unit weights, 16-byte
+// aligned columns and labels, and at least a window of them.
+bool sweep_has_windows(int variant, const SweepArgs &a);
 // Sums the per-block records of tier t (part + t * kMaxTierGrid * kCountFields,
 // g.g[t] blocks) into the tier and sweep counters.
 hipError_t launch_reduce_counts(const unsigned long long *part, TierGrids g,

@@ -309,15 +309,16 @@ void launch_thread_rows(const SweepArgs &a, const int32_t *list, int64_t first, 
     sweep_thread<D, false, false, V4, NEAR><<<grid, BLOCK, 0, s>>>(a, list, first, count, frontier_only);
 }
 
+constexpr int kWindowVariant = 16;  // launch_thread<32>
+
 // 16-byte row loads when the column (and weight) arrays are 16-byte aligned
-// (the library's own copies always are; a caller's array may not be); windows
-// of near labels when the label array is and holds one.
+// (the library's own copies always are; a caller's array may not be).
 template <int D>
 int launch_thread(const SweepArgs &a, const int32_t *list, int64_t first, int64_t count, hipStream_t s) {
   const bool v4 = ((uintptr_t)a.cols & 15) == 0 && ((uintptr_t)a.w & 15) == 0;
   const int grid = grid_for(count, 256, kMaxTierGrid);
   if constexpr (D == 32) {
-    if (a.near && !a.w && v4 && ((uintptr_t)a.C & 15) == 0 && a.n >= kNearLabels) {
+    if (sweep_has_windows(kWindowVariant, a)) {
       // the sweeps that walk a frontier are left to a second launch without
       // windows, whose workgroups are not held to two per compute unit; each
       // returns at once from the other's sweeps, and both write `grid` records
@@ -676,6 +677,11 @@ int launch_lds(const SweepArgs &a, const int32_t *list, int64_t first, int64_t c
 }
 
 }  // namespace
+
+bool sweep_has_windows(int variant, const SweepArgs &a) {
+  return variant == kWindowVariant && a.near && !a.w && ((uintptr_t)a.cols & 15) == 0 && ((uintptr_t)a.C & 15) == 0 &&
+         a.n >= kNearLabels;
+}
 
 hipError_t launch_sweep_tier(int variant, const SweepArgs &a, const int32_t *list, int64_t first,
                              int64_t count, int *grid_out, hipStream_t s) {

@@ -1,0 +1,188 @@
+"""Which way calls run: the small ones in one launch, those it cannot take on
+the general path, and the kernels chosen there -- so that a test that compares
+labels also knows whose labels they are.  Labels against the oracle, no
+tolerance."""
+import os
+import subprocess
+import sys
+import threading
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import graphgen  # noqa: E402
+import oracle  # noqa: E402
+from tests import test_gpu_near, test_gpu_rows64  # noqa: E402
+from tests.gpu_util import say, to_device  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def gsl():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2403_01261_amd as m
+    m.load()
+    return m
+
+
+class Took:
+    """The routes taken inside a with block (those with a count)."""
+
+    def __init__(self, gsl):
+        self.gsl = gsl
+
+    def __enter__(self):
+        self.before = self.gsl.gsl_route_counts()
+        return self
+
+    def __exit__(self, *exc):
+        after = self.gsl.gsl_route_counts()
+        self.routes = {k: after[k] - self.before[k] for k in after if after[k] != self.before[k]}
+
+
+def planted(n, wmax=0):
+    return graphgen.planted(n, max(1, n // 120), 0.12, n // 2, 3 + n % 7, wmin=1 if wmax else 0, wmax=wmax)
+
+
+# one workgroup, workgroups that read each other's words (up to 256), workgroups
+# led by the first, and the largest taken
+@pytest.mark.parametrize("n,wmax", [(200, 0), (200, 9), (10000, 0), (32768, 9), (32769, 0), (131072, 9), (262144, 0)])
+def test_small_graphs_run_in_one_launch(gsl, n, wmax):
+    g = planted(n, wmax)
+    say("routes n=%d wmax=%d" % (n, wmax))
+    ref = oracle.lpa(g).labels
+    for call in (gsl.gsl_lpa, gsl.gsl_lpa_noalloc):
+        with Took(gsl) as t:
+            lab = call(*to_device(g))
+        np.testing.assert_array_equal(lab.cpu().numpy(), ref)
+        assert t.routes == {"one_launch": 1}, call.__name__
+
+
+def test_batches_and_sessions_run_in_one_launch(gsl):
+    gs = [planted(n) for n in (300, 2000, 501)]
+    refs = [oracle.lpa(g) for g in gs]
+    dev = [to_device(g) for g in gs]
+    with Took(gsl) as t:
+        labels, _, _ = gsl.gsl_lpa_graphs(dev)
+    assert t.routes == {"one_launch": 1}
+    vb = np.cumsum([0] + [g.n for g in gs])
+    eb = np.cumsum([0] + [g.nnz for g in gs])
+    off = np.concatenate([g.offsets[:-1] + e for g, e in zip(gs, eb)] + [eb[-1:]])
+    up = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    with Took(gsl) as t:
+        cat, _, _ = gsl.gsl_lpa_batched(up(vb), up(eb), up(off), up(np.concatenate([g.cols for g in gs])))
+    assert t.routes == {"one_launch": 1}
+    cat = cat.cpu().numpy()
+    for k, r in enumerate(refs):
+        np.testing.assert_array_equal(labels[k].cpu().numpy(), r.labels)
+        np.testing.assert_array_equal(cat[vb[k]:vb[k + 1]], r.labels)
+    s = gsl.Session(int(vb[-1]), int(eb[-1]), max_graphs=4)
+    out = [x[2] for x in s.add(dev)]
+    steps = done = 0
+    with Took(gsl) as t:
+        while done < len(gs):
+            done += len(s.step(4))
+            steps += 1
+    assert t.routes == {"one_launch": steps}
+    s.close()
+    for lab, r in zip(out, refs):
+        np.testing.assert_array_equal(lab.cpu().numpy(), r.labels)
+
+
+def test_what_one_launch_cannot_take(gsl):
+    star = graphgen.from_undirected(2050, [(0, k) for k in range(1, 2050)])  # a row of 2,049
+    dense = graphgen.planted(2048, 4, 0.4, 1000, 3)  # all rows above 64: renumbered
+    for g in (star, dense):
+        off, cols, w = to_device(g)
+        with Took(gsl) as t:
+            lab = gsl.gsl_lpa(off, cols, w)
+        assert t.routes == {"declined": 1}
+        np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(g).labels)
+    with Took(gsl) as t:  # in the caller's layout the dense rows stay
+        lab, _ = gsl.gsl_lpa_ex(off, cols, w, layout="original")
+    assert t.routes == {"one_launch": 1}
+    np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(dense).labels)
+    g = planted(262145)
+    with Took(gsl) as t:
+        lab = gsl.gsl_lpa(*to_device(g))
+    assert t.routes.keys() <= {"rows64"}  # not tried
+    np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(g).labels)
+
+
+def test_kernels_of_the_general_path(gsl):
+    with Took(gsl) as t:
+        test_gpu_near.test_batch(gsl)
+    assert t.routes == {"windows": 1}
+    g = test_gpu_near.band(test_gpu_near.N, (1, 5000), 200000, False)
+    off, cols, w = to_device(g)
+    out = torch.empty(g.n + 1, dtype=torch.int32, device="cuda")
+    for labels, want in ((out[:-1], {"windows": 1}), (out[1:], {})):
+        with Took(gsl) as t:
+            gsl.gsl_lpa(off, cols, w, 2, 0.0, out=labels)
+        t.routes.pop("rows64", None)  # some of the wide rows
+        assert t.routes == want
+    with Took(gsl) as t:
+        test_gpu_rows64.test_rows(gsl, 300011, False)
+    assert t.routes == {"rows64": 2}
+    with Took(gsl) as t:
+        test_gpu_rows64.test_rows(gsl, 270000, False)
+    assert t.routes == {}
+
+
+def test_calls_in_one_launch_at_the_same_time(gsl):
+    """Four threads, a stream each, all calls small: beside each other they
+    share the device or take the general path; nobody waits for the limit."""
+    sizes = (900, 6001, 9000, 30000)
+    gs = [planted(n) for n in sizes]
+    refs = [oracle.lpa(g).labels for g in gs]
+    dev = [to_device(g) for g in gs]
+    calls, bad = 60, []
+
+    def work(k):
+        ctx = gsl.Context()
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(calls):
+                lab = ctx.lpa_graphs([dev[k]])[0][0]
+                if not np.array_equal(lab.cpu().numpy(), refs[k]):
+                    bad.append(k)
+        ctx.close()
+
+    with Took(gsl) as t:
+        ts = [threading.Thread(target=work, args=(k,)) for k in range(len(gs))]
+        [x.start() for x in ts]
+        [x.join() for x in ts]
+    assert not bad
+    say("at the same time: %s" % t.routes)
+    assert t.routes.get("one_launch", 0) + t.routes.get("busy", 0) + t.routes.get("ran_out", 0) == calls * len(gs)
+    assert t.routes.get("one_launch", 0) > 0 and "declined" not in t.routes
+
+
+def run_without_patience(code):
+    """Runs `code` (which prints a route dict last) with waits that give up at once: in a process of its own, as the
+    limit is read once."""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=110,
+                       env=dict(os.environ, GSL_SMALL_WAIT_TICKS="0"))
+    assert r.returncode == 0, r.stderr[-2000:]
+    return eval(r.stdout.strip().split("\n")[-1])
+
+
+def test_a_wait_that_runs_out_is_counted():
+    routes = run_without_patience(
+        "import numpy as np, torch, graphgen, oracle, paper_2403_01261_amd as m\n"
+        "g = graphgen.planted(30000, 300, 0.1, 30000, 3)\n"
+        "o, c = torch.from_numpy(g.offsets).cuda(), torch.from_numpy(g.cols).cuda()\n"
+        "assert np.array_equal(m.gsl_lpa(o, c).cpu().numpy(), oracle.lpa(g).labels)\n"
+        "print(m.gsl_route_counts())\n")
+    assert routes["ran_out"] == 1 and routes["one_launch"] == 0
+    routes = run_without_patience(
+        "import paper_2403_01261_amd as m\n"
+        "from tests import test_gpu_session_small as t\n"
+        "m.load()\n"
+        "t.serve(m, t.graphs(0, False), False, 3)\n"
+        "print(m.gsl_route_counts())\n")
+    assert routes["ran_out"] > 0
