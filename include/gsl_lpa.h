@@ -510,7 +510,9 @@ typedef enum gsl_route {
   GSL_ROUTE_WINDOWS = 4,    /* calls whose sweeps read near labels from windows in LDS */
   GSL_ROUTE_ROWS64 = 5,     /* calls that gave their rows of 33 - 64 entries a thread each */
   GSL_ROUTE_CLUSTERED = 6,  /* calls that swept a copy in cluster order (automatic layout) */
-  GSL_ROUTES = 7
+  GSL_ROUTE_HELD_BACK = 7,  /* small enough for one launch, not tried because a wait of the same context,
+                               session or calling path ran out shortly before */
+  GSL_ROUTES = 8
 } gsl_route;
 /* The counts into counts_out[GSL_ROUTES]. */
 int gsl_route_counts(int64_t *counts_out);

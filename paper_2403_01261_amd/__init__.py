@@ -595,7 +595,7 @@ def gsl_release() -> None:
     load().gsl_release()
 
 
-_ROUTES = ("one_launch", "declined", "ran_out", "busy", "windows", "rows64", "clustered")
+_ROUTES = ("one_launch", "declined", "ran_out", "busy", "windows", "rows64", "clustered", "held_back")
 
 
 def gsl_route_counts() -> dict:

@@ -163,6 +163,9 @@ struct Scratch {
   unsigned long long *small_sync = nullptr;
   uint32_t small_epoch = 0;
   gsl::SmallResult *small_result = nullptr;
+  // calls that still keep off the one launch after a wait that ran out, and how
+  // many will after the next such wait
+  int32_t small_hold = 0, small_hold_next = 0;
 };
 
 }  // namespace
@@ -719,6 +722,23 @@ struct SmallSlots {  // the share of one call, given back when it returns
   }
 };
 
+// A wait that ran out cost its call 5 ms, and what caused it (another process,
+// the caller's own kernels, a stream that may use some of the CUs only) mostly
+// lasts: the next calls on the same scratch take the general path, 0.6 - 1.1 ms
+// each, first 16 of them, twice as many after every further wait until a launch
+// ends well, so that waiting is at most a third of the time and soon little of it.
+constexpr int32_t kHoldFirst = 16, kHoldMost = 4096;
+bool held_back(Scratch &s) {
+  if (s.small_hold <= 0) return false;
+  --s.small_hold;
+  took(GSL_ROUTE_HELD_BACK);
+  return true;
+}
+void wait_ran_out(Scratch &s) {
+  s.small_hold = std::max(s.small_hold_next, kHoldFirst);
+  s.small_hold_next = std::min(2 * s.small_hold, kHoldMost);
+}
+
 int ensure_small(Scratch &s, hipStream_t st) {
   if (!s.fixed) {
     if (!s.small_sync && dmalloc(&s.small_sync, kSmallSyncWords) != hipSuccess) {
@@ -772,9 +792,17 @@ int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, gsl::SmallResult *h
   if (!s.fixed) memcpy(head, s.small_result, kHead);
   if (head->aborted == a.epoch) head->status = gsl::kSmallAborted;
   if (head->status == gsl::kSmallPending) return fail(GSL_EDEVICE, "the small-graph kernel reported nothing");
+  if (head->status == gsl::kSmallAborted) {
+    took(GSL_ROUTE_RAN_OUT);
+    wait_ran_out(s);
+    return GSL_OK;
+  }
+  if (head->status == gsl::kSmallDeclined) {
+    took(GSL_ROUTE_DECLINED);
+    return GSL_OK;
+  }
   if (head->status == gsl::kSmallOk) took(GSL_ROUTE_ONE_LAUNCH);
-  if (head->status == gsl::kSmallDeclined) took(GSL_ROUTE_DECLINED);
-  if (head->status == gsl::kSmallAborted) took(GSL_ROUTE_RAN_OUT);
+  s.small_hold_next = 0;
   return GSL_OK;
 }
 
@@ -811,6 +839,7 @@ int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t
                int64_t n, int32_t max_iters, double tolerance, const gsl_options &o, gsl_stats *stats,
                int32_t *labels_out, const Batch *batch, const InFlight &call) {
   const int grid = gsl::small_grid(n, weights != nullptr, batch != nullptr);
+  if (held_back(s)) return kGeneral;
   SmallSlots share;
   if (!share.take(call.dev, weights ? 2 * grid : grid, call.alone)) return kGeneral;
   gsl::SmallArgs a;
@@ -1995,6 +2024,7 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, co
   for (const SessionSlot &x : S.slot)
     if (x.live && x.longest > gsl::kSmallMaxDegree) return GSL_OK;
   const int grid = gsl::small_grid(N, S.weighted, true);
+  if (held_back(s)) return GSL_OK;
   SmallSlots share;
   if (!share.take(S.device, S.weighted ? 2 * grid : grid, call.alone)) return GSL_OK;
   const int p = S.ctrl.it & 1;

@@ -186,3 +186,26 @@ def test_a_wait_that_runs_out_is_counted():
         "t.serve(m, t.graphs(0, False), False, 3)\n"
         "print(m.gsl_route_counts())\n")
     assert routes["ran_out"] > 0
+
+
+def test_calls_keep_off_after_a_wait_that_ran_out():
+    """Not every call pays for the wait: 16 take the general path at once, 32
+    after the next wait that runs out, on each scratch by itself."""
+    routes = run_without_patience(
+        "import numpy as np, torch, graphgen, oracle, paper_2403_01261_amd as m\n"
+        "g = graphgen.planted(30000, 300, 0.1, 30000, 3)\n"
+        "ref = oracle.lpa(g).labels\n"
+        "o, c = torch.from_numpy(g.offsets).cuda(), torch.from_numpy(g.cols).cuda()\n"
+        "for k in range(1 + 16 + 1 + 32 + 1):\n"
+        "    assert np.array_equal(m.gsl_lpa(o, c).cpu().numpy(), ref), k\n"
+        "with m.Context() as ctx:\n"
+        "    assert np.array_equal(ctx.lpa_graphs([(o, c)])[0][0].cpu().numpy(), ref)\n"
+        "print(m.gsl_route_counts())\n")
+    assert routes["ran_out"] == 4 and routes["held_back"] == 48 and routes["one_launch"] == 0
+    routes = run_without_patience(
+        "import paper_2403_01261_amd as m\n"
+        "from tests import test_gpu_session_small as t\n"
+        "m.load()\n"
+        "t.serve(m, t.graphs(0, False), False, 1)\n"
+        "print(m.gsl_route_counts())\n")
+    assert 0 < routes["ran_out"] <= 3 and routes["held_back"] > 2 * routes["ran_out"]
