@@ -678,14 +678,9 @@ static_assert(kSmallRecBytes + kSmallTierRecBytes + (int64_t)gsl::kSmallGrid * 8
                   (int64_t)gsl::kNumTiers * gsl::kMaxTierGrid * gsl::kCountFields * 8,
               "the small-graph records fit the tier records' buffer");
 
-// Workgroups of small-graph launches in flight per device (a weighted one
-// counts twice, for its registers).  They wait for each other, so together
-// they must fit the device.  Beside another call of the library a launch is
-// taken up to kSmallShared of them only, half a workgroup per CU: each launch
-// deals its workgroups out over the XCDs from the first one on, so two that just
-// fit the device may not fit an XCD, and a workgroup of another call that needs
-// much LDS holds up those queued behind it.  Other calls take the general path.
-constexpr int kSmallShared = 128;
+// Workgroups of small-graph launches in flight per device (small_share of each):
+// they wait for each other, so together they must fit it (small_room).  Calls
+// beyond that take the general path.
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_small_blocks[kMaxDevices];
 std::atomic<int> g_calls[kMaxDevices];  // calls in flight, on either path
@@ -703,12 +698,29 @@ struct InFlight {  // one call, until it returns
   InFlight &operator=(const InFlight &) = delete;
 };
 
+// CUs of a device (0: not known); asked once.
+int device_cus(int dev) {
+  static std::atomic<int> cus[kMaxDevices];
+  if (dev < 0 || dev >= kMaxDevices) return 0;
+  int c = cus[dev].load(std::memory_order_relaxed);
+  if (c > 0) return c;
+  if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  cus[dev].store(c, std::memory_order_relaxed);
+  return c;
+}
+
 struct SmallSlots {  // the share of one call, given back when it returns
-  int dev = -1, blocks = 0;
-  bool take(int device, int want, bool alone) {
-    if (device < 0 || device >= kMaxDevices) return false;
+  int dev = -1, blocks = 0, grid = 0;
+  bool take(int device, int64_t n, bool weighted, bool batch, bool alone) {
+    const int cus = device_cus(device);
+    if (cus <= 0) return false;
+    grid = gsl::small_grid(n, weighted, batch, cus);
+    const int want = grid * gsl::small_share(weighted);
     const int before = g_small_blocks[device].fetch_add(want);
-    if (before + want > (alone && before == 0 ? gsl::kSmallGrid : kSmallShared)) {
+    if (grid < 1 || before + want > gsl::small_room(cus, alone && before == 0)) {
       g_small_blocks[device].fetch_sub(want);
       took(GSL_ROUTE_BUSY);
       return false;
@@ -766,7 +778,7 @@ int ensure_small(Scratch &s, hipStream_t st) {
 // set) and waits; the meeting words, records and result are filled in here.
 // head receives the result without the statistics, which stay in
 // s.small_result when they were asked for.
-int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, gsl::SmallResult *head) {
+int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, int grid, gsl::SmallResult *head) {
   int rc = ensure_small(s, st);
   if (rc) return rc;
   char *rec = reinterpret_cast<char *>(s.tier_part);
@@ -786,7 +798,7 @@ int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, gsl::SmallResult *h
     s.small_result->status = gsl::kSmallPending;
     s.small_result->aborted = 0;
   }
-  HIP_TRY(gsl::launch_small(a, st));
+  HIP_TRY(gsl::launch_small(a, grid, st));
   if (s.fixed) HIP_TRY(hipMemcpyAsync(head, s.small_result, kHead, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (!s.fixed) memcpy(head, s.small_result, kHead);
@@ -838,10 +850,9 @@ bool is_default_tiers(const gsl::TierConfig &c) {
 int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
                int64_t n, int32_t max_iters, double tolerance, const gsl_options &o, gsl_stats *stats,
                int32_t *labels_out, const Batch *batch, const InFlight &call) {
-  const int grid = gsl::small_grid(n, weights != nullptr, batch != nullptr);
   if (held_back(s)) return kGeneral;
   SmallSlots share;
-  if (!share.take(call.dev, weights ? 2 * grid : grid, call.alone)) return kGeneral;
+  if (!share.take(call.dev, n, weights != nullptr, batch != nullptr, call.alone)) return kGeneral;
   gsl::SmallArgs a;
   memset(&a, 0, sizeof(a));
   a.off = offsets;
@@ -878,7 +889,7 @@ int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t
     a.graphs = batch->graphs;
   }
   gsl::SmallResult head;
-  int rc = run_small(s, st, a, &head);
+  int rc = run_small(s, st, a, share.grid, &head);
   if (rc) return rc;
   if (head.status == gsl::kSmallDeclined || head.status == gsl::kSmallAborted) return kGeneral;
   if (head.status == gsl::kSmallBadStart)
@@ -2023,10 +2034,9 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, co
   if (N > small_vertices(S.weighted) || S.etop > kSmallMaxEntries || G > kSmallMaxGraphs || !is_default_tiers(cfg)) return GSL_OK;
   for (const SessionSlot &x : S.slot)
     if (x.live && x.longest > gsl::kSmallMaxDegree) return GSL_OK;
-  const int grid = gsl::small_grid(N, S.weighted, true);
   if (held_back(s)) return GSL_OK;
   SmallSlots share;
-  if (!share.take(S.device, S.weighted ? 2 * grid : grid, call.alone)) return GSL_OK;
+  if (!share.take(S.device, N, S.weighted, true, call.alone)) return GSL_OK;
   const int p = S.ctrl.it & 1;
   gsl::SmallArgs a;
   memset(&a, 0, sizeof(a));
@@ -2065,7 +2075,7 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, co
   a.giters_host = S.giters_host;
   HIP_TRY(gsl::launch_session_keep(S.lab[S.cur], N, S.split_in, s.giters, s.gdone, G, S.giters_keep, S.gdone_keep, st));
   gsl::SmallResult head;
-  int rc = run_small(s, st, a, &head);
+  int rc = run_small(s, st, a, share.grid, &head);
   if (rc) return rc;
   if (head.status != gsl::kSmallOk) {
     HIP_TRY(gsl::launch_session_keep(S.split_in, N, S.lab[S.cur], S.giters_keep, S.gdone_keep, G, s.giters, s.gdone, st));

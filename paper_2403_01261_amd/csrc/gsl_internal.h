@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "meeting.h"
+
 namespace gsl {
 
 // ----------------------------------------------------------------------------
@@ -198,16 +200,6 @@ struct TierGrids {
 };
 
 // ---- small graphs: the whole call in one launch (small.hip) ----
-// Most workgroups of a launch, all resident at once: two per CU, with weights
-// one.  Registers and LDS are given out in one piece, so what a CU has room for
-// is what fits however the workgroups there lie, other streams' kernels having
-// come and gone between them: beside one of 128 registers (or of 256) a second
-// of 128 always fits, a third need not, nor a second of 256.  Four and two per
-// CU, which fit an idle device exactly, left one of two concurrent launches
-// waiting for its limit (a server with two slots: p50 805 ms at 2,000 requests
-// a second).
-constexpr int kSmallGrid = 512;
-constexpr int64_t kSmallOne = 256;        // graphs up to here run in one workgroup, in LDS
 constexpr int kSmallMaxSweeps = 100;
 constexpr int kSmallMaxDegree = 2048;     // rows above: the general path
 constexpr int kSmallTierFields = 6;       // processed, edges, changed, marked; vertices, entries of the tier
@@ -266,10 +258,8 @@ struct SmallArgs {
   unsigned long long *heavy;  // [kSmallGrid]
   SmallResult *result;
 };
-// Workgroups of a launch on n vertices (at most kSmallGrid; half as many with
-// weights, whose rows need twice the registers), and the launch.
-int small_grid(int64_t n, bool weighted, bool batch);
-hipError_t launch_small(const SmallArgs &a, hipStream_t s);
+// `grid` workgroups (small_grid).
+hipError_t launch_small(const SmallArgs &a, int grid, hipStream_t s);
 
 // ---- launchers (stream-ordered, no synchronisation) ----
 hipError_t launch_plan(const int64_t *off, int64_t n, int32_t *list, int64_t *blk_counts,

@@ -72,6 +72,7 @@ constexpr int kWaveLanes = kRowWave / kRegs;
 constexpr int kTable = 4096;
 static_assert(2 * kSmallMaxDegree <= kTable, "the workgroup's table holds two slots per entry");
 static_assert(kOneBlock / kLanes == kSmallOne, "one window per graph in one workgroup");
+static_assert(kBlock / kLanes == kSmallWindow, "a window has two lanes per vertex");
 
 // Payload of a slot: changed vertices in the low bits, events above.
 constexpr uint32_t kDnMask = (1u << 28) - 1;
@@ -1051,14 +1052,8 @@ void launch_rows(const SmallArgs &a, int grid, hipStream_t s) {
 
 }  // namespace
 
-int small_grid(int64_t n, bool weighted, bool batch) {
-  if (n <= kSmallOne && !batch) return 1;
-  const int64_t g = (n + kBlock / kLanes - 1) / (kBlock / kLanes), most = weighted ? kSmallGrid / 2 : kSmallGrid;
-  return (int)(g > most ? most : g);
-}
-
-hipError_t launch_small(const SmallArgs &a, hipStream_t s) {
-  const int grid = small_grid(a.n, a.w != nullptr, a.gdn != nullptr);
+hipError_t launch_small(const SmallArgs &a, int grid, hipStream_t s) {
+  if (grid < 1 || grid > kSmallGrid) return hipErrorInvalidValue;
   if (a.n <= kSmallOne && !a.gdn)
     launch_rows<kOneBlock>(a, 1, s);
   else
