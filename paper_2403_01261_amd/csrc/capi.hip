@@ -683,13 +683,21 @@ static_assert(kSmallRecBytes + kSmallTierRecBytes + (int64_t)gsl::kSmallGrid * 8
 // beyond that take the general path.
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_small_blocks[kMaxDevices];
-std::atomic<int> g_calls[kMaxDevices];  // calls in flight, on either path
+std::atomic<int> g_calls[kMaxDevices];  // calls in flight, of every entry point that uses the device
 
-struct InFlight {  // one call, until it returns
-  int dev;
-  bool alone = false;
-  explicit InFlight(int device) : dev(device >= 0 && device < kMaxDevices ? device : -1) {
-    if (dev >= 0) alone = g_calls[dev].fetch_add(1) == 0;
+// One call of the library on the current device, from the lock of its entry
+// point (what waits there holds nothing on the device) until it returns.
+struct InFlight {
+  int dev = -1;
+  InFlight() {
+    int d = 0;
+    if (hipGetDevice(&d) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (d < 0 || d >= kMaxDevices) return;
+    dev = d;
+    g_calls[dev].fetch_add(1);
   }
   ~InFlight() {
     if (dev >= 0) g_calls[dev].fetch_sub(1);
@@ -714,13 +722,14 @@ int device_cus(int dev) {
 
 struct SmallSlots {  // the share of one call, given back when it returns
   int dev = -1, blocks = 0, grid = 0;
-  bool take(int device, int64_t n, bool weighted, bool batch, bool alone) {
+  bool take(int device, int64_t n, bool weighted, bool batch) {
     const int cus = device_cus(device);
     if (cus <= 0) return false;
     grid = gsl::small_grid(n, weighted, batch, cus);
     const int want = grid * gsl::small_share(weighted);
     const int before = g_small_blocks[device].fetch_add(want);
-    if (grid < 1 || before + want > gsl::small_room(cus, alone && before == 0)) {
+    const bool alone = before == 0 && g_calls[device].load() <= 1;  // this call is counted
+    if (grid < 1 || before + want > gsl::small_room(cus, alone)) {
       g_small_blocks[device].fetch_sub(want);
       took(GSL_ROUTE_BUSY);
       return false;
@@ -849,10 +858,10 @@ bool is_default_tiers(const gsl::TierConfig &c) {
 // path has to run it (nothing but scratch and outputs has been written then).
 int small_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
                int64_t n, int32_t max_iters, double tolerance, const gsl_options &o, gsl_stats *stats,
-               int32_t *labels_out, const Batch *batch, const InFlight &call) {
+               int32_t *labels_out, const Batch *batch, int dev) {
   if (held_back(s)) return kGeneral;
   SmallSlots share;
-  if (!share.take(call.dev, n, weights != nullptr, batch != nullptr, call.alone)) return kGeneral;
+  if (!share.take(dev, n, weights != nullptr, batch != nullptr)) return kGeneral;
   gsl::SmallArgs a;
   memset(&a, 0, sizeof(a));
   a.off = offsets;
@@ -994,11 +1003,10 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   const HubLimits hub_lim = current_hub_limits();
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
-  const InFlight call(dev);
   if (n <= small_vertices(weights != nullptr) && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
       !o.async_sweeps && o.layout != 1 && (!batch || batch->graphs <= kSmallMaxGraphs) &&
       is_default_tiers(cfg)) {
-    rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch, call);
+    rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch, dev);
     if (rc != kGeneral) return rc;
   }
   if (o.timing) {
@@ -2026,7 +2034,7 @@ int session_plan(gsl_session &S, const gsl::TierConfig &cfg, const HubLimits &li
 // vertices that join in four groups: 5.2 -> 2.9 ms).  A launch whose wait
 // ran out leaves the session as it was before, its flags no longer exact: the
 // next sweep takes every vertex.
-int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, const InFlight &call, bool *ran) {
+int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, bool *ran) {
   *ran = false;
   Scratch &s = S.s;
   const hipStream_t st = S.stream;
@@ -2036,7 +2044,7 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, co
     if (x.live && x.longest > gsl::kSmallMaxDegree) return GSL_OK;
   if (held_back(s)) return GSL_OK;
   SmallSlots share;
-  if (!share.take(S.device, N, S.weighted, true, call.alone)) return GSL_OK;
+  if (!share.take(S.device, N, S.weighted, true)) return GSL_OK;
   const int p = S.ctrl.it & 1;
   gsl::SmallArgs a;
   memset(&a, 0, sizeof(a));
@@ -2174,8 +2182,7 @@ int session_step(gsl_session &S, int32_t sweeps, int64_t capacity, int64_t *done
   bool split_done = false;
   std::vector<uint8_t> gdone((size_t)S.cap_g);
   std::vector<int32_t> giters((size_t)S.cap_g);
-  const InFlight call(S.device);
-  if ((rc = session_small(S, sweeps, cfg, call, &split_done))) return rc;
+  if ((rc = session_small(S, sweeps, cfg, &split_done))) return rc;
   if (split_done) {
     std::copy_n(S.gdone_host, S.cap_g, gdone.begin());
     std::copy_n(S.giters_host, S.cap_g, giters.begin());
@@ -2240,6 +2247,7 @@ int gsl_lpa_ex(const int64_t *offsets, const int32_t *cols, const uint32_t *weig
   int rc = check_lpa(n, max_iters, tolerance, offsets, labels_out);
   if (rc) return rc == kNoop ? GSL_OK : rc;
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   Scratch *sp = nullptr;
   if ((rc = get_scratch(&sp))) return rc;
   return lpa_impl(*sp, g_stream, offsets, cols, weights, n, max_iters, tolerance, opt, stats, labels_out);
@@ -2256,6 +2264,7 @@ int gsl_lpa_noalloc(const int64_t *offsets, const int32_t *cols, const uint32_t 
     return fail(GSL_EINVAL, "max_iters = %d exceeds the %d sweeps of gsl_lpa_noalloc", max_iters,
                 GSL_NOALLOC_MAX_ITERS);
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   NoAlloc &na = g_noalloc[dev];
@@ -2270,6 +2279,7 @@ int gsl_lpa_f32(const int64_t *offsets, const int32_t *cols, const float *weight
   int rc = check_lpa(n, max_iters, tolerance, offsets, labels_out);
   if (rc) return rc == kNoop ? GSL_OK : rc;
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   Scratch *sp = nullptr;
   if ((rc = get_scratch(&sp))) return rc;
   Scratch &s = *sp;
@@ -2304,6 +2314,7 @@ int gsl_lpa_batched_ex(int64_t num_graphs, const int64_t *vtx_base, const int64_
   int rc = check_batch(num_graphs, max_iters, tolerance);
   if (rc) return rc == kNoop ? GSL_OK : rc;
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   Scratch *sp = nullptr;
   if ((rc = get_scratch(&sp))) return rc;
   return batched_concat(*sp, g_stream, num_graphs, vtx_base, edge_base, offsets, cols, weights, max_iters,
@@ -2315,6 +2326,7 @@ int gsl_check_graph(const int64_t *offsets, const int32_t *cols, int64_t n) {
   if (n == 0) return GSL_OK;
   if (!offsets) return fail(GSL_EINVAL, "offsets must not be NULL");
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   Scratch *sp = nullptr;
   const int rc = get_scratch(&sp);
   if (rc) return rc;
@@ -2391,12 +2403,14 @@ int gsl_lpa_graphs(gsl_context *ctx, int64_t num_graphs, const gsl_graph *graphs
   }
   if (!ctx) {
     std::lock_guard<std::mutex> lk(g_mu);
+    const InFlight call;
     Scratch *sp = nullptr;
     if ((rc = get_scratch(&sp))) return rc;
     return batched_graphs(*sp, g_stream, num_graphs, graphs, max_iters, tolerance, opt, stats, iterations_out,
                           status_out);
   }
   std::lock_guard<std::mutex> lk(ctx->mu);
+  const InFlight call;
   int cur = 0;
   HIP_TRY(hipGetDevice(&cur));
   if (cur != ctx->device) return fail(GSL_EINVAL, "the context belongs to device %d, current is %d", ctx->device, cur);
@@ -2407,6 +2421,7 @@ int gsl_lpa_graphs(gsl_context *ctx, int64_t num_graphs, const gsl_graph *graphs
 int gsl_split(const int64_t *offsets, const int32_t *cols, int64_t n, const int32_t *labels_in,
               int32_t *labels_out) {
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   if (n < 0 || n >= ((int64_t)1 << 31)) return fail(GSL_EINVAL, "n out of range");
   if (n == 0) return GSL_OK;
   if (!offsets || !labels_in || !labels_out) return fail(GSL_EINVAL, "NULL argument");
@@ -2441,6 +2456,7 @@ int gsl_split_ex(const int64_t *offsets, const int32_t *cols, int64_t n, const i
   if (!offsets || !labels_in || !labels_out) return fail(GSL_EINVAL, "NULL argument");
   if (labels_in == labels_out) return fail(GSL_EINVAL, "labels_out must not alias labels_in");
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   const hipStream_t st = g_stream;
   Scratch *sp = nullptr;
   int rc = get_scratch(&sp);
@@ -2492,6 +2508,7 @@ int gsl_disconnected(const int64_t *offsets, const int32_t *cols, int64_t n, con
   if (n == 0) return GSL_OK;
   if (!offsets || !labels) return fail(GSL_EINVAL, "NULL argument");
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   const hipStream_t st = g_stream;
   Scratch *sp = nullptr;
   int rc = get_scratch(&sp);
@@ -2521,6 +2538,7 @@ int gsl_disconnected(const int64_t *offsets, const int32_t *cols, int64_t n, con
 int gsl_modularity(const int64_t *offsets, const int32_t *cols, const uint32_t *weights, int64_t n,
                    const int32_t *labels, double *q_out) {
   std::lock_guard<std::mutex> lk(g_mu);
+  const InFlight call;
   if (!q_out) return fail(GSL_EINVAL, "q_out must not be NULL");
   *q_out = 0.0;
   if (n < 0 || n >= ((int64_t)1 << 31)) return fail(GSL_EINVAL, "n out of range");
@@ -2757,6 +2775,7 @@ int gsl_session_add(gsl_session *S, int64_t num_graphs, const gsl_graph *graphs,
   if (num_graphs == 0) return GSL_OK;
   if (!graphs || !tickets_out || !status_out) return fail(GSL_EINVAL, "NULL argument");
   std::lock_guard<std::mutex> lk(S->mu);
+  const InFlight call;
   int cur = 0;
   HIP_TRY(hipGetDevice(&cur));
   if (cur != S->device) return fail(GSL_EINVAL, "the session belongs to device %d, current is %d", S->device, cur);
@@ -2776,6 +2795,7 @@ int gsl_session_step(gsl_session *S, int32_t sweeps, int64_t capacity, int64_t *
   if (sweeps < 1 || sweeps > kSessionSweepCap) return fail(GSL_EINVAL, "sweeps must be in [1, %d]", kSessionSweepCap);
   if (capacity < 0 || (capacity > 0 && !done_tickets)) return fail(GSL_EINVAL, "bad done_tickets / capacity");
   std::lock_guard<std::mutex> lk(S->mu);
+  const InFlight call;
   int cur = 0;
   HIP_TRY(hipGetDevice(&cur));
   if (cur != S->device) return fail(GSL_EINVAL, "the session belongs to device %d, current is %d", S->device, cur);

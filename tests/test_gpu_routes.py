@@ -209,3 +209,37 @@ def test_calls_keep_off_after_a_wait_that_ran_out():
         "t.serve(m, t.graphs(0, False), False, 1)\n"
         "print(m.gsl_route_counts())\n")
     assert 0 < routes["ran_out"] <= 3 and routes["held_back"] > 2 * routes["ran_out"]
+
+
+@pytest.mark.parametrize("op", ["modularity", "split", "disconnected"])
+def test_every_entry_point_counts_as_a_call_in_flight(gsl, op):
+    """A graph of more than a quarter of the device's workgroups is not taken in
+    one launch beside another call, whichever that is."""
+    big = planted(1000000)
+    off, cols, w = to_device(big)
+    raw = gsl.gsl_lpa_ex(off, cols, w, split=False)[0]
+    other = {"modularity": lambda: gsl.gsl_modularity(off, cols, w, raw), "split": lambda: gsl.gsl_split(off, cols, raw),
+             "disconnected": lambda: gsl.gsl_disconnected(off, cols, raw)}[op]
+    other()
+    g = planted(60000)
+    dev, ref = to_device(g), oracle.lpa(g).labels
+    started, stop = threading.Event(), threading.Event()
+
+    def beside():
+        while not stop.is_set():
+            other()
+            started.set()
+
+    th = threading.Thread(target=beside)
+    with gsl.Context() as ctx:
+        ctx.lpa_graphs([dev])
+        th.start()
+        started.wait()
+        with Took(gsl) as t:
+            for _ in range(60):
+                lab = ctx.lpa_graphs([dev])[0][0]
+                np.testing.assert_array_equal(lab.cpu().numpy(), ref)
+        stop.set()
+        th.join()
+    say("beside %s: %s" % (op, t.routes))
+    assert t.routes.get("busy", 0) > 0
