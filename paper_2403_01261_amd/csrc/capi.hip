@@ -976,11 +976,20 @@ bool wants_clusters(int64_t n, int64_t nnz, int32_t max_iters, const Counters &p
          8 * plan.tier_count[1] >= 7 * np && plan.spread[0] > 0 && 2 * plan.spread[1] > plan.spread[0];
 }
 
-// Windows of near labels in LDS: for graphs whose sampled entries are mostly
-// near.  The labels of 7 M vertices (256 planted graphs, 8.0 ms either way) or
-// fewer stay in the L2s well enough; 15 M 14.7 -> 13.9 ms, 30 M 28.8 -> 25.7.
-constexpr int64_t kNearMinVertices = int64_t(1) << 23;
-bool wants_near(const Counters &plan) { return plan.spread[0] > 0 && 2 * plan.spread[2] > plan.spread[0]; }
+// Most of a sample of the entries lie near their vertices.  The split's first
+// pass then takes tiles in LDS at any size that is sampled (planted graphs of
+// 2.1, 2.6, 4 and 6 M vertices 1.91 -> 1.68, 2.12 -> 1.98, 3.12 -> 2.90 and 4.46 ->
+// 4.17 ms per call).  The sweeps read labels from windows in LDS in larger graphs
+// only: fewer labels stay in the L2s well enough, and a window loads 64 KB
+// whatever it is asked.  Planted graphs without -> with windows: 2.6, 4, 5.3 and 6 M
+// vertices 1.98 -> 2.21, 2.90 -> 2.98, 3.72 -> 3.79 and 4.17 -> 4.07 ms, 8 M 5.8 ->
+// 5.2; batches, whose vertices also look up their graph, 5.6, 6.4 and 6.9 M vertices
+// 5.94 -> 6.05, 6.73 -> 6.84 and 7.12 -> 7.10, 15 and 30 M 14.7 -> 13.9 and 28.8 -> 25.7.
+constexpr int64_t kWindowMinVertices = int64_t(11) << 19, kWindowMinBatch = int64_t(1) << 23;
+bool is_near(const Counters &plan) { return plan.spread[0] > 0 && 2 * plan.spread[2] > plan.spread[0]; }
+
+// Vertices from which a single graph's entries are sampled, for the two rules above.
+constexpr int64_t kSpreadMinVertices = kClusterMinVertices;
 
 // f32: `weights` holds fp32 values (summed in fp64) instead of uint32.
 int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *cols, const uint32_t *weights,
@@ -1014,7 +1023,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
     if ((rc = ensure_events(s))) return rc;
     HIP_TRY(hipEventRecord(s.ev[0], st));
   }
-  if ((rc = run_plan(s, offsets, n, cfg, st, s.pin, batch && n >= kNearMinVertices ? cols : nullptr))) return rc;
+  if ((rc = run_plan(s, offsets, n, cfg, st, s.pin, batch && n >= kWindowMinBatch ? cols : nullptr))) return rc;
   if (s.pin[0] != 0) return fail(GSL_EINVAL, "offsets[0] must be 0 (got %lld)", (long long)s.pin[0]);
   if (s.pin[1] < 0) return fail(GSL_EINVAL, "offsets[n] must be >= 0");
   const int64_t nnz = s.pin[1];
@@ -1038,7 +1047,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   bool clustered = false;
   // A sample of the entries' spread, for graphs large enough to use it (a
   // batch's was taken with its plan).
-  if (!batch && !renumber && n >= std::min(kNearMinVertices, kClusterMinVertices) && nnz > 0) {
+  if (!batch && !renumber && n >= kSpreadMinVertices && nnz > 0) {
     HIP_TRY(gsl::launch_spread(offsets, cols, n, s.ctr->spread, st));
     HIP_TRY(hipMemcpyAsync(s.pin, s.ctr->spread, sizeof(plan.spread), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -1138,7 +1147,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   a.gdone = batch ? s.gdone : nullptr;
   a.inplace = o.async_sweeps ? 1 : 0;
   a.ids = !renumber && !a.inplace ? 1 : 0;
-  a.near = !a.inplace && !f32 && !renumber && wants_near(plan) ? 1 : 0;
+  a.near = !a.inplace && !f32 && !renumber && n >= (batch ? kWindowMinBatch : kWindowMinVertices) && is_near(plan) ? 1 : 0;
   a.n = n;
   if (clustered) took(GSL_ROUTE_CLUSTERED);
   // Sparse sweeps walk a frontier of the active vertices per tier, built at
@@ -1375,7 +1384,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   } else if (o.split) {
     HIP_TRY(gsl::launch_split(offsets, cols, n, C, s.parent, labels_out, s.list, plan.tier_count,
                               plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st,
-                              batch != nullptr || wants_near(plan)));
+                              batch != nullptr || is_near(plan)));
   }
   if (batch && (rc = finish_batch(s, st, batch, n, labels_out))) return rc;
   if (timed) HIP_TRY(hipEventRecord(s.ev[3], st));

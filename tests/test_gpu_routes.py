@@ -243,3 +243,20 @@ def test_every_entry_point_counts_as_a_call_in_flight(gsl, op):
         th.join()
     say("beside %s: %s" % (op, t.routes))
     assert t.routes.get("busy", 0) > 0
+
+
+@pytest.mark.parametrize("n,batch,windows", [(2500000, False, False), (5700000, False, False), (5800000, False, True),
+                                             (5800000, True, False)])
+def test_windows_are_for_large_graphs(gsl, n, batch, windows):
+    """Single graphs below 11 * 2^19 vertices and batches below 2^23 sweep without windows."""
+    g = test_gpu_near.band(n, (1, 2), 200, False)
+    off, cols, w = to_device(g)
+    say("windows n=%d batch=%s" % (n, batch))
+    with Took(gsl) as t:
+        if batch:
+            ends = torch.tensor([[0, n], [0, g.nnz]], dtype=torch.int64, device="cuda")
+            lab = gsl.gsl_lpa_batched(ends[0].contiguous(), ends[1].contiguous(), off, cols, None, 3, 0.0)[0]
+        else:
+            lab = gsl.gsl_lpa(off, cols, w, 3, 0.0)
+    assert t.routes == ({"windows": 1} if windows else {})
+    np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(g, 3, 0.0).labels)
