@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstddef>
 #include <cstdarg>
@@ -783,6 +784,24 @@ int ensure_small(Scratch &s, hipStream_t st) {
   return GSL_OK;
 }
 
+// Whether a launch says within kDeclineWait that it leaves the call to the
+// general path.  That takes it some 10 us; the general path's first kernels then
+// follow the launch at once instead of after a round trip (R-MAT of 2^16 and 2^18
+// vertices 1,031 -> 1,020 and 1,487 -> 1,471 us a call).  Other calls take longer
+// than the wait.
+constexpr int64_t kDeclineWait = 30;  // us
+bool declined_soon(const gsl::SmallResult *r, uint32_t epoch) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int k = 1;; ++k) {
+    if (__atomic_load_n(&r->declined, __ATOMIC_ACQUIRE) == epoch) return true;
+    if (k % 16 == 0) {
+      if (__atomic_load_n(&r->status, __ATOMIC_RELAXED) != gsl::kSmallPending) return false;
+      if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kDeclineWait)) return false;
+    }
+    __builtin_ia32_pause();
+  }
+}
+
 // Launches `a` (its graph, labels, flags, split arrays, batch and loop state
 // set) and waits; the meeting words, records and result are filled in here.
 // head receives the result without the statistics, which stay in
@@ -806,8 +825,14 @@ int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, int grid, gsl::Smal
   if (!s.fixed) {
     s.small_result->status = gsl::kSmallPending;
     s.small_result->aborted = 0;
+    s.small_result->declined = 0;
   }
   HIP_TRY(gsl::launch_small(a, grid, st));
+  if (!s.fixed && a.init && declined_soon(s.small_result, a.epoch)) {
+    head->status = gsl::kSmallDeclined;
+    took(GSL_ROUTE_DECLINED);
+    return GSL_OK;
+  }
   if (s.fixed) HIP_TRY(hipMemcpyAsync(head, s.small_result, kHead, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (!s.fixed) memcpy(head, s.small_result, kHead);

@@ -215,6 +215,7 @@ enum : int32_t {
 struct SmallResult {
   int32_t status;
   uint32_t aborted;   // the launch's epoch when a workgroup's wait ran out
+  uint32_t declined;  // the launch's epoch as soon as it leaves the call before its first sweep
   int64_t first_offset, nnz;
   SweepCtrl ctrl;   // the loop state after the last sweep
   // statistics (SmallArgs::stats): tier[0][0] is the largest degree

@@ -605,40 +605,51 @@ __device__ __forceinline__ int64_t small_heavy(const SmallArgs &a, Shared<BLOCK>
 
 // Whether a fixed sample of the rows already says that the call is for the
 // general path: a row above kSmallMaxDegree, or most entries in rows that the
-// layout rule counts (small_heavy decides the close ones, a sweep later).
-// Every wavefront of the grid reads the same rows and answers alike, without a
-// meeting or a barrier.  Such a sweep takes 60 us (2^16 vertices of an R-MAT
-// graph) to 120 us (2^18), which the general path then repeats; the sample
-// takes 6 us (whole calls of 2^12, 2^16 and 2^18 vertices: 766 -> 734, 1,092 ->
-// 1,023 and 1,586 -> 1,477 us; accepted calls within 1 us).  Near a half
-// the share is not clear from 512 rows, and a call turned away wrongly loses
-// more (400 us and up) than one let through: the line is three fifths.  The
-// rows are spread by a multiplicative hash: no period of the ids meets it.
-constexpr int kSampleRows = 8;  // rows per lane
+// layout rule counts.  A sweep takes 60 us (2^16 vertices of an R-MAT graph) to
+// 120 us (2^18), which the general path would repeat.  Every wavefront of the
+// grid reads the same rows and answers alike, without a meeting or a barrier.
+// 512 rows say enough where none of them counts (or, where the layout does not
+// matter, none is above a quarter of kSmallMaxDegree) or nearly all entries lie
+// in those that do; else up to kSampleRounds times as many are read, 1 us each
+// time.  The share of a sample near a half says little, and a call turned away
+// wrongly loses 400 us and up: the line is nine sixteenths, and small_heavy
+// decides between, a sweep later.  (R-MAT of 2^16 vertices, 400,000 weighted
+// edges, some 56 % of the entries in such rows, in turn on three graphs: 1,884 us
+// a call when the first sweep found out, 1,800 here and on the general path
+// alone.)  The rows are spread by a multiplicative hash: no period of the ids
+// meets it.
+constexpr int kSampleRows = 8;  // rows per lane and round
+constexpr int kSampleRounds = 8;
 
 template <int BLOCK>
 __device__ __forceinline__ bool small_sampled_out(const SmallArgs &a) {
-  int64_t d[kSampleRows];
-#pragma unroll
-  for (int k = 0; k < kSampleRows; ++k) {
-    const uint32_t h = (uint32_t)(threadIdx.x % kWave + k * kWave + 1) * 2654435761u;
-    const int64_t v = (int64_t)(((uint64_t)h * (uint64_t)a.n) >> 32);  // < n
-    d[k] = a.off[v + 1] - a.off[v];
-  }
   uint32_t sum = 0, heavy = 0;
-  bool over = false;
+#pragma unroll 1
+  for (int round = 0; round < kSampleRounds; ++round) {
+    int64_t d[kSampleRows];
 #pragma unroll
-  for (int k = 0; k < kSampleRows; ++k) {
-    over = over || d[k] > kSmallMaxDegree;
-    const uint32_t c = d[k] > 0 && d[k] <= kSmallMaxDegree ? (uint32_t)d[k] : 0u;
-    sum += c;
-    heavy += c > 64 ? c : 0u;
+    for (int k = 0; k < kSampleRows; ++k) {
+      const uint32_t h = (uint32_t)(threadIdx.x % kWave + (round * kSampleRows + k) * kWave + 1) * 2654435761u;
+      const int64_t v = (int64_t)(((uint64_t)h * (uint64_t)a.n) >> 32);  // < n
+      d[k] = a.off[v + 1] - a.off[v];
+    }
+    uint32_t rs = 0, rh = 0;
+    bool over = false;
+    const uint32_t line = a.layout_auto ? 64 : kSmallMaxDegree / 4;
+#pragma unroll
+    for (int k = 0; k < kSampleRows; ++k) {
+      over = over || d[k] > kSmallMaxDegree;
+      const uint32_t c = d[k] > 0 && d[k] <= kSmallMaxDegree ? (uint32_t)d[k] : 0u;
+      rs += c;
+      rh += c > line ? c : 0u;
+    }
+    if (__ballot(over)) return true;
+    sum += wave_sum_u32(rs);
+    heavy += wave_sum_u32(rh);
+    if (!heavy) return false;
+    if (a.layout_auto && 4 * heavy > 3 * sum) return true;
   }
-  if (__ballot(over)) return true;
-  if (!a.layout_auto) return false;
-  sum = wave_sum_u32(sum);
-  heavy = wave_sum_u32(heavy);
-  return 5 * (unsigned long long)heavy > 3 * (unsigned long long)sum;
+  return a.layout_auto && 16 * heavy > 9 * sum;
 }
 
 // After a sweep (every slot in at meeting m): per-graph stops of a batch (workgroup 0) and
@@ -865,7 +876,11 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
     return;
   }
   if (a.init && a.ctrl.max_iters > 0 && small_sampled_out<BLOCK>(a)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.result->status = kSmallDeclined;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      // the host looks for this word while the launch runs
+      __hip_atomic_store(&a.result->declined, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      a.result->status = kSmallDeclined;
+    }
     return;
   }
   const int64_t base0 = (int64_t)blockIdx.x * V, step = (int64_t)gridDim.x * V;

@@ -260,3 +260,54 @@ def test_windows_are_for_large_graphs(gsl, n, batch, windows):
             lab = gsl.gsl_lpa(off, cols, w, 3, 0.0)
     assert t.routes == ({"windows": 1} if windows else {})
     np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(g, 3, 0.0).labels)
+
+
+def hubs(count, leaves, extra=0, fill=0):
+    """`count` vertices with `leaves` neighbours of their own each -- half of all entries in rows of more than 64 --
+    and `extra` edges among them (more than half then) or `fill` among the leaves (less)."""
+    n = count * (leaves + 1)
+    hub = np.arange(count) * (leaves + 1)
+    edges = [(h, h + 1 + k) for h in hub for k in range(leaves)]
+    edges += [(hub[k], hub[k + 1]) for k in range(extra)] + [(2 * k + 1, 2 * k + 2) for k in range(fill) if (2 * k + 2) % (leaves + 1)]
+    perm = np.random.default_rng(n).permutation(n)
+    return graphgen.from_undirected(n, [(int(perm[u]), int(perm[v])) for u, v in edges])
+
+
+# one workgroup, workgroups that read each other's words, workgroups led by the first
+@pytest.mark.parametrize("count,leaves", [(3, 70), (60, 90), (700, 80)])
+def test_the_line_of_the_layout_rule_is_exact(gsl, count, leaves):
+    """A call is turned away where rows of more than 64 entries hold more than half of all, on any sample."""
+    for extra, fill, want in ((0, 0, "one_launch"), (1, 0, "declined"), (0, 1, "one_launch")):
+        g = hubs(count, leaves, extra, fill)
+        deg = np.diff(g.offsets)
+        say("line n=%d heavy %d of %d" % (g.n, deg[deg > 64].sum(), g.nnz))
+        off, cols, w = to_device(g)
+        with Took(gsl) as t:
+            lab, st = gsl.gsl_lpa_ex(off, cols, w)
+        assert t.routes == {want: 1}
+        r = oracle.lpa(g)
+        np.testing.assert_array_equal(lab.cpu().numpy(), r.labels)
+        assert st["iterations"] == r.iterations and st["renumbered"] == (want == "declined")
+
+
+def test_long_rows_are_seen_before_the_first_sweep_or_after_it(gsl):
+    """One row of 2,049 beside many of 300 (counted first), one beside short rows only (found by its window), and none
+    above 2,048; weights, a batch, and the call that never allocates."""
+    rng = np.random.default_rng(5)
+    for n, heavy, longest, want in ((30000, 60, 2049, "declined"), (30000, 60, 2048, "one_launch"), (30000, 0, 2049, "declined"),
+                                    (70000, 60, 2049, "declined")):
+        u = np.concatenate([np.full(300, k + 1) for k in range(heavy)] + [np.zeros(longest, dtype=np.int64), np.arange(n // 2, n - 1)])
+        v = np.concatenate([rng.choice(np.arange(n // 2, n), 300, replace=False) for _ in range(heavy)] +
+                           [rng.choice(np.arange(n // 2, n), longest, replace=False), np.arange(n // 2 + 1, n)])
+        g = graphgen.from_undirected(n, list(zip(u.tolist(), v.tolist())), rng.integers(1, 9, size=u.size) if heavy else None)
+        assert np.diff(g.offsets).max() == longest
+        say("long row n=%d heavy=%d longest=%d" % (n, heavy, longest))
+        off, cols, w = to_device(g)
+        ref = oracle.lpa(g).labels
+        for call in (lambda: gsl.gsl_lpa_ex(off, cols, w, layout="original")[0], lambda: gsl.gsl_lpa_noalloc(off, cols, w),
+                     lambda: gsl.gsl_lpa_graphs([(off, cols, w)])[0][0]):
+            for _ in range(2):
+                with Took(gsl) as t:
+                    lab = call()
+                assert t.routes == {want: 1}
+                np.testing.assert_array_equal(lab.cpu().numpy(), ref)
