@@ -1104,8 +1104,9 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
       HIP_TRY(hipEventRecord(s.ev_reorder, st));
     }
     if (clustered)
-      HIP_TRY(gsl::launch_cluster_order(offsets, cols, n, plan.tier_count, plan.tier_start, cfg.bound[1], s.parent,
-                                        s.rep, s.lab2, s.minorig, s.blk_counts, s.list, s.crows, s.old2new, st));
+      HIP_TRY(gsl::launch_cluster_order(offsets, cols, n, plan.tier_count, plan.tier_start, cfg.bound[1],
+                                        (int64_t)plan.max_degree, s.parent, s.rep, s.lab2, s.minorig, s.blk_counts,
+                                        s.list, s.crows, s.old2new, st));
     HIP_TRY(gsl::launch_reorder(offsets, cols, weights, n, s.list, plan.tier_count, plan.tier_start,
                                 s.hub_chunk_start, s.hub_chunk_owner, H > 0 ? s.h_chunk[(size_t)H] : 0, s.old2new, s.off2,
                                 s.cols2, weights ? s.w2 : nullptr, s.lab2, s.blk_counts, s.first_key,

@@ -456,9 +456,10 @@ constexpr int64_t kSpreadFar = int64_t(1) << 19;
 constexpr int64_t kSpreadNear = 4096;
 hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, uint64_t *out, hipStream_t s);
 // The rows of tier 1 (up to `longest` entries) in cluster order, which
-// launch_reorder then lists, and the inverse of the whole list.  A cluster is a vertex that is the smallest
-// neighbour of its members or of theirs, so members are within four edges of
-// each other and a row's neighbours mostly share its cluster.  A wavefront of
+// launch_reorder then lists, and the inverse of the whole list.  max_degree is
+// the graph's longest row.  A cluster is a vertex that is the smallest neighbour
+// of its members or of theirs, so members are within four edges of each other
+// and a row's neighbours mostly share its cluster.  A wavefront of
 // 64 rows of a shuffled road graph then gathers its labels from 0.23 128-byte
 // lines per entry instead of 1.0 (24 M vertices: 1,210 -> 340 us per sweep, the
 // sort of 8 registers instead of 32 included), 2.2 GB a sweep at 6.5 TB/s: what
@@ -467,9 +468,9 @@ hipError_t launch_spread(const int64_t *off, const int32_t *cols, int64_t n, uin
 // scattered output 0.6 ms.  first, cluster, rank and count are scratch of n
 // entries each, scan_tmp of plan_blocks(n).
 hipError_t launch_cluster_order(const int64_t *off, const int32_t *cols, int64_t n, const int64_t *tier_count_h,
-                                const int64_t *tier_start_h, int64_t longest, int32_t *first, int32_t *cluster,
-                                int32_t *rank, int32_t *count, int64_t *scan_tmp, const int32_t *list, ClusterRow *rows,
-                                int32_t *old2new, hipStream_t s);
+                                const int64_t *tier_start_h, int64_t longest, int64_t max_degree, int32_t *first,
+                                int32_t *cluster, int32_t *rank, int32_t *count, int64_t *scan_tmp,
+                                const int32_t *list, ClusterRow *rows, int32_t *old2new, hipStream_t s);
 hipError_t launch_reorder_scatter(const int32_t *list, const int32_t *val, int64_t np, int64_t n,
                                   int32_t *out, hipStream_t s);
 hipError_t launch_check_labels(const int32_t *labels, int64_t n, unsigned long long *bad,
