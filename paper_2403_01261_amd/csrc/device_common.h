@@ -36,34 +36,6 @@ __device__ __forceinline__ int table_log2(int64_t d, int lo, int hi) {
   return l < lo ? lo : (l > hi ? hi : l);
 }
 
-// Adds weight w to label `label` in an LDS open-addressing table of 2^log2s
-// slots (linear probing).  The table must have a free slot for every distinct
-// label inserted.  A slot's label never changes once claimed, so a stale read
-// can only cost a failed compare-and-swap.
-__device__ __forceinline__ void lds_table_add(unsigned long long *tab, int log2s, uint32_t label,
-                                              uint32_t w) {
-  const uint32_t mask = (1u << log2s) - 1u;
-  uint32_t h = slot_hash(label, log2s);
-  const unsigned long long mine = ((unsigned long long)label << 32) | w;
-  for (;;) {
-    const unsigned long long cur = __hip_atomic_load(&tab[h], __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-    if ((uint32_t)(cur >> 32) == label) {
-      atomicAdd(&tab[h], (unsigned long long)w);
-      return;
-    }
-    if (cur == kEmptySlot) {
-      const unsigned long long prev = atomicCAS(&tab[h], kEmptySlot, mine);
-      if (prev == kEmptySlot) return;
-      if ((uint32_t)(prev >> 32) == label) {
-        atomicAdd(&tab[h], (unsigned long long)w);
-        return;
-      }
-    }
-    h = (h + 1u) & mask;
-  }
-}
-
 // Adds (label, w) to an LDS table with a compare-and-swap first: returns the
 // slot index if this call claimed a new slot for `label`, -1 if the label was
 // already present (its weight was added).  The table must keep a free slot
@@ -79,36 +51,6 @@ __device__ __forceinline__ int lds_insert(unsigned long long *tab, int log2s, ui
     if ((uint32_t)(prev >> 32) == label) {
       atomicAdd(&tab[h], (unsigned long long)w);
       return -1;
-    }
-    h = (h + 1u) & mask;
-  }
-}
-
-// Same on a global-memory table private to one workgroup: workgroup-scope
-// atomics (performed in the L2 of the workgroup's XCD).
-__device__ __forceinline__ void global_table_add(unsigned long long *tab, int log2s, uint32_t label,
-                                                 uint32_t w) {
-  const uint32_t mask = (1u << log2s) - 1u;
-  uint32_t h = slot_hash(label, log2s);
-  const unsigned long long mine = ((unsigned long long)label << 32) | w;
-  for (;;) {
-    unsigned long long cur = __hip_atomic_load(&tab[h], __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-    if ((uint32_t)(cur >> 32) == label) {
-      __hip_atomic_fetch_add(&tab[h], (unsigned long long)w, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-      return;
-    }
-    if (cur == kEmptySlot) {
-      unsigned long long expected = kEmptySlot;
-      if (__hip_atomic_compare_exchange_strong(&tab[h], &expected, mine, __ATOMIC_RELAXED,
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
-        return;
-      if ((uint32_t)(expected >> 32) == label) {
-        __hip_atomic_fetch_add(&tab[h], (unsigned long long)w, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-        return;
-      }
     }
     h = (h + 1u) & mask;
   }
