@@ -428,7 +428,13 @@ def roofline_from_stats(stats, weighted, steps, wname, n):
     import paper_2403_01261_amd as gsl
     variants = gsl.gsl_tier_variants()
     levels = gsl.gsl_get_tiers()
-    kernel = "hub_insert" if dom == NUM_TIERS - 1 else gsl.variant_kernel_name(variants[levels[dom - 1][1]], weighted, n)
+    # the variant that the call took, which may be another than the table's
+    took, windows = gsl.gsl_last_variants()
+    if dom == NUM_TIERS - 1:
+        kernel = "hub_insert"
+    else:
+        v = took[dom - 1] if took[dom - 1] >= 0 else levels[dom - 1][1]
+        kernel = gsl.variant_kernel_name(variants[v], weighted, n, windows=windows and v == 16)
     lps = launches // max(steps, 1)
     return {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(wname, kernel, levels, lps),

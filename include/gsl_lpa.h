@@ -517,6 +517,13 @@ typedef enum gsl_route {
 /* The counts into counts_out[GSL_ROUTES]. */
 int gsl_route_counts(int64_t *counts_out);
 
+/* Sweep variant of every level in this thread's last label-propagation call
+ * (variants_out[GSL_TIER_LEVELS]; -1 for all of them if it ran in one launch,
+ * failed early or had float weights): with the default tiers a call may take
+ * another than the table's for its rows.  *windows_out is 1 if its dense sweeps of
+ * the level with variant 16 read near labels from windows.  Either may be NULL. */
+int gsl_last_variants(int32_t *variants_out, int32_t *windows_out);
+
 /* Message of the last failed call on this thread ("" if none). */
 const char *gsl_last_error(void);
 

@@ -17,7 +17,7 @@ import torch
 __all__ = ["gsl_lpa", "gsl_lpa_ex", "gsl_lpa_f32", "gsl_lpa_batched", "gsl_lpa_graphs", "gsl_check_graph", "Context",
            "gsl_split", "gsl_split_ex", "gsl_disconnected", "gsl_set_tiers", "gsl_get_tiers",
            "gsl_tier_variants",
-           "gsl_modularity", "gsl_convergence_limit", "gsl_set_stream", "gsl_route_counts", "gsl_release", "gsl_version",
+           "gsl_modularity", "gsl_convergence_limit", "gsl_set_stream", "gsl_route_counts", "gsl_last_variants", "gsl_release", "gsl_version",
            "GslError", "LIB_PATH", "load"]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libgsl_lpa.so")
@@ -143,6 +143,7 @@ def load(path: str = None):
     lib.gsl_session_info.argtypes = [_VP] + [ctypes.POINTER(ctypes.c_int64)] * 6
     lib.gsl_set_stream.argtypes = [_VP]
     lib.gsl_route_counts.argtypes = [ctypes.POINTER(ctypes.c_int64)]
+    lib.gsl_last_variants.argtypes = [ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
     lib.gsl_last_error.restype = ctypes.c_char_p
     lib.gsl_version.restype = ctypes.c_char_p
     lib.gsl_release.restype = None
@@ -151,7 +152,8 @@ def load(path: str = None):
               lib.gsl_lpa_graphs, lib.gsl_check_graph, lib.gsl_disconnected, lib.gsl_set_tiers,
               lib.gsl_get_tiers, lib.gsl_tier_variant, lib.gsl_split_ex, lib.gsl_lpa_f32,
               lib.gsl_set_hub_limits, lib.gsl_lpa_noalloc, lib.gsl_session_create, lib.gsl_session_add,
-              lib.gsl_session_step, lib.gsl_session_info, lib.gsl_route_counts):
+              lib.gsl_session_step, lib.gsl_session_info, lib.gsl_route_counts,
+              lib.gsl_last_variants):
         f.restype = ctypes.c_int
     _lib = lib
     return lib
@@ -563,16 +565,25 @@ def gsl_tier_variants():
                     "per_lane": info.per_lane, "capacity": info.capacity})
 
 
-def variant_kernel_name(v: dict, weighted: bool = False, n: int = 0, aligned: bool = True) -> str:
+def gsl_last_variants():
+    """(sweep variant of every level, whether windows were used) of this
+    thread's last label-propagation call; the variants are -1 if it ran in one
+    launch or had float weights."""
+    v, w = (ctypes.c_int32 * TIER_LEVELS)(), ctypes.c_int32()
+    _check(load().gsl_last_variants(v, ctypes.byref(w)))
+    return list(v), bool(w.value)
+
+
+def variant_kernel_name(v: dict, weighted: bool = False, n: int = 0, aligned: bool = True, windows: bool = False) -> str:
     """The sweep kernel's name as profilers print it (template arguments;
     the thread variants have weighted and unit-weight kernels, each with
     32-bit gather offsets for fewer than 2^30 vertices or 64-bit ones, and
     16-byte row loads when the column and weight arrays are 16-byte aligned,
-    as the library's own copies always are; graphs whose rows name near
-    vertices only run the kernel whose last argument is true)."""
+    as the library's own copies always are, and windows of near labels in
+    those sweeps that do not walk a frontier)."""
     if v["group"] == 1:
         t = lambda x: "true" if x else "false"  # noqa: E731
-        return "sweep_thread<%d, %s, %s, %s, false>" % (v["per_lane"], t(weighted), t(n < (1 << 30)), t(aligned))
+        return "sweep_thread<%d, %s, %s, %s, %s>" % (v["per_lane"], t(weighted), t(n < (1 << 30)), t(aligned), t(windows))
     return "sweep_lds<%d, %d, %d, %d>" % (v["group"], v["table_log2"], v["block"], v["per_lane"])
 
 

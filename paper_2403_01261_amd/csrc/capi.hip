@@ -51,6 +51,14 @@ HubLimits g_hub_limits;
 std::atomic<int64_t> g_routes[GSL_ROUTES];  // gsl_route_counts
 void took(gsl_route r) { g_routes[r].fetch_add(1, std::memory_order_relaxed); }
 
+// gsl_last_variants
+struct LastVariants {
+  int32_t v[GSL_TIER_LEVELS];
+  int32_t windows = 0;
+  LastVariants() { std::fill_n(v, GSL_TIER_LEVELS, -1); }
+};
+thread_local LastVariants t_last;
+
 gsl::TierConfig current_tiers() {
   std::lock_guard<std::mutex> lk(g_tier_mu);
   return g_tiers;
@@ -1023,6 +1031,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   gsl_options o = {1, 1, 0, 0, 0};
   if (opt) o = *opt;
   if (stats) memset(stats, 0, sizeof(*stats));
+  t_last = LastVariants();
   if (n < 0 || n >= ((int64_t)1 << 31)) return fail(GSL_EINVAL, "n = %lld out of range", (long long)n);
   if (max_iters < 0) return fail(GSL_EINVAL, "max_iters must be >= 0");
   if (bad_tolerance(tolerance)) return fail(GSL_EINVAL, "tolerance must be in [0, 1]");
@@ -1204,6 +1213,11 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   for (int t = 1; t < gsl::kNumTiers - 1; ++t)
     windows = windows || (!f32 && plan.tier_count[t] > 0 && gsl::sweep_has_windows(variant[t], a));
   if (windows) took(GSL_ROUTE_WINDOWS);
+  static_assert(GSL_TIER_LEVELS == gsl::kNumTiers - 2, "a level per tier but the isolated vertices and the hubs");
+  if (!f32) {
+    std::copy_n(variant + 1, GSL_TIER_LEVELS, t_last.v);
+    t_last.windows = windows ? 1 : 0;
+  }
 
   // Timing records (timing mode only).
   std::vector<Launch> launches;
@@ -2677,6 +2691,12 @@ int gsl_set_stream(void *hip_stream) {
 int gsl_route_counts(int64_t *counts_out) {
   if (!counts_out) return fail(GSL_EINVAL, "counts_out must not be NULL");
   for (int r = 0; r < GSL_ROUTES; ++r) counts_out[r] = g_routes[r].load(std::memory_order_relaxed);
+  return GSL_OK;
+}
+
+int gsl_last_variants(int32_t *variants_out, int32_t *windows_out) {
+  if (variants_out) std::copy_n(t_last.v, GSL_TIER_LEVELS, variants_out);
+  if (windows_out) *windows_out = t_last.windows;
   return GSL_OK;
 }
 

@@ -311,3 +311,28 @@ def test_long_rows_are_seen_before_the_first_sweep_or_after_it(gsl):
                     lab = call()
                 assert t.routes == {want: 1}
                 np.testing.assert_array_equal(lab.cpu().numpy(), ref)
+
+
+def test_the_last_calls_variants(gsl):
+    """The sweep variants that a call took where they are not the table's."""
+    table = [v for _, v in gsl.gsl_get_tiers()]
+    n = 300000
+    v = np.arange(n, dtype=np.int64)
+
+    def ring(reach):
+        rows = np.concatenate([v] * (2 * reach))
+        cols = np.concatenate([(v + h) % n for h in range(1, reach + 1)] + [(v - h) % n for h in range(1, reach + 1)])
+        return to_device(graphgen.from_entries(n, rows, cols))
+
+    for reach, want in ((3, {0: 0}), (8, {0: 15}), (16, {}), (20, {1: 18})):
+        gsl.gsl_lpa(*ring(reach), max_iters=2)
+        took, windows = gsl.gsl_last_variants()
+        assert not windows and took == [want.get(k, x) for k, x in enumerate(table)], reach
+    g = to_device(planted(3000))
+    gsl.gsl_lpa(*g)
+    assert gsl.gsl_last_variants() == ([-1] * 7, False)  # one launch
+    test_gpu_near.test_batch(gsl)
+    took, windows = gsl.gsl_last_variants()
+    assert windows and took[0] == 16
+    gsl.gsl_lpa_f32(g[0], g[1], torch.ones(g[1].numel(), device="cuda"))
+    assert gsl.gsl_last_variants() == ([-1] * 7, False)
