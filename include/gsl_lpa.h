@@ -502,8 +502,8 @@ int gsl_set_stream(void *hip_stream);
  */
 typedef enum gsl_route {
   GSL_ROUTE_ONE_LAUNCH = 0, /* label-propagation calls and session steps that ran in one launch */
-  GSL_ROUTE_DECLINED = 1,   /* such launches that left the call to the general path: a long row, many
-                               entries, or a graph that the layout rule renumbers */
+  GSL_ROUTE_DECLINED = 1,   /* small enough for one launch, left to the general path after a look at the
+                               rows: long ones, many entries, or a graph that the layout rule renumbers */
   GSL_ROUTE_RAN_OUT = 2,    /* such launches given up because their workgroups waited too long for
                                each other; the general path ran the call */
   GSL_ROUTE_BUSY = 3,       /* small enough for one launch, not tried beside other calls */

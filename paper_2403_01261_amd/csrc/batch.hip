@@ -78,10 +78,11 @@ __global__ __launch_bounds__(kBlock) void globalize_cols(const int32_t *__restri
 constexpr unsigned kParts = 32;
 
 // Separate graphs: cnt[g] = offsets[n] - offsets[0], negative when the offsets
-// decrease somewhere, and cnt[G + g] the longest row.
+// decrease somewhere, cnt[G + g] the longest row, and cnt[2 G + g], cnt[3 G + g]
+// and cnt[4 G + g] the rows of 65 - 128, 129 - 512 and more entries.
 __global__ void graph_entries_init(int64_t *cnt, int64_t G) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g < 2 * G) cnt[g] = g < G ? 0x7fffffffffffffffll : 0;
+  if (g < 5 * G) cnt[g] = g < G ? 0x7fffffffffffffffll : 0;
 }
 
 __global__ __launch_bounds__(kBlock) void graph_entries(const GraphDesc *__restrict__ d, int64_t G, int64_t *cnt) {
@@ -91,10 +92,20 @@ __global__ __launch_bounds__(kBlock) void graph_entries(const GraphDesc *__restr
     if (blockIdx.y > 0 && (int64_t)blockIdx.y * kBlock >= x.n) continue;  // uniform
     int bad = 0;
     unsigned long long longest = 0;
+    uint32_t rows[3] = {0, 0, 0};
     for (int64_t i = (int64_t)blockIdx.y * kBlock + threadIdx.x; i < x.n; i += (int64_t)gridDim.y * kBlock) {
       const int64_t r = x.offsets[i + 1] - x.offsets[i];
       bad |= r < 0 ? 1 : 0;
       longest = r > 0 && (unsigned long long)r > longest ? (unsigned long long)r : longest;
+      rows[0] += r > 64 && r <= 128 ? 1 : 0;
+      rows[1] += r > 128 && r <= 512 ? 1 : 0;
+      rows[2] += r > 512 ? 1 : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t q = wave_sum_u32(rows[k]);
+      if (threadIdx.x % kWave == 0 && q)
+        atomicAdd(reinterpret_cast<unsigned long long *>(&cnt[(2 + k) * G + g]), (unsigned long long)q);
     }
     bad = __syncthreads_or(bad);
     longest = group_max<kWave>(longest);
@@ -384,7 +395,7 @@ hipError_t launch_check_bases(const int64_t *vtx_base, const int64_t *edge_base,
 
 hipError_t launch_graph_entries(const GraphDesc *d, int64_t G, int64_t *cnt, hipStream_t s) {
   if (G <= 0) return hipSuccess;
-  graph_entries_init<<<(unsigned)((2 * G + 255) / 256), 256, 0, s>>>(cnt, G);
+  graph_entries_init<<<(unsigned)((5 * G + 255) / 256), 256, 0, s>>>(cnt, G);
   graph_entries<<<graph_grid(G), kBlock, 0, s>>>(d, G, cnt);
   return hipGetLastError();
 }

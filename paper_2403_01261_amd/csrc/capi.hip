@@ -191,11 +191,30 @@ struct gsl_context {
 
 namespace {
 // One graph of a session (host side).
+// The rows of a graph that matter to the one launch (launch_graph_entries).
+struct LongRows {
+  int64_t n = 0, longest = 0;
+  int64_t kind[3] = {0, 0, 0};  // rows of 65 - 128, 129 - 512 and more entries
+  LongRows() = default;
+  LongRows(const std::vector<int64_t> &cnt, int64_t G, int64_t g, int64_t vertices)
+      : n(vertices), longest(cnt[(size_t)(G + g)]), kind{cnt[(size_t)(2 * G + g)], cnt[(size_t)(3 * G + g)], cnt[(size_t)(4 * G + g)]} {}
+  void add(const LongRows &x) {
+    n += x.n;
+    longest = std::max(longest, x.longest);
+    for (int k = 0; k < 3; ++k) kind[k] += x.kind[k];
+  }
+  uint32_t cost(bool weighted) const {  // of a window (smaller graphs share one)
+    uint32_t e[3];
+    for (int k = 0; k < 3; ++k) e[k] = (uint32_t)(kind[k] * 64 * gsl::kSmallWindow / std::max(n, gsl::kSmallWindow));
+    return gsl::small_rows_cost(weighted, e[0], e[1], e[2], gsl::kSmallPerPass);
+  }
+};
+
 struct SessionSlot {
   bool live = false;
   int64_t ticket = -1;
   int64_t vb = 0, n = 0, eb = 0, nnz = 0, limit = 0;
-  int64_t longest = 0;  // its longest row
+  LongRows rows;
   int32_t *labels_out = nullptr;
 };
 constexpr int kSessionSweepCap = 64;  // most sweeps one gsl_session_step runs
@@ -652,6 +671,7 @@ struct Batch {
   const gsl::GraphDesc *scatter;   // separate graphs: descriptors of the outputs, else NULL
   const uint32_t *flags;           // separate graphs: per-graph bad-entry flags (device)
   uint32_t *flags_host;            // copy of those flags (host) or NULL
+  bool general = false;            // its rows are known not to suit the one launch
 };
 
 // One timing record: an event pair around a launch of tier `tier` in sweep
@@ -662,9 +682,10 @@ struct Launch {
 };
 
 // ---- small graphs: the whole call in one launch (small.hip) ----
-// Vertices up to which a call runs as one launch.  With weights a CU holds one
-// workgroup only: 199,999 vertices of degree 32 take 990 us that way and 915 us
-// on the general path (unit weights are faster here throughout).
+// Vertices up to which a call runs as one launch.  With weights a CU is sure to
+// hold one workgroup only: 199,999 vertices of degree 32 take 990 us that way and
+// 886 us on the general path, 131,072 vertices 667 and 855 (unit weights are
+// faster here throughout: 262,144 vertices 543 us instead of 843).
 constexpr int64_t kSmallMaxVertices = int64_t(1) << 18, kSmallMaxWeighted = int64_t(1) << 17;
 constexpr int64_t small_vertices(bool weighted) { return weighted ? kSmallMaxWeighted : kSmallMaxVertices; }
 constexpr int64_t kSmallMaxEntries = int64_t(1) << 24;
@@ -683,7 +704,7 @@ constexpr int64_t kSmallSlotWords = (int64_t)gsl::kMeetingCopies * gsl::kSmallGr
 constexpr int64_t kSmallSyncWords = kSmallSlotWords + 32;  // the release word on a cache line of its own
 constexpr int64_t kSmallRecBytes = (int64_t)gsl::kSmallMaxSweeps * gsl::kSmallGrid * 8;
 constexpr int64_t kSmallTierRecBytes = (int64_t)gsl::kSmallGrid * gsl::kNumTiers * gsl::kSmallTierFields * 4;
-static_assert(kSmallRecBytes + kSmallTierRecBytes + (int64_t)gsl::kSmallGrid * 8 <=
+static_assert(kSmallRecBytes + kSmallTierRecBytes <=
                   (int64_t)gsl::kNumTiers * gsl::kMaxTierGrid * gsl::kCountFields * 8,
               "the small-graph records fit the tier records' buffer");
 
@@ -728,6 +749,22 @@ int device_cus(int dev) {
   cus[dev].store(c, std::memory_order_relaxed);
   return c;
 }
+
+// Whether the long rows of n vertices in all, graph by graph, suit one launch:
+// the tests that the kernel makes on a sample and on each window.
+struct RowsForOneLaunch {
+  bool weighted, ok;
+  int windows = 1;
+  LongRows all;
+  RowsForOneLaunch(int64_t n, bool w, int cus) : weighted(w), ok(cus > 0) {
+    if (ok) windows = gsl::small_windows(n, gsl::small_grid(n, w, true, cus));
+  }
+  void add(const LongRows &x) {
+    ok = ok && x.longest <= gsl::kSmallMaxDegree && x.cost(weighted) <= 2 * gsl::small_rows_line(windows);
+    all.add(x);
+  }
+  bool suit() const { return ok && (uint32_t)windows * all.cost(weighted) <= gsl::small_rows_line(windows); }
+};
 
 struct SmallSlots {  // the share of one call, given back when it returns
   int dev = -1, blocks = 0, grid = 0;
@@ -819,8 +856,7 @@ int run_small(Scratch &s, hipStream_t st, gsl::SmallArgs &a, int grid, gsl::Smal
   if (rc) return rc;
   char *rec = reinterpret_cast<char *>(s.tier_part);
   a.rec = reinterpret_cast<unsigned long long *>(rec);
-  a.heavy = reinterpret_cast<unsigned long long *>(rec + kSmallRecBytes);
-  a.tier_rec = reinterpret_cast<unsigned int *>(rec + kSmallRecBytes + (int64_t)gsl::kSmallGrid * 8);
+  a.tier_rec = reinterpret_cast<unsigned int *>(rec + kSmallRecBytes);
   a.slots = s.small_sync;
   a.release = s.small_sync + kSmallSlotWords + 16;
   a.epoch = s.small_epoch;
@@ -1047,7 +1083,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   if (n <= small_vertices(weights != nullptr) && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
-      !o.async_sweeps && o.layout != 1 && (!batch || batch->graphs <= kSmallMaxGraphs) &&
+      !o.async_sweeps && o.layout != 1 && (!batch || (batch->graphs <= kSmallMaxGraphs && !batch->general)) &&
       is_default_tiers(cfg)) {
     rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch, dev);
     if (rc != kGeneral) return rc;
@@ -1661,7 +1697,7 @@ int ensure_batch(Scratch &s, int64_t N, int64_t G) {
     if (dmalloc(&s.giters, G) != hipSuccess || dmalloc(&s.glimit, G) != hipSuccess ||
         dmalloc(&s.gdn, G) != hipSuccess || dmalloc(&s.gdone, G) != hipSuccess ||
         dmalloc(&s.gvb, G + 1) != hipSuccess || dmalloc(&s.geb, G + 1) != hipSuccess ||
-        dmalloc(&s.gcnt, 2 * G) != hipSuccess || dmalloc(&s.gdesc, G) != hipSuccess ||
+        dmalloc(&s.gcnt, gsl::kGraphCounts * G) != hipSuccess || dmalloc(&s.gdesc, G) != hipSuccess ||
         dmalloc(&s.gflag, G) != hipSuccess) {
       (void)hipGetLastError();
       return fail(GSL_ENOMEM, "batch allocation (%lld graphs) failed", (long long)G);
@@ -1730,8 +1766,8 @@ int batched_graphs(Scratch &s, hipStream_t st, int64_t G, const gsl_graph *graph
   if (rc) return rc;
   HIP_TRY(hipMemcpyAsync(s.gdesc, graphs, (size_t)G * sizeof(gsl_graph), hipMemcpyHostToDevice, st));
   HIP_TRY(gsl::launch_graph_entries(s.gdesc, G, s.gcnt, st));
-  std::vector<int64_t> cnt((size_t)G);
-  HIP_TRY(hipMemcpyAsync(cnt.data(), s.gcnt, (size_t)G * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+  std::vector<int64_t> cnt((size_t)(gsl::kGraphCounts * G));
+  HIP_TRY(hipMemcpyAsync(cnt.data(), s.gcnt, cnt.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   // Graphs with decreasing offsets are left out (no vertices in the batch).
   std::vector<int64_t> vb((size_t)G + 1, 0), eb((size_t)G + 1, 0);
@@ -1766,7 +1802,17 @@ int batched_graphs(Scratch &s, hipStream_t st, int64_t G, const gsl_graph *graph
     gsl_options o = {1, 1, 0, 0, 0};
     if (opt) o = *opt;
     o.layout = 2;
-    const Batch b{G, s.gvb, nullptr, iters_out, s.gdesc, s.gflag, flags.data()};
+    Batch b{G, s.gvb, nullptr, iters_out, s.gdesc, s.gflag, flags.data()};
+    if (N <= small_vertices(weighted)) {
+      // the long rows are known here: no launch has to find them
+      int dev = 0;
+      HIP_TRY(hipGetDevice(&dev));
+      RowsForOneLaunch rows(N, weighted, device_cus(dev));
+      for (int64_t g = 0; g < G; ++g)
+        if (const int64_t n = vb[(size_t)g + 1] - vb[(size_t)g]; n > 0) rows.add(LongRows(cnt, G, g, n));
+      b.general = !rows.suit();
+      if (b.general) took(GSL_ROUTE_DECLINED);
+    }
     rc = lpa_impl(s, st, s.goff, s.gcols, weighted ? s.gw : nullptr, N, max_iters, tolerance, &o, stats, s.glab,
                   &b);
     if (rc) return rc;
@@ -1835,7 +1881,7 @@ int64_t graphs_bytes(int64_t n, int64_t nnz, int64_t graphs, bool weighted, int3
   int64_t b = n * (4 + 4 + 4 + 4 + 8) + 3 * flag + gsl::plan_scratch(n) * 8;   // Cn list parent rep sigma, flags, plan
   b += 2 * 4096 * 8 + (int64_t)gsl::kNumTiers * gsl::kMaxTierGrid * gsl::kCountFields * 8;
   b += (int64_t)sizeof(Counters) + 4 * 8 * (int64_t)(max_iters > 0 ? max_iters : 1) + (int64_t)sizeof(gsl::SweepCtrl);
-  b += n * 4 + G * (4 + 8 + 8 + 1 + 8 + 8 + 16 + (int64_t)sizeof(gsl::GraphDesc) + 4) + 8;  // batch arrays
+  b += n * 4 + G * (4 + 8 + 8 + 1 + 8 + 8 + 8 * gsl::kGraphCounts + (int64_t)sizeof(gsl::GraphDesc) + 4) + 8;  // batch arrays
   b += (n + 1) * 8 + nnz * 4 * (weighted ? 2 : 1) + n * 4;                          // gathered CSR, labels
   b += kSmallSyncWords * 8;
   return b + hub_bytes_bound(nnz);
@@ -1855,7 +1901,7 @@ int64_t session_bytes(int64_t cap_v, int64_t cap_e, int64_t cap_g, bool weighted
   b += cap_v * (4 + 4 + 4 + 4 + 8) + 3 * flag + gsl::plan_scratch(cap_v) * 8;      // Cn list parent rep sigma, flags, plan
   b += 2 * 4096 * 8 + (int64_t)gsl::kNumTiers * gsl::kMaxTierGrid * gsl::kCountFields * 8;  // partials, tier records
   b += (int64_t)sizeof(Counters) + 4 * 8 * (kSessionSweepCap + 2) + (int64_t)sizeof(gsl::SweepCtrl);
-  b += cap_v * 4 + G * (4 + 8 + 8 + 1 + 8 + 8 + 16 + (int64_t)sizeof(gsl::GraphDesc) + 4) + 8;  // batch arrays
+  b += cap_v * 4 + G * (4 + 8 + 8 + 1 + 8 + 8 + 8 * gsl::kGraphCounts + (int64_t)sizeof(gsl::GraphDesc) + 4) + 8;  // batch arrays
   b += kSmallSyncWords * 8;
   return b + hub_bytes_bound(cap_e);
 }
@@ -1967,8 +2013,8 @@ int session_add(gsl_session &S, int64_t G, const gsl_graph *graphs, int64_t *tic
   }
   HIP_TRY(hipMemcpyAsync(s.gdesc, desc.data(), (size_t)G * sizeof(gsl_graph), hipMemcpyHostToDevice, st));
   HIP_TRY(gsl::launch_graph_entries(s.gdesc, G, s.gcnt, st));
-  std::vector<int64_t> cnt(2 * (size_t)G);
-  HIP_TRY(hipMemcpyAsync(cnt.data(), s.gcnt, 2 * (size_t)G * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+  std::vector<int64_t> cnt((size_t)(gsl::kGraphCounts * G));
+  HIP_TRY(hipMemcpyAsync(cnt.data(), s.gcnt, cnt.size() * sizeof(int64_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));  // also keeps desc alive until the copy is done
   // admit in order while the arena has room (compacting once if that makes room)
   std::vector<int64_t> take;
@@ -2043,7 +2089,8 @@ int session_add(gsl_session &S, int64_t G, const gsl_graph *graphs, int64_t *tic
     const int32_t k = S.free_slot.back();
     S.free_slot.pop_back();
     SessionSlot &sl = S.slot[(size_t)k];
-    sl = SessionSlot{true, S.next_ticket++, x.vb, n, x.eb, c, x.limit, cnt[(size_t)(G + g)], graphs[g].labels_out};
+    sl = SessionSlot{true, S.next_ticket++, x.vb, n, x.eb, c, x.limit, LongRows(cnt, G, g, n),
+                     graphs[g].labels_out};
     tickets[g] = sl.ticket;
     gsl::SessionRange y = x;
     y.slot = k;
@@ -2089,8 +2136,13 @@ int session_small(gsl_session &S, int32_t sweeps, const gsl::TierConfig &cfg, bo
   const hipStream_t st = S.stream;
   const int64_t N = S.vtop, G = (int64_t)S.cap_g + 1;
   if (N > small_vertices(S.weighted) || S.etop > kSmallMaxEntries || G > kSmallMaxGraphs || !is_default_tiers(cfg)) return GSL_OK;
+  RowsForOneLaunch rows(N, S.weighted, device_cus(S.device));
   for (const SessionSlot &x : S.slot)
-    if (x.live && x.longest > gsl::kSmallMaxDegree) return GSL_OK;
+    if (x.live) rows.add(x.rows);
+  if (!rows.suit()) {
+    took(GSL_ROUTE_DECLINED);
+    return GSL_OK;
+  }
   if (held_back(s)) return GSL_OK;
   SmallSlots share;
   if (!share.take(S.device, N, S.weighted, true)) return GSL_OK;

@@ -236,7 +236,7 @@ struct SmallArgs {
   SweepCtrl ctrl;         // loop state before the first sweep
   int32_t init;           // the call starts here: labels are the vertex ids, flags and parents are set up
   int32_t split, stats;
-  int32_t layout_auto;    // decline graphs that the layout rule renumbers
+  int32_t layout_auto;    // decline graphs that the layout rule would clearly renumber
   TierBounds tiers;       // for the statistics
   // batches (gdn NULL for a single graph)
   const int32_t *gid;
@@ -256,7 +256,6 @@ struct SmallArgs {
   long long spin_limit;   // ticks (100 MHz) after which a wait gives up
   unsigned long long *rec;    // [kSmallMaxSweeps][kSmallGrid] processed, edges
   unsigned int *tier_rec;     // [kSmallGrid][kNumTiers][kSmallTierFields]
-  unsigned long long *heavy;  // [kSmallGrid]
   SmallResult *result;
 };
 // `grid` workgroups (small_grid).
@@ -370,7 +369,9 @@ hipError_t launch_check_bases(const int64_t *vtx_base, const int64_t *edge_base,
 hipError_t launch_globalize_cols(const int32_t *cols, const int64_t *edge_base, const int64_t *vtx_base,
                                  int64_t G, int64_t nnz, int32_t *out, hipStream_t s);
 // cnt[g] = offsets[n] - offsets[0] of graph g, negative if its offsets decrease;
-// cnt[G + g] = its longest row (2 G entries in all).
+// cnt[G + g] = its longest row, cnt[2 G + g], cnt[3 G + g] and cnt[4 G + g] = its rows
+// of 65 - 128, 129 - 512 and more entries (kGraphCounts * G entries in all).
+constexpr int64_t kGraphCounts = 5;
 hipError_t launch_graph_entries(const GraphDesc *d, int64_t G, int64_t *cnt, hipStream_t s);
 // Separate graphs -> one global CSR (off [N + 1], cols [nnz], w [nnz] or NULL),
 // vertex ids shifted by vshift and entry positions by eshift (the position

@@ -26,15 +26,15 @@
 //  - The split needs three more meetings: link, flatten, hook, write out.
 //
 // Measured (MI355X, whole calls, general path -> here): planted graphs of 200
-// vertices 675 -> 102 us (16 sweeps), 10,000 vertices 611 -> 153 us, 28,901
-// vertices (no allocation) 660 -> 187 us, 100,001 weighted vertices 722 -> 614
-// us.  All device functions are inlined and no
-// member of the arguments is indexed by a variable: a call by reference or such
-// an index moves the arguments to scratch memory, where every use reads them
-// (the first three took 137, 190 and 223 us that way).  A sweep of the 10,000 vertices takes 3.9
-// us of work (1.6 us gather and sort, the rest flags, counts and barriers) and
-// 3 us of meeting; the launches of such a sweep took about 25 us.  What bounds
-// it is latency: the label gathers after a meeting miss both caches.
+// vertices 559 -> 87 us (16 sweeps), 10,000 vertices 613 -> 145 us, 28,901
+// vertices (no allocation) 647 -> 187 us, 131,072 weighted vertices 855 -> 667
+// us.  All device functions are inlined and no member of the arguments is
+// indexed by a variable: a call by reference or such an index moves the
+// arguments to scratch memory, where every use reads them (some 35 us a call).  A
+// sweep of the 10,000 vertices takes 3.9 us of work (1.6 us gather and sort, the
+// rest flags, counts and barriers) and 3 us of meeting; the launches of such a
+// sweep took about 25 us.  What bounds it is latency: the label gathers after a
+// meeting miss both caches.
 //
 // The workgroups wait for each other, so all of them must be resident at
 // once: the host launches at most kSmallGrid and keeps the sum over concurrent
@@ -73,6 +73,7 @@ constexpr int kTable = 4096;
 static_assert(2 * kSmallMaxDegree <= kTable, "the workgroup's table holds two slots per entry");
 static_assert(kOneBlock / kLanes == kSmallOne, "one window per graph in one workgroup");
 static_assert(kBlock / kLanes == kSmallWindow, "a window has two lanes per vertex");
+static_assert(kBlock / kWaveLanes == kSmallPerPass, "half a wavefront per row of up to kRowWave entries");
 
 // Payload of a slot: changed vertices in the low bits, events above.
 constexpr uint32_t kDnMask = (1u << 28) - 1;
@@ -546,6 +547,14 @@ __device__ __forceinline__ void small_window(const SmallArgs &a, Shared<BLOCK> &
   if (in && !take && lead) set_label(s, m, r.v, own);  // every label is written
   __syncthreads();
   const int n0 = s.qn[0], n1 = s.qn[1], n2 = s.qn[2];
+  // long rows that the sample missed because they lie together: twice the line in
+  // this window alone, as rows spread evenly vary around their mean
+  if (first && a.init && n1 + n2 &&
+      small_rows_cost(W, 0, 64u * (uint32_t)n1, 64u * (uint32_t)n2, BLOCK / kWaveLanes) >
+          2 * small_rows_line(BLOCK == kOneBlock ? 1 : small_windows(a.n, (int)gridDim.x))) {
+    if (threadIdx.x == 0) atomicOr(&s.events, kDecline);
+    return;
+  }
   if (n0 + n1 + n2) {
     for (int i0 = 0; i0 < n0; i0 += BLOCK / kGroup) {
       const int i = i0 + (int)threadIdx.x / kGroup;
@@ -589,67 +598,67 @@ __device__ __forceinline__ void small_window(const SmallArgs &a, Shared<BLOCK> &
   }
 }
 
-// Entries in rows of degree above 64 (workgroup 0, after the first meeting):
-// where they are most of the graph, the general path renumbers it.
-template <int BLOCK>
-__device__ __forceinline__ int64_t small_heavy(const SmallArgs &a, Shared<BLOCK> &s) {
-  unsigned long long h = 0;
-  for (unsigned int b = threadIdx.x; b < gridDim.x; b += BLOCK) h += a.heavy[b];
-  h = block_sum(h, s.red);
-  if (threadIdx.x == 0) s.red2[0] = h;
-  __syncthreads();
-  h = s.red2[0];
-  __syncthreads();
-  return (int64_t)h;
-}
-
 // Whether a fixed sample of the rows already says that the call is for the
-// general path: a row above kSmallMaxDegree, or most entries in rows that the
-// layout rule counts.  A sweep takes 60 us (2^16 vertices of an R-MAT graph) to
-// 120 us (2^18), which the general path would repeat.  Every wavefront of the
-// grid reads the same rows and answers alike, without a meeting or a barrier.
-// 512 rows say enough where none of them counts (or, where the layout does not
-// matter, none is above a quarter of kSmallMaxDegree) or nearly all entries lie
-// in those that do; else up to kSampleRounds times as many are read, 1 us each
-// time.  The share of a sample near a half says little, and a call turned away
-// wrongly loses 400 us and up: the line is nine sixteenths, and small_heavy
-// decides between, a sweep later.  (R-MAT of 2^16 vertices, 400,000 weighted
-// edges, some 56 % of the entries in such rows, in turn on three graphs: 1,884 us
-// a call when the first sweep found out, 1,800 here and on the general path
-// alone.)  The rows are spread by a multiplicative hash: no period of the ids
-// meets it.
+// general path: a row above kSmallMaxDegree, rows that cost more than the launches
+// saved (small_rows_cost), or most entries in rows that the layout rule counts.  A
+// sweep takes 60 us (2^16 vertices of an R-MAT graph) to 120 us (2^18), which
+// the general path would repeat.  Every wavefront of the grid reads the same rows
+// and answers alike, without a meeting or a barrier.
+// 512 rows say enough where none has more than 64 entries or there are very many
+// of them; else up to kSampleRounds times as many are read, 1 us each time, until
+// the answer is clear.  Where the share is near a half either way will do, and a
+// call turned away loses 400 us and up: the line is nine sixteenths (an R-MAT graph
+// of 4,096 vertices, half of its entries in such rows, runs in 166 us here and 632
+// on the general path; it was 651 when the exact share, known after the first
+// sweep, turned it away).  (R-MAT of 2^16 vertices, 400,000 weighted edges, in turn
+// on three graphs: 1,884 us a call when the first sweep found out, 1,800 here and
+// on the general path alone.)  The rows are spread by a multiplicative hash: no
+// period of the ids meets it.
 constexpr int kSampleRows = 8;  // rows per lane and round
 constexpr int kSampleRounds = 8;
 
-template <int BLOCK>
+template <int BLOCK, bool W>
 __device__ __forceinline__ bool small_sampled_out(const SmallArgs &a) {
-  uint32_t sum = 0, heavy = 0;
+  const int windows = BLOCK == kOneBlock ? 1 : small_windows(a.n, (int)gridDim.x);
+  const uint32_t line = small_rows_line(windows);
+  const uint32_t V = BLOCK == kOneBlock ? (uint32_t)a.n : (uint32_t)kSmallWindow;
+  uint32_t sum = 0, heavy = 0, cost = 0, c1 = 0, c2 = 0, c3 = 0;
 #pragma unroll 1
-  for (int round = 0; round < kSampleRounds; ++round) {
+  for (uint32_t round = 1; round <= kSampleRounds; ++round) {
     int64_t d[kSampleRows];
 #pragma unroll
     for (int k = 0; k < kSampleRows; ++k) {
-      const uint32_t h = (uint32_t)(threadIdx.x % kWave + (round * kSampleRows + k) * kWave + 1) * 2654435761u;
+      const uint32_t h = (uint32_t)(threadIdx.x % kWave + ((round - 1) * kSampleRows + k) * kWave + 1) * 2654435761u;
       const int64_t v = (int64_t)(((uint64_t)h * (uint64_t)a.n) >> 32);  // < n
       d[k] = a.off[v + 1] - a.off[v];
     }
-    uint32_t rs = 0, rh = 0;
+    uint32_t rs = 0, rh = 0, rc = 0;  // entries, those of rows above 64; the three kinds of those rows, 10 bits each
     bool over = false;
-    const uint32_t line = a.layout_auto ? 64 : kSmallMaxDegree / 4;
 #pragma unroll
     for (int k = 0; k < kSampleRows; ++k) {
       over = over || d[k] > kSmallMaxDegree;
       const uint32_t c = d[k] > 0 && d[k] <= kSmallMaxDegree ? (uint32_t)d[k] : 0u;
       rs += c;
-      rh += c > line ? c : 0u;
+      rh += c > 64 ? c : 0u;
+      rc += c > kRowWave ? 1u << 20 : c > 128 ? 1u << 10 : c > 64 ? 1u : 0u;
     }
     if (__ballot(over)) return true;
     sum += wave_sum_u32(rs);
     heavy += wave_sum_u32(rh);
     if (!heavy) return false;
-    if (a.layout_auto && 4 * heavy > 3 * sum) return true;
+    rc = wave_sum_u32(rc);
+    c1 += rc & 1023u;
+    c2 += rc >> 10 & 1023u;
+    c3 += rc >> 20;
+    // of a window of V rows, in 64ths
+    const uint32_t rows = 64u * kSampleRows * round;
+    cost = (uint32_t)windows * small_rows_cost(W, 64u * V * c1 / rows, 64u * V * c2 / rows, 64u * V * c3 / rows, BLOCK / kWaveLanes);
+    // the more rows, the closer to the lines an answer may lie
+    if (cost * round > line * (round + 1) || (a.layout_auto && (round < 4 ? 4 * heavy > 3 * sum : 8 * heavy > 5 * sum))) return true;
+    if (cost * (round + 1) < line * round && (!a.layout_auto || (round < 4 ? 4 * heavy < sum : 8 * heavy < 3 * sum))) return false;
+    if (rows >= 4 * (uint32_t)a.n) break;
   }
-  return a.layout_auto && 16 * heavy > 9 * sum;
+  return cost > line || (a.layout_auto && 16 * heavy > 9 * sum);
 }
 
 // After a sweep (every slot in at meeting m): per-graph stops of a batch (workgroup 0) and
@@ -875,7 +884,7 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
     }
     return;
   }
-  if (a.init && a.ctrl.max_iters > 0 && small_sampled_out<BLOCK>(a)) {
+  if (a.init && a.ctrl.max_iters > 0 && small_sampled_out<BLOCK, W>(a)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       // the host looks for this word while the launch runs
       __hip_atomic_store(&a.result->declined, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -937,13 +946,6 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
         a.rec[(size_t)(it - it0) * kSmallGrid + blockIdx.x] = ((unsigned long long)processed << 32) | edges;
       }
     }
-    if (it == it0 && a.init && a.layout_auto && threadIdx.x == kWave) {
-      unsigned long long heavy = 0;
-#pragma unroll
-      for (int t = 1; t < kNumTiers; ++t)
-        if (a.tiers.b[t - 1] >= 64) heavy += s.tstat[t][5];
-      a.heavy[blockIdx.x] = heavy;
-    }
     // the classes of kLanes and kGroup lanes are the tier table's first two tiers
     if (threadIdx.x < 8) s.tstat[1 + threadIdx.x / 4][threadIdx.x % 4] += s.cnt[threadIdx.x / 4][threadIdx.x % 4];
     __syncthreads();
@@ -952,7 +954,7 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
     uint32_t leave = got & (kAbort | kDecline);
     if (kOne || all || blockIdx.x == 0) {
       if (!leave) {
-        if ((s.acc[meeting_copy(m)][1] & kDecline) || (it == it0 && a.init && a.layout_auto && 2 * small_heavy(a, s) > nnz))
+        if (s.acc[meeting_copy(m)][1] & kDecline)
           leave = kDecline;
         else
           small_decide(a, s, m, c);

@@ -103,10 +103,13 @@ def test_what_one_launch_cannot_take(gsl):
             lab = gsl.gsl_lpa(off, cols, w)
         assert t.routes == {"declined": 1}
         np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(g).labels)
-    with Took(gsl) as t:  # in the caller's layout the dense rows stay
-        lab, _ = gsl.gsl_lpa_ex(off, cols, w, layout="original")
-    assert t.routes == {"one_launch": 1}
-    np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(dense).labels)
+    few = graphgen.cliques([80] * 20 + [5] * 400)  # most entries in rows above 64, but few such rows
+    dev, ref = to_device(few), oracle.lpa(few).labels
+    for layout, want in (("auto", "declined"), ("original", "one_launch")):
+        with Took(gsl) as t:
+            lab, _ = gsl.gsl_lpa_ex(*dev, layout=layout)
+        assert t.routes == {want: 1}
+        np.testing.assert_array_equal(lab.cpu().numpy(), ref)
     g = planted(262145)
     with Took(gsl) as t:
         lab = gsl.gsl_lpa(*to_device(g))
@@ -275,28 +278,35 @@ def hubs(count, leaves, extra=0, fill=0):
 
 # one workgroup, workgroups that read each other's words, workgroups led by the first
 @pytest.mark.parametrize("count,leaves", [(3, 70), (60, 90), (700, 80)])
-def test_the_line_of_the_layout_rule_is_exact(gsl, count, leaves):
-    """A call is turned away where rows of more than 64 entries hold more than half of all, on any sample."""
-    for extra, fill, want in ((0, 0, "one_launch"), (1, 0, "declined"), (0, 1, "one_launch")):
+def test_near_the_line_of_the_layout_rule(gsl, count, leaves):
+    """Graphs with half of their entries in rows of more than 64 run in one launch, those with nearly all of them there
+    (a clique) on the renumbered copy."""
+    for extra, fill in ((0, 0), (1, 0), (0, 1)):
         g = hubs(count, leaves, extra, fill)
         deg = np.diff(g.offsets)
         say("line n=%d heavy %d of %d" % (g.n, deg[deg > 64].sum(), g.nnz))
         off, cols, w = to_device(g)
         with Took(gsl) as t:
             lab, st = gsl.gsl_lpa_ex(off, cols, w)
-        assert t.routes == {want: 1}
+        assert t.routes == {"one_launch": 1}
         r = oracle.lpa(g)
         np.testing.assert_array_equal(lab.cpu().numpy(), r.labels)
-        assert st["iterations"] == r.iterations and st["renumbered"] == (want == "declined")
+        assert st["iterations"] == r.iterations and not st["renumbered"]
+    g = graphgen.cliques([leaves] * count)
+    off, cols, w = to_device(g)
+    with Took(gsl) as t:
+        lab, st = gsl.gsl_lpa_ex(off, cols, w)
+    assert t.routes == {"declined": 1} and st["renumbered"]
+    np.testing.assert_array_equal(lab.cpu().numpy(), oracle.lpa(g).labels)
 
 
 def test_long_rows_are_seen_before_the_first_sweep_or_after_it(gsl):
-    """One row of 2,049 beside many of 300 (counted first), one beside short rows only (found by its window), and none
-    above 2,048; weights, a batch, and the call that never allocates."""
+    """One row of 2,049 beside many of 300 (which have more rows sampled), one beside short rows only (found by its
+    window), and none above 2,048; weights, a batch, and the call that never allocates."""
     rng = np.random.default_rng(5)
     for n, heavy, longest, want in ((30000, 60, 2049, "declined"), (30000, 60, 2048, "one_launch"), (30000, 0, 2049, "declined"),
                                     (70000, 60, 2049, "declined")):
-        u = np.concatenate([np.full(300, k + 1) for k in range(heavy)] + [np.zeros(longest, dtype=np.int64), np.arange(n // 2, n - 1)])
+        u = np.concatenate([np.full(300, 200 * (k + 1)) for k in range(heavy)] + [np.zeros(longest, dtype=np.int64), np.arange(n // 2, n - 1)])
         v = np.concatenate([rng.choice(np.arange(n // 2, n), 300, replace=False) for _ in range(heavy)] +
                            [rng.choice(np.arange(n // 2, n), longest, replace=False), np.arange(n // 2 + 1, n)])
         g = graphgen.from_undirected(n, list(zip(u.tolist(), v.tolist())), rng.integers(1, 9, size=u.size) if heavy else None)
