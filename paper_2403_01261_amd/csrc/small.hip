@@ -96,6 +96,8 @@ struct Shared {
   // kLanes lanes, of kGroup lanes, longer ones
   unsigned int cnt[3][4];
   unsigned int events;
+  int32_t gone;              // batches: the graph whose changes are summed here until the workgroup
+  unsigned int gsum;         // comes to another or the sweep ends
   unsigned int tstat[kNumTiers][kSmallTierFields];
   unsigned long long red[NW], red2[NW];
   unsigned int acc[kMeetingCopies][2];  // a meeting's sums (meeting_copy): changed vertices, events
@@ -484,6 +486,15 @@ __device__ __forceinline__ void long_row(const SmallArgs &a, Shared<BLOCK> &s, c
     row_count(a, s, m, (unsigned int)d, ch);
 }
 
+// Thread 0: the summed changes of graph s.gone to its counter.
+template <int BLOCK>
+__device__ __forceinline__ void small_graph_changes(const SmallArgs &a, Shared<BLOCK> &s) {
+  if (s.gsum)
+    __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.gdn) + s.gone, (unsigned long long)s.gsum,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  s.gsum = 0;
+}
+
 // One window of BLOCK / kLanes consecutive vertices in one sweep; rows that
 // need more lanes are packed and follow.  `r` holds the window's rows
 // (`resident`) or just their bounds.
@@ -503,6 +514,13 @@ __device__ __forceinline__ void small_window(const SmallArgs &a, Shared<BLOCK> &
   }
   bool take = on && d > 0;
   if (threadIdx.x < 3) s.qn[threadIdx.x] = 0;
+  if (BLOCK != kOneBlock && a.gdn && threadIdx.x == 0) {  // a batch is never one workgroup of its own
+    const int32_t g = a.gid[base];
+    if (g != s.gone) {
+      small_graph_changes(a, s);
+      s.gone = g;
+    }
+  }
   if (lead) s.chg[t] = 0;
   __syncthreads();
   if (first && a.init) {
@@ -582,17 +600,24 @@ __device__ __forceinline__ void small_window(const SmallArgs &a, Shared<BLOCK> &
     }
     __syncthreads();
   }
-  if (a.gdn) {
-    // changes per graph of a batch: one atomic per run of vertices of a graph
+  if (BLOCK != kOneBlock && a.gdn) {
+    // changes per graph of a batch, by runs of vertices of a graph: those of the
+    // window's first graph meet in LDS, one atomic for all of the sweep's (with
+    // one per run a batch of four graphs, 260,000 vertices in all that keep
+    // changing, took 2,160 us a call)
     const bool c = lead && s.chg[t];
     unsigned long long pending = __ballot(c);
     const int32_t g = c ? a.gid[r.v] : -1;
     while (pending) {
       const int32_t lg = __shfl(g, __ffsll((long long)pending) - 1);
       const unsigned long long same = __ballot(c && g == lg);
-      if (lane == 0)
-        __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.gdn) + lg, (unsigned long long)__popcll(same),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (lane == 0) {
+        if (lg == s.gone)
+          atomicAdd(&s.gsum, (unsigned int)__popcll(same));
+        else
+          __hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(a.gdn) + lg, (unsigned long long)__popcll(same),
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       pending &= ~same;
     }
   }
@@ -900,7 +925,10 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
   if (resident) row_slice<W, V4>(a, r, true);
   for (int i = threadIdx.x; i < kTable; i += BLOCK) s.tab[i] = kEmptySlot;
   for (int i = threadIdx.x; i < F; i += BLOCK) (&s.tstat[0][0])[i] = 0;
-  if (threadIdx.x == 0) s.events = 0;
+  if (threadIdx.x == 0) {
+    s.events = s.gsum = 0;
+    s.gone = -1;
+  }
   if (threadIdx.x < 12) s.cnt[threadIdx.x / 4][threadIdx.x % 4] = 0;
   SweepCtrl c = a.ctrl;
   const int it0 = c.it;
@@ -936,6 +964,7 @@ __global__ __launch_bounds__(BLOCK, W || BLOCK == kOneBlock ? 2 : 4) void small_
       small_window<BLOCK, W, V4>(a, s, md, base, it == it0, r, resident);
       __syncthreads();  // the next window clears the queues and change flags
     }
+    if (!kOne && a.gdn && threadIdx.x == 0) small_graph_changes(a, s);
     const uint32_t payload = ((s.cnt[0][2] + s.cnt[1][2] + s.cnt[2][2]) & kDnMask) | s.events;
     if (threadIdx.x == 0) {
       const uint32_t processed = s.cnt[0][0] + s.cnt[1][0] + s.cnt[2][0], edges = s.cnt[0][1] + s.cnt[1][1] + s.cnt[2][1];

@@ -346,3 +346,17 @@ def test_the_last_calls_variants(gsl):
     assert windows and took[0] == 16
     gsl.gsl_lpa_f32(g[0], g[1], torch.ones(g[1].numel(), device="cuda"))
     assert gsl.gsl_last_variants() == ([-1] * 7, False)
+
+
+def test_few_graphs_that_keep_changing(gsl):
+    """A workgroup's changes of one graph are counted together: graphs of many windows, of parts of one, and both."""
+    sizes = [40000, 37, 200, 129, 100000, 64, 64, 1, 70000]
+    gs = [graphgen.planted(n, max(1, n // 400), 0.02, n, 3 + n % 5) for n in sizes]
+    dev = [to_device(g) for g in gs]
+    with Took(gsl) as t:
+        labels, sweeps, _ = gsl.gsl_lpa_graphs(dev, 20, 0.0)
+    assert t.routes == {"one_launch": 1}
+    for g, lab, ran in zip(gs, labels, sweeps):
+        r = oracle.lpa(g, 20, 0.0)
+        np.testing.assert_array_equal(lab.cpu().numpy(), r.labels)
+        assert ran == r.iterations
