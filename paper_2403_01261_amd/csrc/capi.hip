@@ -1054,6 +1054,11 @@ bool wants_clusters(int64_t n, int64_t nnz, int32_t max_iters, const Counters &p
 // vertices 1.98 -> 2.21, 2.90 -> 2.98, 3.72 -> 3.79 and 4.17 -> 4.07 ms, 8 M 5.8 ->
 // 5.2; batches, whose vertices also look up their graph, 5.6, 6.4 and 6.9 M vertices
 // 5.94 -> 6.05, 6.73 -> 6.84 and 7.12 -> 7.10, 15 and 30 M 14.7 -> 13.9 and 28.8 -> 25.7.
+// A batch, whose graphs lie together, takes the tiles without a sample, but not
+// where they are too few for the device's CUs (4,096 vertices each): 0.16, 0.18,
+// 0.57 and 0.69 M weighted vertices 1,025, 1,205, 1,910 and 2,422 us with, 949, 1,169,
+// 1,889 and 2,413 without; 1.06 and 2.1 M 2,823 and 4,089 with, 2,830 and 4,160 without.
+constexpr int64_t kTileMinVertices = int64_t(3) << 18;
 constexpr int64_t kWindowMinVertices = int64_t(11) << 19, kWindowMinBatch = int64_t(1) << 23;
 bool is_near(const Counters &plan) { return plan.spread[0] > 0 && 2 * plan.spread[2] > plan.spread[0]; }
 
@@ -1460,7 +1465,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   } else if (o.split) {
     HIP_TRY(gsl::launch_split(offsets, cols, n, C, s.parent, labels_out, s.list, plan.tier_count,
                               plan.tier_start, nullptr, nullptr, n, s.rep, s.sigma, clipped(cfg, plan), st,
-                              batch != nullptr || is_near(plan)));
+                              n >= kTileMinVertices && (batch != nullptr || is_near(plan))));
   }
   if (batch && (rc = finish_batch(s, st, batch, n, labels_out))) return rc;
   if (timed) HIP_TRY(hipEventRecord(s.ev[3], st));
