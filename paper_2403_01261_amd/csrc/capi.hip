@@ -688,6 +688,12 @@ struct Launch {
 // faster here throughout: 262,144 vertices 543 us instead of 843).
 constexpr int64_t kSmallMaxVertices = int64_t(1) << 18, kSmallMaxWeighted = int64_t(1) << 17;
 constexpr int64_t small_vertices(bool weighted) { return weighted ? kSmallMaxWeighted : kSmallMaxVertices; }
+// A graph of a weighted batch counts as 16 vertices more: workgroup 0 decides on
+// every graph after each sweep, which the few sweeps of thousands of tiny weighted
+// graphs do not pay back (4,096 of 10 - 60 vertices, 115,000 in all: 1,008 us a call
+// in one launch, 943 on the general path; unit weights 884 and 873, and 4,096 of 16
+// vertices 815 and 1,160 with weights).
+constexpr int64_t small_size(int64_t n, int64_t graphs, bool weighted) { return n + (weighted ? 16 * graphs : 0); }
 constexpr int64_t kSmallMaxEntries = int64_t(1) << 24;
 constexpr int64_t kSmallMaxGraphs = 4096;
 // Ticks (100 MHz) after which a workgroup's wait for the others gives up: 5 ms,
@@ -1087,7 +1093,7 @@ int lpa_impl(Scratch &s, hipStream_t st, const int64_t *offsets, const int32_t *
   const HubLimits hub_lim = current_hub_limits();
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
-  if (n <= small_vertices(weights != nullptr) && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
+  if (small_size(n, batch ? batch->graphs : 0, weights != nullptr) <= small_vertices(weights != nullptr) && max_iters >= 1 && max_iters <= gsl::kSmallMaxSweeps && !o.timing && !f32 &&
       !o.async_sweeps && o.layout != 1 && (!batch || (batch->graphs <= kSmallMaxGraphs && !batch->general)) &&
       is_default_tiers(cfg)) {
     rc = small_impl(s, st, offsets, cols, weights, n, max_iters, tolerance, o, stats, labels_out, batch, dev);

@@ -348,6 +348,39 @@ def test_the_last_calls_variants(gsl):
     assert gsl.gsl_last_variants() == ([-1] * 7, False)
 
 
+def test_batches_of_thousands_of_graphs(gsl):
+    """Up to 4,096 graphs share one launch; thousands with weights count as larger."""
+    b = graphgen.batched_planted(4096, 5, nmin=2, nmax=40, kmin=1, kmax=3)
+    off, cols, _ = to_device(b)
+    vb, eb = torch.from_numpy(b.vtx_base).cuda(), torch.from_numpy(b.edge_base).cuda()
+    w = torch.ones_like(cols)
+    say("batch of 4,096: %d vertices" % b.n)
+    assert b.n + 16 * 4096 <= 1 << 17
+    with Took(gsl) as t:
+        plain = gsl.gsl_lpa_batched(vb, eb, off, cols)
+        weighted = gsl.gsl_lpa_batched(vb, eb, off, cols, w)
+    assert t.routes == {"one_launch": 2}
+    n = (1 << 17) - 16 * 4096 + 4096  # vertices beyond the line for weights, 4,096 graphs
+    size = n // 4096
+    g = graphgen.cliques([size] * 4096)
+    base = np.arange(4097, dtype=np.int64) * size
+    up = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    local = (g.cols - np.repeat(np.repeat(base[:-1], size), np.diff(g.offsets))).astype(np.int32)
+    args = up(base), up(g.offsets[base]), up(g.offsets), up(local)
+    with Took(gsl) as t:
+        a = gsl.gsl_lpa_batched(*args, torch.ones(g.nnz, dtype=torch.int32, device="cuda"))
+    assert t.routes == {}
+    with Took(gsl) as t:
+        c = gsl.gsl_lpa_batched(*args)
+    assert t.routes == {"one_launch": 1}
+    assert torch.equal(a[0], c[0]) and torch.equal(a[1], c[1])
+    assert torch.equal(plain[0], weighted[0])
+    for k in range(0, 4096, 97):
+        r = oracle.lpa(b.subgraph(k))
+        np.testing.assert_array_equal(plain[0][int(vb[k]):int(vb[k + 1])].cpu().numpy(), r.labels, err_msg="graph %d" % k)
+        assert plain[1][k] == r.iterations
+
+
 def test_few_graphs_that_keep_changing(gsl):
     """A workgroup's changes of one graph are counted together: graphs of many windows, of parts of one, and both."""
     sizes = [40000, 37, 200, 129, 100000, 64, 64, 1, 70000]
