@@ -114,7 +114,15 @@ __global__ __launch_bounds__(kModBlock) void mod_rows(const int64_t *__restrict_
       const int64_t vb = __shfl(b, src, kWave), ve = __shfl(e, src, kWave);
       const int32_t vc = __shfl(c, src, kWave);
       unsigned long long k = 0, in = 0;
-      mod_entries(cols, w, C, vb + lane, ve, kWave, vc, k, in);
+      if (ve - vb <= kWave) {  // one entry a lane: nothing to have on the way
+        const int64_t p = vb + lane;
+        const int32_t j = p < ve ? cols[p] : -1;
+        const uint32_t we = p < ve ? (w ? w[p] : 1u) : 0u;
+        k = we;
+        in = j >= 0 && C[j] == vc ? we : 0u;
+      } else {
+        mod_entries(cols, w, C, vb + lane, ve, kWave, vc, k, in);
+      }
       k = wave_sum(k);
       in = wave_sum(in);
       if (lane == 0) {
