@@ -190,7 +190,6 @@ struct gsl_context {
 };
 
 namespace {
-// One graph of a session (host side).
 // The rows of a graph that matter to the one launch (launch_graph_entries).
 struct LongRows {
   int64_t n = 0, longest = 0;
@@ -210,6 +209,7 @@ struct LongRows {
   }
 };
 
+// One graph of a session (host side).
 struct SessionSlot {
   bool live = false;
   int64_t ticket = -1;

@@ -26,8 +26,8 @@
 //  - The split needs three more meetings: link, flatten, hook, write out.
 //
 // Measured (MI355X, whole calls, general path -> here): planted graphs of 200
-// vertices 559 -> 87 us (16 sweeps), 10,000 vertices 613 -> 145 us, 28,901
-// vertices (no allocation) 647 -> 187 us, 131,072 weighted vertices 855 -> 667
+// vertices 596 -> 83 us (16 sweeps), 10,000 vertices 626 -> 146 us, 28,901
+// vertices (no allocation) 653 -> 185 us, 131,072 weighted vertices 855 -> 667
 // us.  All device functions are inlined and no member of the arguments is
 // indexed by a variable: a call by reference or such an index moves the
 // arguments to scratch memory, where every use reads them (some 35 us a call).  A

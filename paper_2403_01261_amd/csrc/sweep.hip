@@ -74,11 +74,12 @@ __device__ __forceinline__ void flush_counts(const SweepArgs &a, const LocalCoun
 // W: weighted rows; without it every entry weighs 1.
 //
 // The sweep waits on its vector memory instructions (row loads and label
-// gathers, one lane access each; the texture addresser is busy 85 % of the
-// time): with V4 a row comes in as 16-byte words (load_row), each label is
-// loaded into the register that held its column, and with O32 (fewer than 2^30
-// vertices) the gather address is the label array's base plus a 32-bit byte
-// offset, which needs no 64-bit address registers.  A sparse sweep after few
+// gathers, one lane access each; the texture addresser is busy 91 % of a dense
+// sweep of planted graphs where the labels are not in LDS): with V4 a row comes
+// in as 16-byte words (load_row), each label is loaded into the register that
+// held its column, and with O32 (fewer than 2^30 vertices) the gather address is
+// the label array's base plus a 32-bit byte offset, which needs no 64-bit
+// address registers.  A sparse sweep after few
 // changes walks the frontier instead of the tier list.
 //
 // In the loop's first sweep every label is its vertex's id (IDS), so a row
